@@ -100,7 +100,9 @@ def draw(rng):
                  ragged=ragged)
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """Yields ("slid", k, v) for the tokens the window has slid past, ("chunk", k, v) for each cached chunk, ("new", k, v)
+    for the chunk that run() appends and ("query", q, k_cur, v_cur), in this order, where the case has them."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(int(seed))
     heads, dim, io = case["heads"], case["dim"], torch.bfloat16 if case["io"] == "bf16" else torch.float32
@@ -116,30 +118,43 @@ def prepare(case, seed):
     def kv(tokens):   # values that BF16 holds, in the tensors' type
         return (normal(tokens, heads) * gain).to(torch.bfloat16).to(io), normal(tokens, heads).to(io)
 
-    # Tokens in the cache before the chunk that run() appends (all of the window where it appends none).
-    ahead = case["cached"] - (case["chunk"] if case["call"] in ("step", "append") else 0)
-    ragged, first = case["ragged"], min(case["chunk"], ahead)
-    capacity = max(case["cached"] + 64, ragged + first)
+    ahead = _ahead(case)
+    if case["ragged"] and ahead:       # the window has slid: older tokens came before its first chunk and are gone
+        yield ("slid", *kv(case["ragged"]))
+    for start in range(0, ahead, case["chunk"]):
+        yield ("chunk", *kv(min(case["chunk"], ahead - start)))
+    if case["call"] in ("step", "append"):
+        yield ("new", *kv(case["chunk"]))
+    if case["call"] != "append":
+        yield ("query", normal(case["rows"], heads * case["ratio"]).to(io), *kv(case["current"]))
+
+
+def _ahead(case):   # tokens in the cache before the chunk that run() appends (all of the window where it appends none)
+    return case["cached"] - (case["chunk"] if case["call"] in ("step", "append") else 0)
+
+
+def prepare(case, seed):
+    heads, ragged, ahead = case["heads"], case["ragged"], _ahead(case)
+    capacity = max(case["cached"] + 64, ragged + min(case["chunk"], ahead))
     cache = kvq.Cache(kvq.make_desc(
-        heads, dim, case["bits"], capacity, kvq.KVQ_BF16 if case["io"] == "bf16" else kvq.KVQ_FP32, case["group"], 1,
+        heads, case["dim"], case["bits"], capacity, kvq.KVQ_BF16 if case["io"] == "bf16" else kvq.KVQ_FP32, case["group"], 1,
         kvq.KVQ_META_FP32 if case["meta"] == "fp32" else kvq.KVQ_META_FP8_BF16,
         kvq.KVQ_KEYS_PER_TOKEN if case["axis"] == "token" else kvq.KVQ_KEYS_PER_CHANNEL), DEV)
     cache.storage.zero_()
-    state = {"case": case, "cache": cache}
-    if ragged and ahead:       # the window has slid: older tokens came before its first chunk and are gone
-        kvq.kvq_quantize_append(cache, *kv(ragged))
-    for start in range(0, ahead, case["chunk"]):
-        kvq.kvq_quantize_append(cache, *kv(min(case["chunk"], ahead - start)))
-        if ragged and start == 0:
-            kvq.kvq_cache_evict(cache, ragged)
-    state["base"] = ahead
-    if case["call"] in ("step", "append"):
-        state["k"], state["v"] = kv(case["chunk"])
-    if case["call"] != "append":
-        q = normal(case["rows"], heads * case["ratio"]).to(io)
-        state.update(q=q, out=torch.empty_like(q))
-        state["k_cur"], state["v_cur"] = kv(case["current"])
-        state["mass"] = torch.empty((heads * case["ratio"], case["rows"]), dtype=torch.float32, device=DEV)
+    state = {"case": case, "cache": cache, "base": ahead}
+    slid = 0
+    for what, *tensors in _inputs(case, seed):
+        if what == "query":
+            q, state["k_cur"], state["v_cur"] = tensors
+            state.update(q=q, out=torch.empty_like(q))
+            state["mass"] = torch.empty((heads * case["ratio"], case["rows"]), dtype=torch.float32, device=DEV)
+        elif what == "new":
+            state["k"], state["v"] = tensors
+        else:
+            kvq.kvq_quantize_append(cache, *tensors)
+            if what == "chunk" and slid:
+                kvq.kvq_cache_evict(cache, slid)
+            slid = ragged if what == "slid" else 0
     return state
 
 
@@ -182,3 +197,71 @@ def tolerance(case):
     if case["io"] == "fp32":
         return {"rel": 1e-5, "max": 1e-4}
     return {"rel": 1e-2, "max": 0.15} if case["dim"] == 128 else {"rel": 7e-3, "max": 2e-2}
+
+
+def _round_trip(x, bits, group, meta, per_channel, dim):
+    """A chunk [tokens][heads][dim] after rotation, quantization and reconstruction, with the steps [tokens][heads][group
+    or 1] (all in the rotated basis): asymmetric round-to-nearest over groups of `group` channels of a token, or over the
+    chunk's tokens for each channel."""
+    levels, norm = 2.0 ** bits - 1.0, dim ** -0.5
+    u = x.double() @ _hadamard(dim)
+    u = u if per_channel else u.unflatten(2, (dim // group, group))
+    axis = 0 if per_channel else 3
+    lo, hi = u.amin(axis, keepdim=True), u.amax(axis, keepdim=True)
+    lo, hi = torch.where(hi == lo, lo.clamp(max=0), lo), torch.where(hi == lo, hi.clamp(min=0), hi)
+    step = (hi - lo) / levels * norm
+    if meta == "fp8":          # the smallest E4M3 value that covers the range; the nearest BF16 zero-point
+        ulp = torch.exp2(torch.floor(torch.log2(step.clamp(2.0 ** -6, 448.0))) - 3)
+        step = torch.ceil(step.clamp(max=448.0) / ulp) * ulp
+    inv = torch.where(step > 0, norm / step, torch.zeros_like(step))
+    zero = -torch.round(lo * inv)
+    if meta == "fp8":
+        zero = zero.to(torch.bfloat16).double()
+    else:
+        step = step.float().double()
+    code = (torch.round(u * inv) + zero).clamp(0, levels)
+    return ((code - zero) * step).reshape(x.shape), (step if per_channel else step.squeeze(3)).expand(x.shape[0], -1, -1)
+
+
+def _hadamard(dim):
+    h = torch.ones((1, 1), dtype=torch.float64, device=DEV)
+    while h.shape[0] < dim:
+        h = torch.cat([torch.cat([h, h], 1), torch.cat([h, -h], 1)], 0)
+    return h
+
+
+def exact(case, seed):
+    """Quantizer and attention in 64 bits: scores of the cached keys less softmax_scale^2 / 24 * sum over groups of
+    step^2 * |q of the group|^2, one softmax over cached and current keys.  None for appended bytes."""
+    if case["call"] == "append":
+        return None
+    dim, per_channel = case["dim"], case["axis"] == "channel"
+    cached = []
+    for what, *tensors in _inputs(case, seed):
+        if what == "query":
+            q, k_cur, v_cur = tensors
+        elif what != "slid":
+            k, step = _round_trip(tensors[0], case["bits"], case["group"], case["meta"], per_channel, dim)
+            v, _ = _round_trip(tensors[1], case["bits"], case["group"], case["meta"], False, dim)
+            cached.append((k.float(), v.float(), step.float()))   # products of a small integer and a stored step
+    k_hat, v_hat, step = (torch.cat(t) for t in zip(*cached))
+    rows, heads_q, current, scale = case["rows"], case["heads"] * case["ratio"], case["current"], dim ** -0.5
+    rot = _hadamard(dim) * scale
+    out = torch.empty((rows, heads_q, dim), dtype=torch.float64, device=DEV)
+    mass = torch.empty((heads_q, rows), dtype=torch.float64, device=DEV)
+    for h in range(heads_q):
+        g = h // case["ratio"]
+        k_s, v_s, step2 = k_hat[:, g].double(), v_hat[:, g].double(), step[:, g].double() ** 2
+        k_r, v_r = k_cur[:, g].double(), v_cur[:, g].double()
+        for r in range(0, rows, 1024):
+            x = q[r:r + 1024, h].double()
+            y = x @ rot
+            nu = (y * y).unflatten(1, (step2.shape[1], dim // step2.shape[1])).sum(2)
+            s = torch.cat([y @ k_s.T * scale - nu @ step2.T * (scale * scale / 24.0), x @ k_r.T * scale], 1)
+            if case["call"] == "prefill":
+                row = torch.arange(r, r + x.shape[0], device=DEV)[:, None] + (current - rows)
+                s[:, k_s.shape[0]:].masked_fill_(torch.arange(current, device=DEV)[None, :] > row, float("-inf"))
+            p = torch.softmax(s, 1)
+            out[r:r + 1024, h] = p[:, :k_s.shape[0]] @ v_s @ rot + p[:, k_s.shape[0]:] @ v_r
+            mass[h, r:r + 1024] = p[:, :k_s.shape[0]].sum(1)
+    return {"out": out, "mass": mass}
