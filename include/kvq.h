@@ -229,6 +229,22 @@ kvq_status kvq_chunk_attention_ex(const kvq_cache *cache, int64_t cache_start, i
                                   float softmax_scale, int correction, const kvq_attention_opts *opts,
                                   void *out, float *mass_cached, void *hip_stream);
 
+/*
+ * kvq_chunk_attention_ex with a work space.  Calls whose row blocks do not fill the GPU (few heads, few query rows, a
+ * partly filled last round) split the key range of a row block over several workgroups; their partial results need device
+ * memory, which the library does not allocate.  workspace: device memory, 256-byte aligned, used by this call only until
+ * its work on the stream is done (calls that overlap need a work space each); NULL with 0 bytes, or fewer bytes than
+ * kvq_attention_workspace_bytes returns for the call: nothing is split.  Results agree within the tolerance of the path
+ * either way.  kvq_attention_workspace_bytes returns 0 where a call is not split.
+ */
+kvq_status kvq_chunk_attention_ws(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,
+                                  const void *q, const void *k_cur, const void *v_cur,
+                                  int64_t m, int64_t n_cur, int64_t stride_token, int64_t stride_head,
+                                  float softmax_scale, int correction, const kvq_attention_opts *opts,
+                                  void *out, float *mass_cached, void *workspace, size_t workspace_bytes, void *hip_stream);
+size_t kvq_attention_workspace_bytes(const kvq_cache *cache, int64_t cache_start, int64_t cache_len, int64_t m,
+                                     int64_t n_cur, int q_heads_per_kv_head);
+
 /* Same contract as kvq_chunk_attention, but always runs the fp32 vector-ALU kernel (Alg. 1 in
  * single precision, no matrix cores): slow, for reference-precision results on any cache. */
 kvq_status kvq_chunk_attention_fp32(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,

@@ -24,7 +24,7 @@ EXPORTED = (
     "kvq_cache_bytes", "kvq_cache_create", "kvq_cache_destroy", "kvq_cache_len", "kvq_cache_reset",
     "kvq_cache_truncate", "kvq_cache_evict", "kvq_cache_set_rotation_signs", "kvq_quantize_append",
     "kvq_quantize_append_static", "kvq_chunk_attention", "kvq_chunk_attention_fp32",
-    "kvq_chunk_attention_ex", "kvq_attention_diagnostics",
+    "kvq_chunk_attention_ex", "kvq_chunk_attention_ws", "kvq_attention_workspace_bytes", "kvq_attention_diagnostics",
     "kvq_cache_export", "kvq_status_string", "kvq_version",
 )
 
@@ -76,6 +76,9 @@ def lib() -> ctypes.CDLL:
     L.kvq_chunk_attention.argtypes = att
     L.kvq_chunk_attention_fp32.argtypes = att
     L.kvq_chunk_attention_ex.argtypes = att[:12] + [ctypes.POINTER(kvq_attention_opts)] + att[12:]
+    L.kvq_chunk_attention_ws.argtypes = att[:12] + [ctypes.POINTER(kvq_attention_opts)] + att[12:14] + [vp, ctypes.c_size_t, vp]
+    L.kvq_attention_workspace_bytes.argtypes = [vp, i64, i64, i64, i64, ci]
+    L.kvq_attention_workspace_bytes.restype = ctypes.c_size_t
     L.kvq_attention_diagnostics.argtypes = [vp, i64, i64, vp, vp, vp, vp, vp, i64, i64, i64, i64, cf, ci, vp, vp]
     L.kvq_cache_export.argtypes = [vp, ci, i64, i64, vp, vp, vp, vp]
     L.kvq_status_string.argtypes = [ci]
@@ -222,6 +225,34 @@ def kvq_quantize_append_static(cache: Cache, k: torch.Tensor, v: torch.Tensor,
                                             _stream(stream)), "kvq_quantize_append_static")
 
 
+def _workspace(cache: Cache, nbytes: int, stream: Optional[torch.cuda.Stream]) -> Optional[torch.Tensor]:
+    """Device memory for the partial results of one call, from the allocator pool of the stream that the call runs on: it
+    may be reused by later work on that stream as soon as the tensor is gone.  None where there is none to be had: the
+    call then runs unsplit."""
+    dev = cache.storage.device
+    on = torch.cuda.current_stream() if stream is None else stream
+    if on.device != dev:
+        return None
+    try:
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    except torch.OutOfMemoryError:
+        return None
+
+
+def _launch(cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
+            opts, out, mass_cached, stream, where: str) -> None:
+    nbytes = lib().kvq_attention_workspace_bytes(cache.handle, int(cache_start), int(cache_len), q.shape[0], n_cur,
+                                                 opts.q_heads_per_kv_head if opts is not None else 1)
+    ws = _workspace(cache, nbytes, stream) if nbytes else None
+    _check(lib().kvq_chunk_attention_ws(
+        cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur), _ptr(v_cur), q.shape[0], n_cur, st, sh,
+        float(softmax_scale), int(correction), None if opts is None else ctypes.byref(opts), out.data_ptr(),
+        _ptr(mass_cached), _ptr(ws), 0 if ws is None else nbytes, _stream(stream)), where)
+
+
 def _attention(fn, cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_cur, softmax_scale, correction,
                out, mass_cached, stream):
     st, sh = _tok_head_strides(q)
@@ -240,6 +271,9 @@ def _attention(fn, cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_c
         raise ValueError("q must be in the cache's io dtype")
     if mass_cached is not None and (mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous()):
         raise ValueError("mass_cached must be a contiguous float32 [heads][m] tensor")
+    if fn is None:
+        return _launch(cache, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction, None, out,
+                       mass_cached, stream, "kvq_chunk_attention")
     _check(fn(cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur), _ptr(v_cur), q.shape[0],
               n_cur, st, sh, float(softmax_scale), int(correction), out.data_ptr(), _ptr(mass_cached),
               _stream(stream)), "kvq_chunk_attention")
@@ -249,7 +283,7 @@ def kvq_chunk_attention(cache: Cache, cache_start: int, cache_len: int, q: torch
                         k_cur: Optional[torch.Tensor], v_cur: Optional[torch.Tensor], out: torch.Tensor,
                         mass_cached: Optional[torch.Tensor] = None, softmax_scale: float = 0.0,
                         correction: int = 1, stream: Optional[torch.cuda.Stream] = None) -> None:
-    _attention(lib().kvq_chunk_attention, cache, cache_start, cache_len, q, k_cur, v_cur, softmax_scale, correction,
+    _attention(None, cache, cache_start, cache_len, q, k_cur, v_cur, softmax_scale, correction,
                out, mass_cached, stream)
 
 
@@ -280,10 +314,8 @@ def kvq_chunk_attention_ex(cache: Cache, cache_start: int, cache_len: int, q: to
     st, sh = _tok_head_strides(kv) if kv is not None and kv.shape[0] > 0 else (cache.desc.num_heads * cache.desc.head_dim, cache.desc.head_dim)
     opts = kvq_attention_opts(q.shape[1] // cache.desc.num_heads, int(bool(causal)), qst, qsh)
     n_cur = 0 if k_cur is None else k_cur.shape[0]
-    _check(lib().kvq_chunk_attention_ex(cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur),
-                                        _ptr(v_cur), q.shape[0], n_cur, st, sh, float(softmax_scale), int(correction),
-                                        ctypes.byref(opts), out.data_ptr(), _ptr(mass_cached), _stream(stream)),
-           "kvq_chunk_attention_ex")
+    _launch(cache, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction, opts, out,
+            mass_cached, stream, "kvq_chunk_attention_ex")
 
 
 def kvq_attention_diagnostics(cache: Cache, cache_start: int, cache_len: int, q: torch.Tensor,

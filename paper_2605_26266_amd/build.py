@@ -35,6 +35,7 @@ SOURCES = {
     "kvq_attention_simt.hip": [],
     "kvq_attention_mfma.hip": [],
     "kvq_attention_mfma_group.hip": [],
+    "kvq_attention_merge.hip": [],
 }
 
 

@@ -82,6 +82,46 @@ bool tensor_ok(const void *p, int64_t stride_token, int64_t stride_head, int hea
     return true;
 }
 
+// How a matrix-core call of `units` 256-row blocks and `tiles` 32-key tiles per block is laid over the 256 compute units
+// (one workgroup each).  The blocks that fill whole rounds of the chip stay whole; the key ranges of the rest are cut into
+// the number of pieces with the shortest estimated time, in tiles (about 1 us): rounds * (tiles per piece + what a
+// workgroup pays once: query preparation, rotation back, writing its result) + the merge.
+// The constants follow measurements: 8 heads x 1024 rows x (4096 + 1024) keys, 32 blocks: 208 / 133 / 96 / 77.5 / 112 / 180 us
+// with 1 / 2 / 4 / 8 / 12 / 32 pieces; 32 query heads x 1 row x (8192 + 64) keys: 366 / 112 / 70 / 90 / 130 us with 1 / 4 /
+// 8 / 16 / 32; 24 heads x 4680 rows x (28080 + 4680) keys, 200 blocks after a full round: 2182 / 2286 / 2146 / 2219 / 2331 us
+// with 1 / 2 / 5 / 6 / 9.
+kvq::SplitArgs plan_split(int64_t m, int64_t q_heads, int64_t tiles)
+{
+    constexpr int kComputeUnits = 256, kMaxSplits = 64;
+    constexpr double kFixed = 30.0, kMerge = 6.0, kMergePerSplit = 0.12, kMergePerBlock = 0.0025;
+    kvq::SplitArgs sp = {};
+    sp.row_blocks = (int32_t)((m + kvq::kSplitRows - 1) / kvq::kSplitRows);
+    sp.part_blocks = (int32_t)(m < kvq::kSplitRows ? (m + 31) / 32 : kvq::kSplitRows / 32);
+    const int64_t units = sp.row_blocks * q_heads, rest = units % kComputeUnits;
+    int64_t best = 1;
+    double best_cost = (double)tiles + kFixed;
+    for (int64_t s = 2; rest > 0 && s <= kMaxSplits && s <= tiles && rest * s <= kvq::kMaxPieces; ++s) {
+        const int64_t rounds = (rest * s + kComputeUnits - 1) / kComputeUnits;
+        const double cost = (double)rounds * ((double)((tiles + s - 1) / s) + kFixed) + kMerge +
+                            kMergePerSplit * (double)s + kMergePerBlock * (double)(rest * s * sp.part_blocks);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = s;
+        }
+    }
+    sp.splits = (int32_t)best;
+    sp.pieces = (int32_t)(best > 1 ? rest * best : 0);
+    sp.whole = (int32_t)(best > 1 ? units - rest : units);
+    return sp;
+}
+
+// Tiles of a call's key range: cached tiles that the window touches and tiles of the current block.
+int64_t key_tiles(int64_t start, int64_t cache_len, int64_t n_cur)
+{
+    const int64_t cached = cache_len > 0 ? (start + cache_len - 1) / kvq::kTileTokens - start / kvq::kTileTokens + 1 : 0;
+    return cached + (n_cur + kvq::kTileTokens - 1) / kvq::kTileTokens;
+}
+
 }  // namespace
 
 extern "C" {
@@ -261,7 +301,8 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
                                    int64_t n_cur, int64_t stride_token, int64_t stride_head,
                                    float softmax_scale, int correction, void *out, float *mass_cached,
                                    void *hip_stream, bool force_vector, const kvq_attention_opts *opts = nullptr,
-                                   const void *k_ref = nullptr, const void *v_ref = nullptr, float *diag = nullptr)
+                                   const void *k_ref = nullptr, const void *v_ref = nullptr, float *diag = nullptr,
+                                   void *workspace = nullptr, size_t workspace_bytes = 0)
 {
     // diag != nullptr: the diagnostics call (no out / mass_cached; k_ref, v_ref hold the cached tokens unquantized)
     kvq_attention_opts o = {1, 0, stride_token, stride_head};
@@ -342,9 +383,23 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (diag) return kvq::launch_diagnostics_simt(a, k_ref, v_ref, diag, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
     const bool group_matrix_path = !force_vector && kvq::attention_mfma_group_supported(cache->view);
-    hipError_t e = matrix_path         ? kvq::launch_attention_mfma(a, s)
-                   : group_matrix_path ? kvq::launch_attention_mfma_group(a, s)
+    kvq::SplitArgs sp = {};
+    if (matrix_path || group_matrix_path) {
+        const int64_t q_heads = (int64_t)d.num_heads * o.q_heads_per_kv_head;
+        if ((m + kvq::kSplitRows - 1) / kvq::kSplitRows * q_heads > 0x7fffffff) return KVQ_ERR_HIP;
+        sp = plan_split(m, q_heads, key_tiles(a.cache_start, cache_len, n_cur));
+        if (sp.pieces > 0 && workspace_bytes < kvq::split_workspace_bytes(sp)) {   // no room for partial results: whole units
+            sp.whole += sp.pieces / sp.splits;
+            sp.splits = 1;
+            sp.pieces = 0;
+        }
+        sp.part_o = static_cast<float *>(workspace);
+        sp.part_ml = reinterpret_cast<float4 *>(sp.part_o + (size_t)sp.pieces * sp.part_blocks * 32 * 128);
+    }
+    hipError_t e = matrix_path         ? kvq::launch_attention_mfma(a, sp, s)
+                   : group_matrix_path ? kvq::launch_attention_mfma_group(a, sp, s)
                                        : kvq::launch_attention_simt(a, s);
+    if (e == hipSuccess && sp.pieces > 0) e = kvq::launch_attention_merge(a, sp, s);
     if (e == hipSuccess && (matrix_path || group_matrix_path) && a.status) {
         // A cache that has ever stored a zero-point beyond the matrix-core kernels' domain carries a flag: the launch
         // above has then returned without writing anything, and this one, which otherwise returns at once, does the work.
@@ -382,6 +437,29 @@ kvq_status kvq_chunk_attention_ex(const kvq_cache *cache, int64_t cache_start, i
 {
     return attention_common(cache, cache_start, cache_len, q, k_cur, v_cur, m, n_cur, stride_token, stride_head,
                             softmax_scale, correction, out, mass_cached, hip_stream, false, opts);
+}
+
+size_t kvq_attention_workspace_bytes(const kvq_cache *cache, int64_t cache_start, int64_t cache_len, int64_t m, int64_t n_cur,
+                                     int q_heads_per_kv_head)
+{
+    if (!cache || m <= 0 || n_cur < 0 || cache_len < 0 || cache_start < 0 || q_heads_per_kv_head < 1 || q_heads_per_kv_head > 64) return 0;
+    const kvq_cache_desc &d = cache->desc;
+    if (d.io_dtype != KVQ_BF16 || d.head_dim != 128 || cache_start + cache_len > cache->len) return 0;
+    if (m > ((int64_t)1 << 31) - 256 || n_cur > ((int64_t)1 << 31) - 256) return 0;
+    return kvq::split_workspace_bytes(plan_split(m, (int64_t)d.num_heads * q_heads_per_kv_head,
+                                                 key_tiles(cache->base + cache_start, cache_len, n_cur)));
+}
+
+kvq_status kvq_chunk_attention_ws(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,
+                                  const void *q, const void *k_cur, const void *v_cur, int64_t m,
+                                  int64_t n_cur, int64_t stride_token, int64_t stride_head,
+                                  float softmax_scale, int correction, const kvq_attention_opts *opts,
+                                  void *out, float *mass_cached, void *workspace, size_t workspace_bytes, void *hip_stream)
+{
+    if (workspace ? reinterpret_cast<uintptr_t>(workspace) % 256 != 0 : workspace_bytes != 0) return KVQ_ERR_INVALID_ARG;
+    return attention_common(cache, cache_start, cache_len, q, k_cur, v_cur, m, n_cur, stride_token, stride_head,
+                            softmax_scale, correction, out, mass_cached, hip_stream, false, opts, nullptr, nullptr, nullptr,
+                            workspace, workspace_bytes);
 }
 
 kvq_status kvq_attention_diagnostics(const kvq_cache *cache, int64_t cache_start, int64_t cache_len, const void *q,

@@ -128,7 +128,7 @@ template <int BITS> constexpr size_t lds_bytes()
 // block's correction sigma^2 / 24 * sum_c (q^_c step_c)^2.  The cached keys are therefore processed block by
 // block, the query operands prepared anew for each.
 template <int BITS, bool CORR, bool FP8META, bool PERCH = false>
-__global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionArgs a, int row_blocks)
+__global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionArgs a, SplitArgs sp)
 {
     if (cache_flagged(a.status)) return;   // the vector kernel enqueued behind this launch serves such a cache
     using St = Stage<BITS>;
@@ -141,25 +141,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
 
-    // Workgroups are handed to the 8 XCDs round-robin; keep all row blocks of all query heads of a
-    // key/value head on one XCD so that its packed cache is fetched into that XCD's L2 once.
-    int head, qhead, rblk;   // key/value head, query head, 256-row block
-    {
-        const int bid = blockIdx.x;
-        const int per_head = row_blocks * a.q_per_kv;
-        int j;
-        if ((cv.num_heads & 7) == 0) {
-            const int xcd = bid & 7;
-            j = bid >> 3;
-            head = (j / per_head) * 8 + xcd;
-        } else {
-            j = bid;
-            head = j / per_head;
-        }
-        const int local = j % per_head;
-        qhead = head * a.q_per_kv + local / row_blocks;
-        rblk = local % row_blocks;
-    }
+    const Place place = locate(a, sp);
+    const int head = place.head, qhead = place.qhead, rblk = place.rblk;   // key/value head, query head, 256-row block
     const int64_t wave_row0 = (int64_t)rblk * kRowsPerBlock + wave * kRowsPerWave;
     const int64_t head_off = (int64_t)head * a.stride_head;          // k_cur / v_cur
     const int64_t qhead_off = (int64_t)qhead * a.q_stride_head;      // q / out
@@ -837,15 +820,16 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
     };
 
     // ---------------------------------------------------------------------- cached keys ----
-    if (a.cache_len > 0) {
+    if (place.cs < place.ce) {
         // Per-channel caches: one pass per key block of the window, each with its own query operands.
         for (int bi = 0; bi < (PERCH ? a.n_key_blocks : 1); ++bi) {
-        int64_t cs = a.cache_start, ce = a.cache_start + a.cache_len;
-        int phys_first = (int)a.phys_tile_first;
-        if constexpr (PERCH) {
+        int64_t cs = place.cs, ce = place.ce;
+        int phys_first = place.phys_first;
+        if constexpr (PERCH) {   // the part of the block that lies in this workgroup's key range
             const KeyBlock kb = a.key_blocks[bi];
-            cs = a.cache_start + kb.start;
-            ce = a.cache_start + kb.end;
+            cs = a.cache_start + kb.start > cs ? a.cache_start + kb.start : cs;
+            ce = a.cache_start + kb.end < ce ? a.cache_start + kb.end : ce;
+            if (cs >= ce) continue;
             phys_first = (int)((a.phys_tile_first + (cs / kTileTokens - a.cache_start / kTileTokens)) % cv.cap_tiles);
             __syncthreads();   // every wave has left the previous block's tiles and staging rows
             reprepare(cv.kc_scale + ((int64_t)kb.slot * cv.num_heads + head) * D,
@@ -1502,45 +1486,24 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
 #include "kvq_mfma_current_phase.inc"
 
     // ------------------------------------------------------------------------- epilogue ----
-    uint16_t *out_base = static_cast<uint16_t *>(a.out) + qhead_off;
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-        const float ls = l_s[rb] + xhalf(l_s[rb]);
-        const float lr = l_r[rb] + xhalf(l_r[rb]);
-        const float inv = 1.0f / (ls + lr);
-        const int64_t row = wave_row0 + 32 * rb + n;
-        if (row < a.m) {
-            uint16_t *dst = out_base + row * a.q_stride_token + 4 * hh;
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    u32x2 w;
-                    w.x = pack_bf16(o[b][rb][4 * g] * inv, o[b][rb][4 * g + 1] * inv);
-                    w.y = pack_bf16(o[b][rb][4 * g + 2] * inv, o[b][rb][4 * g + 3] * inv);
-                    *reinterpret_cast<u32x2 *>(dst + 32 * b + 8 * g) = w;
-                }
-            if (a.mass_cached && hh == 0) a.mass_cached[(int64_t)qhead * a.m + row] = ls * inv;
-        }
-    }
+#include "kvq_mfma_epilogue.inc"
 }
 
-template <int BITS, bool CORR, bool FP8META, bool PERCH = false> hipError_t launch(const AttentionArgs &a, hipStream_t stream)
+template <int BITS, bool CORR, bool FP8META, bool PERCH = false> hipError_t launch(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const void *fn = reinterpret_cast<const void *>(&attention_mfma_kernel<BITS, CORR, FP8META, PERCH>);
     const hipError_t ce = configure_dynamic_lds(fn, lds_bytes<BITS>(), configured);
     if (ce != hipSuccess) return ce;
-    const int row_blocks = (int)((a.m + kRowsPerBlock - 1) / kRowsPerBlock);
-    const int64_t blocks = (int64_t)row_blocks * a.cv.num_heads * a.q_per_kv;
+    const int64_t blocks = (int64_t)sp.whole + sp.pieces;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     return launch_kernel(attention_mfma_kernel<BITS, CORR, FP8META, PERCH>, dim3((unsigned)blocks), dim3(kThreads), lds_bytes<BITS>(),
-                         stream, a, row_blocks);
+                         stream, a, sp);
 }
 
 }  // namespace
 
-hipError_t launch_attention_mfma(const AttentionArgs &a, hipStream_t stream)
+hipError_t launch_attention_mfma(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
     if (a.cv.head_dim != D || a.cv.io_dtype != KVQ_BF16) return hipErrorInvalidValue;
     if (a.cv.meta_format != KVQ_META_FP32 && a.cv.group_size != D) return hipErrorInvalidValue;
@@ -1548,13 +1511,13 @@ hipError_t launch_attention_mfma(const AttentionArgs &a, hipStream_t stream)
     const bool fp8 = a.cv.meta_format == KVQ_META_FP8_BF16;
     if (a.cv.key_axis == KVQ_KEYS_PER_CHANNEL) {   // the caller has listed the key blocks of the window
         if (fp8 || a.n_key_blocks < 1 || a.n_key_blocks > kMaxKeyBlocks || a.cache_len < 1) return hipErrorInvalidValue;
-        if (a.cv.bits == 2) return a.correction ? launch<2, true, false, true>(a, stream) : launch<2, false, false, true>(a, stream);
-        return a.correction ? launch<4, true, false, true>(a, stream) : launch<4, false, false, true>(a, stream);
+        if (a.cv.bits == 2) return a.correction ? launch<2, true, false, true>(a, sp, stream) : launch<2, false, false, true>(a, sp, stream);
+        return a.correction ? launch<4, true, false, true>(a, sp, stream) : launch<4, false, false, true>(a, sp, stream);
     }
-    if (a.cv.bits == 2 && !fp8) return a.correction ? launch<2, true, false>(a, stream) : launch<2, false, false>(a, stream);
-    if (a.cv.bits == 4 && !fp8) return a.correction ? launch<4, true, false>(a, stream) : launch<4, false, false>(a, stream);
-    if (a.cv.bits == 2 && fp8) return a.correction ? launch<2, true, true>(a, stream) : launch<2, false, true>(a, stream);
-    if (a.cv.bits == 4 && fp8) return a.correction ? launch<4, true, true>(a, stream) : launch<4, false, true>(a, stream);
+    if (a.cv.bits == 2 && !fp8) return a.correction ? launch<2, true, false>(a, sp, stream) : launch<2, false, false>(a, sp, stream);
+    if (a.cv.bits == 4 && !fp8) return a.correction ? launch<4, true, false>(a, sp, stream) : launch<4, false, false>(a, sp, stream);
+    if (a.cv.bits == 2 && fp8) return a.correction ? launch<2, true, true>(a, sp, stream) : launch<2, false, true>(a, sp, stream);
+    if (a.cv.bits == 4 && fp8) return a.correction ? launch<4, true, true>(a, sp, stream) : launch<4, false, true>(a, sp, stream);
     return hipErrorInvalidValue;
 }
 

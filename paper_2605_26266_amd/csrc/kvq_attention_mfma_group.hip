@@ -126,7 +126,7 @@ template <int BITS, int G> constexpr size_t group_lds_bytes()
 }
 
 template <int BITS, bool CORR, int G>
-__global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(AttentionArgs a, int row_blocks)
+__global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(AttentionArgs a, SplitArgs sp)
 {
     static_assert(kRB == 2, "64 rows per wave");
     if (cache_flagged(a.status)) return;   // the vector kernel enqueued behind this launch serves such a cache
@@ -149,25 +149,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(Atten
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
 
-    // Workgroups are handed to the 8 XCDs round-robin; keep all row blocks of all query heads of a
-    // key/value head on one XCD so that its packed cache is fetched into that XCD's L2 once.
-    int head, qhead, rblk;   // key/value head, query head, 256-row block
-    {
-        const int bid = blockIdx.x;
-        const int per_head = row_blocks * a.q_per_kv;
-        int j;
-        if ((cv.num_heads & 7) == 0) {
-            const int xcd = bid & 7;
-            j = bid >> 3;
-            head = (j / per_head) * 8 + xcd;
-        } else {
-            j = bid;
-            head = j / per_head;
-        }
-        const int local = j % per_head;
-        qhead = head * a.q_per_kv + local / row_blocks;
-        rblk = local % row_blocks;
-    }
+    const Place place = locate(a, sp);
+    const int head = place.head, qhead = place.qhead, rblk = place.rblk;   // key/value head, query head, 256-row block
     const int64_t wave_row0 = (int64_t)rblk * kRowsPerBlock + wave * kRowsPerWave;
     const int64_t head_off = (int64_t)head * a.stride_head;          // k_cur / v_cur
     const int64_t qhead_off = (int64_t)qhead * a.q_stride_head;      // q / out
@@ -383,8 +366,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(Atten
     };
 
     // ---------------------------------------------------------------------- cached keys ----
-    if (a.cache_len > 0) {
-        const int64_t cs = a.cache_start, ce = a.cache_start + a.cache_len;
+    if (place.cs < place.ce) {
+        const int64_t cs = place.cs, ce = place.ce;
         const int64_t t_first = cs / kTileTokens, t_last = (ce - 1) / kTileTokens;
         const int n_tiles = (int)(t_last - t_first + 1);
         const int n_stages = (n_tiles + kStageTiles - 1) / kStageTiles;
@@ -407,7 +390,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(Atten
         // stage's first physical tile is uniform, a thread adds its tile inside the stage and wraps once more.
         const int cap = (int)cv.cap_tiles;
         const int first_off = (int)(cs - t_first * kTileTokens);   // position of cache_start inside its tile
-        const int win_len = (int)a.cache_len;
+        const int win_len = (int)(ce - cs);
         const uint32_t *code_src[kCodeIters];
         int code_tile[kCodeIters];
 #pragma unroll
@@ -418,7 +401,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(Atten
         }
         auto prefetch = [&](int stage) {
             if (stage >= n_stages) return;
-            int ring0 = (int)a.phys_tile_first + stage * kStageTiles;   // < 2 cap + 4: n_tiles <= cap + 1
+            int ring0 = place.phys_first + stage * kStageTiles;   // < 2 cap + 4: n_tiles <= cap + 1
             ring0 -= ring0 >= cap ? cap : 0;
             ring0 -= ring0 >= cap ? cap : 0;
 #pragma unroll
@@ -883,41 +866,19 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(Atten
 #include "kvq_mfma_current_phase.inc"
 
     // ------------------------------------------------------------------------- epilogue ----
-    uint16_t *out_base = static_cast<uint16_t *>(a.out) + qhead_off;
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-        const float ls = l_s[rb] + xhalf(l_s[rb]);
-        const float lr = l_r[rb] + xhalf(l_r[rb]);
-        const float inv = 1.0f / (ls + lr);
-        const int64_t row = wave_row0 + 32 * rb + n;
-        if (row < a.m) {
-            uint16_t *dst = out_base + row * a.q_stride_token + 4 * hh;
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    u32x2 w;
-                    w.x = pack_bf16(o[b][rb][4 * g] * inv, o[b][rb][4 * g + 1] * inv);
-                    w.y = pack_bf16(o[b][rb][4 * g + 2] * inv, o[b][rb][4 * g + 3] * inv);
-                    *reinterpret_cast<u32x2 *>(dst + 32 * b + 8 * g) = w;
-                }
-            if (a.mass_cached && hh == 0) a.mass_cached[(int64_t)qhead * a.m + row] = ls * inv;
-        }
-    }
+#include "kvq_mfma_epilogue.inc"
 }
 
-template <int BITS, bool CORR, int G> hipError_t launch_group(const AttentionArgs &a, hipStream_t stream)
+template <int BITS, bool CORR, int G> hipError_t launch_group(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
     static std::atomic<uint64_t> configured{0};  // per instantiation and device
     const void *fn = reinterpret_cast<const void *>(&attention_mfma_group_kernel<BITS, CORR, G>);
     const hipError_t ce = configure_dynamic_lds(fn, group_lds_bytes<BITS, G>(), configured);
     if (ce != hipSuccess) return ce;
-    const int row_blocks = (int)((a.m + kRowsPerBlock - 1) / kRowsPerBlock);
-    const int64_t blocks = (int64_t)row_blocks * a.cv.num_heads * a.q_per_kv;
+    const int64_t blocks = (int64_t)sp.whole + sp.pieces;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const size_t lds_size = group_lds_bytes<BITS, G>();
-    return launch_kernel(attention_mfma_group_kernel<BITS, CORR, G>, dim3((unsigned)blocks), dim3(kThreads), lds_size, stream, a,
-                         row_blocks);
+    return launch_kernel(attention_mfma_group_kernel<BITS, CORR, G>, dim3((unsigned)blocks), dim3(kThreads), lds_size, stream, a, sp);
 }
 
 }  // namespace
@@ -928,14 +889,14 @@ bool attention_mfma_group_supported(const CacheView &cv)
            (cv.bits == 2 || cv.bits == 4) && (cv.group_size == 32 || cv.group_size == 64);
 }
 
-hipError_t launch_attention_mfma_group(const AttentionArgs &a, hipStream_t stream)
+hipError_t launch_attention_mfma_group(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
     if (!attention_mfma_group_supported(a.cv)) return hipErrorInvalidValue;
     if (a.cache_len > (int64_t)0x3fffffff * kTileTokens) return hipErrorInvalidValue;
-    if (a.cv.bits == 4 && a.cv.group_size == 32) return a.correction ? launch_group<4, true, 4>(a, stream) : launch_group<4, false, 4>(a, stream);
-    if (a.cv.bits == 4) return a.correction ? launch_group<4, true, 2>(a, stream) : launch_group<4, false, 2>(a, stream);
-    if (a.cv.group_size == 32) return a.correction ? launch_group<2, true, 4>(a, stream) : launch_group<2, false, 4>(a, stream);
-    return a.correction ? launch_group<2, true, 2>(a, stream) : launch_group<2, false, 2>(a, stream);
+    if (a.cv.bits == 4 && a.cv.group_size == 32) return a.correction ? launch_group<4, true, 4>(a, sp, stream) : launch_group<4, false, 4>(a, sp, stream);
+    if (a.cv.bits == 4) return a.correction ? launch_group<4, true, 2>(a, sp, stream) : launch_group<4, false, 2>(a, sp, stream);
+    if (a.cv.group_size == 32) return a.correction ? launch_group<2, true, 4>(a, sp, stream) : launch_group<2, false, 4>(a, sp, stream);
+    return a.correction ? launch_group<2, true, 2>(a, sp, stream) : launch_group<2, false, 2>(a, sp, stream);
 }
 
 }  // namespace kvq

@@ -222,3 +222,65 @@ template <int N, typename F> __device__ inline void static_for(F &&f)
         f(IntC<N - 1>{});
     }
 }
+
+// What one workgroup works on (see SplitArgs): rows and keys.
+struct Place {
+    int head, qhead, rblk;      // key/value head, query head, 256-row block
+    int piece;                  // index of the partial result, -1: a whole unit
+    int64_t cs, ce;             // cached keys [cs, ce), logical positions
+    int phys_first;             // physical tile that holds cs
+    int cur0, cur1;             // tiles of the current block [cur0, cur1)
+};
+// Workgroups are handed to the 8 XCDs round-robin: index b of `total` -> the XCD's contiguous share of them, so that
+// the row blocks, query heads and pieces of a key/value head meet in one XCD's L2.
+__device__ inline int xcd_contiguous(int b, int total)
+{
+    const int x = b & 7, rest = total & 7;
+    return x * (total >> 3) + (x < rest ? x : rest) + (b >> 3);
+}
+__device__ inline Place locate(const AttentionArgs &a, const SplitArgs &sp)
+{
+    Place w;
+    const int bid = blockIdx.x;
+    int unit, split = 0;
+    if (bid < sp.whole) {
+        unit = xcd_contiguous(bid, sp.whole);
+        w.piece = -1;
+    } else {
+        w.piece = xcd_contiguous(bid - sp.whole, sp.pieces);
+        unit = sp.whole + w.piece / sp.splits;
+        split = w.piece % sp.splits;
+    }
+    w.qhead = unit / sp.row_blocks;
+    w.rblk = unit % sp.row_blocks;
+    w.head = w.qhead / a.q_per_kv;
+    // Current keys some row of the block sees: under the causal mask none past its last row.
+    int64_t n_keys = a.n_cur;
+    if (a.causal) {
+        int64_t last_row = (int64_t)w.rblk * kRowsPerBlock + kRowsPerBlock - 1;
+        last_row = last_row < a.m ? last_row : a.m - 1;
+        const int64_t upto = last_row + (a.n_cur - a.m) + 1;
+        n_keys = upto < n_keys ? upto : n_keys;
+    }
+    w.cs = a.cache_start;
+    w.ce = a.cache_start + a.cache_len;
+    w.phys_first = (int)a.phys_tile_first;
+    w.cur0 = 0;
+    w.cur1 = (int)((n_keys + kTileTokens - 1) / kTileTokens);
+    if (w.piece >= 0) {
+        const int64_t t_first = w.cs / kTileTokens;
+        const int tc = a.cache_len > 0 ? (int)((w.ce - 1) / kTileTokens - t_first) + 1 : 0, all = tc + w.cur1;
+        const int x0 = (int)((int64_t)all * split / sp.splits), x1 = (int)((int64_t)all * (split + 1) / sp.splits);
+        const int c0 = x0 < tc ? x0 : tc, c1 = x1 < tc ? x1 : tc;
+        if (c0 > 0) w.cs = (t_first + c0) * kTileTokens;
+        if (c1 < tc) w.ce = (t_first + c1) * kTileTokens;
+        if (c1 <= c0) w.ce = w.cs;
+        const int cap = (int)a.cv.cap_tiles;
+        w.phys_first += c0;                                  // <= 2 cap: a window has at most cap + 1 tiles
+        w.phys_first -= w.phys_first >= cap ? cap : 0;
+        w.phys_first -= w.phys_first >= cap ? cap : 0;
+        w.cur0 = x0 - c0;                                    // x0 < tc: 0
+        w.cur1 = x1 - c1;
+    }
+    return w;
+}

@@ -1,0 +1,85 @@
+"""Calls whose key range is split over workgroups (kvq_chunk_attention_ws) against the same call unsplit."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2605_26266_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _call(cache, start, length, q, k, v, ratio, causal, workspace):
+    """The C entry itself; workspace None: nothing is split."""
+    out = torch.full_like(q, float("nan"))
+    mass = torch.full((q.shape[1], q.shape[0]), float("nan"), dtype=torch.float32, device=DEV)
+    n_cur = 0 if k is None else k.shape[0]
+    opts = B.kvq_attention_opts(ratio, int(causal), q.stride(0), q.stride(1))
+    heads, dim = cache.desc.num_heads, cache.desc.head_dim
+    status = B.lib().kvq_chunk_attention_ws(
+        cache.handle, start, length, q.data_ptr(), None if k is None else k.data_ptr(), None if v is None else v.data_ptr(),
+        q.shape[0], n_cur, heads * dim, dim, 0.0, 1, ctypes.byref(opts), out.data_ptr(), mass.data_ptr(),
+        None if workspace is None else workspace.data_ptr(), 0 if workspace is None else workspace.numel(),
+        int(torch.cuda.current_stream().cuda_stream))
+    assert status == B.KVQ_OK
+    torch.cuda.synchronize()
+    return out.float(), mass
+
+
+FORMATS = [(2, B.KVQ_META_FP32, 128, 0), (4, B.KVQ_META_FP32, 128, 0), (2, B.KVQ_META_FP8_BF16, 32, 0),
+           (4, B.KVQ_META_FP8_BF16, 64, 0), (2, B.KVQ_META_FP32, 128, 1)]
+# (heads, ratio, rows, current keys, causal, appended blocks, first cached token, cached tokens)
+SHAPES = [
+    (1, 1, 1, 1, True, [400], 0, 400),               # one row, one current key
+    (2, 3, 33, 70, True, [500, 269], 45, 700),       # ragged window over two blocks, rows that see part of a piece only
+    (3, 1, 300, 300, True, [96], 0, 96),             # pieces that hold current tiles alone, some invisible to early rows
+    (8, 1, 257, 1, False, [1024], 31, 993),          # a second row block with one row
+    (5, 1, 64, 0, False, [2000], 1, 1999),           # no current block
+    (2, 1, 600, 857, False, [], 0, 0),               # no cached tokens
+    (44, 1, 1600, 33, False, [900], 0, 900),         # 308 units: 256 whole, 52 split
+]
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("shape", SHAPES)
+def test_split_call_agrees_with_the_unsplit_one(fmt, shape):
+    bits, meta, group, axis = fmt
+    heads, ratio, rows, current, causal, blocks, start, length = shape
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7)
+
+    def t(tokens, h):
+        return torch.randn((tokens, h, 128), generator=gen, device=DEV).to(torch.bfloat16)
+
+    cache = B.Cache(B.make_desc(heads, 128, bits, max(sum(blocks), 32) + 64, B.KVQ_BF16, group, 1, meta, axis), DEV)
+    for n in blocks:
+        B.kvq_quantize_append(cache, t(n, heads), t(n, heads))
+    q = t(rows, heads * ratio)
+    k, v = (t(current, heads), t(current, heads)) if current else (None, None)
+    nbytes = B.lib().kvq_attention_workspace_bytes(cache.handle, start, length, rows, current, ratio)
+    if axis == 0 or length:
+        assert nbytes > 0, "the shape is meant to be split"
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)     # NaN patterns: only what was written may be read
+    out, mass = _call(cache, start, length, q, k, v, ratio, causal, ws)
+    ref, ref_mass = _call(cache, start, length, q, k, v, ratio, causal, None)
+    assert torch.isfinite(out).all()
+    # Either side rounds its probabilities and its output to 16 bits (2^-9 relative each, weights sum to 1): their
+    # distance is at most 4 * 2^-9 of the largest value a row can average.
+    bound = 4 * 2.0 ** -9 * max(float(ref.abs().max()), 1.0) * 4
+    assert float((out - ref).abs().max()) <= bound
+    # fp32 sums of the same terms in another order; the group-wise kernel sums f16-rounded ones (2^-11 each)
+    torch.testing.assert_close(mass, ref_mass, rtol=1e-3, atol=1e-6)
+
+
+def test_too_small_a_workspace_means_no_split():
+    cache = B.Cache(B.make_desc(2, 128, 2, 512, B.KVQ_BF16), DEV)
+    x = torch.randn((480, 2, 128), device=DEV).to(torch.bfloat16)
+    B.kvq_quantize_append(cache, x, x)
+    q = x[:40].contiguous()
+    nbytes = B.lib().kvq_attention_workspace_bytes(cache.handle, 0, 480, 40, 40, 1)
+    short = torch.full((nbytes - 256,), 0x5A, dtype=torch.uint8, device=DEV)
+    out, mass = _call(cache, 0, 480, q, q, q, 1, False, short)
+    ref, ref_mass = _call(cache, 0, 480, q, q, q, 1, False, None)
+    assert torch.equal(out, ref) and torch.equal(mass, ref_mass)
+    assert (short == 0x5A).all()
