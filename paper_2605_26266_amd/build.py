@@ -36,6 +36,7 @@ SOURCES = {
     "kvq_attention_mfma.hip": [],
     "kvq_attention_mfma_group.hip": [],
     "kvq_attention_merge.hip": [],
+    "kvq_attention_f32.hip": [],
 }
 
 

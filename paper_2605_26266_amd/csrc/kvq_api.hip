@@ -82,28 +82,40 @@ bool tensor_ok(const void *p, int64_t stride_token, int64_t stride_head, int hea
     return true;
 }
 
-// How a matrix-core call of `units` 256-row blocks and `tiles` 32-key tiles per block is laid over the 256 compute units
-// (one workgroup each).  The blocks that fill whole rounds of the chip stay whole; the key ranges of the rest are cut into
-// the number of pieces with the shortest estimated time, in tiles (about 1 us): rounds * (tiles per piece + what a
-// workgroup pays once: query preparation, rotation back, writing its result) + the merge.
-// The constants follow measurements: 8 heads x 1024 rows x (4096 + 1024) keys, 32 blocks: 208 / 133 / 96 / 77.5 / 112 / 180 us
-// with 1 / 2 / 4 / 8 / 12 / 32 pieces; 32 query heads x 1 row x (8192 + 64) keys: 366 / 112 / 70 / 90 / 130 us with 1 / 4 /
-// 8 / 16 / 32; 24 heads x 4680 rows x (28080 + 4680) keys, 200 blocks after a full round: 2182 / 2286 / 2146 / 2219 / 2331 us
-// with 1 / 2 / 5 / 6 / 9.
-kvq::SplitArgs plan_split(int64_t m, int64_t q_heads, int64_t tiles)
+// How a matrix-core call is laid over the 256 compute units (one workgroup each).  The units (row blocks) that fill whole
+// rounds of the chip stay whole; the key ranges of the rest are cut into the number of pieces with the shortest estimated
+// time: rounds * (tiles per piece + what a workgroup pays once: query preparation, rotation back, writing its result) + the
+// merge.  The constants (microseconds) follow measurements of the 16-bit kernels: 8 heads x 1024 rows x (4096 + 1024)
+// keys, 32 units: 208 / 133 / 96 / 77.5 / 112 / 180 us with 1 / 2 / 4 / 8 / 12 / 32 pieces; 32 query heads x 1 row x (8192
+// + 64) keys: 366 / 112 / 70 / 90 / 130 us with 1 / 4 / 8 / 16 / 32; 24 heads x 4680 rows x (28080 + 4680) keys, 200
+// units after a full round: 2182 / 2286 / 2146 / 2219 / 2331 us with 1 / 2 / 5 / 6 / 9.
+struct KernelCost {
+    int rows;          // query rows of a unit
+    int tiles_step;    // tiles that a workgroup works on side by side
+    double tile, fixed;
+};
+constexpr KernelCost kCost16{256, 1, 1.0, 30.0};
+constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 8, 0.45, 8.0}, kCostF32Dim128{kvq::kF32Rows, 8, 0.9, 10.0};
+
+kvq::SplitArgs plan_split(const KernelCost &k, int64_t m, int64_t q_heads, int64_t tiles)
 {
     constexpr int kComputeUnits = 256, kMaxSplits = 64;
-    constexpr double kFixed = 30.0, kMerge = 6.0, kMergePerSplit = 0.12, kMergePerBlock = 0.0025;
+    constexpr double kMerge = 6.0, kMergePerSplit = 0.12, kMergePerBlock = 0.0025;
     kvq::SplitArgs sp = {};
-    sp.row_blocks = (int32_t)((m + kvq::kSplitRows - 1) / kvq::kSplitRows);
-    sp.part_blocks = (int32_t)(m < kvq::kSplitRows ? (m + 31) / 32 : kvq::kSplitRows / 32);
+    sp.rows = k.rows;
+    sp.row_blocks = (int32_t)((m + k.rows - 1) / k.rows);
+    sp.part_blocks = (int32_t)(m < k.rows ? (m + 31) / 32 : k.rows / 32);
     const int64_t units = sp.row_blocks * q_heads, rest = units % kComputeUnits;
+    auto piece_cost = [&](int64_t s) {
+        const int64_t steps = (tiles + s * k.tiles_step - 1) / (s * k.tiles_step);
+        return (double)(steps * k.tiles_step) * k.tile + k.fixed;
+    };
     int64_t best = 1;
-    double best_cost = (double)tiles + kFixed;
+    double best_cost = piece_cost(1);
     for (int64_t s = 2; rest > 0 && s <= kMaxSplits && s <= tiles && rest * s <= kvq::kMaxPieces; ++s) {
         const int64_t rounds = (rest * s + kComputeUnits - 1) / kComputeUnits;
-        const double cost = (double)rounds * ((double)((tiles + s - 1) / s) + kFixed) + kMerge +
-                            kMergePerSplit * (double)s + kMergePerBlock * (double)(rest * s * sp.part_blocks);
+        const double cost = (double)rounds * piece_cost(s) + kMerge + kMergePerSplit * (double)s +
+                            kMergePerBlock * (double)(rest * s * sp.part_blocks);
         if (cost < best_cost) {
             best_cost = cost;
             best = s;
@@ -113,6 +125,21 @@ kvq::SplitArgs plan_split(int64_t m, int64_t q_heads, int64_t tiles)
     sp.pieces = (int32_t)(best > 1 ? rest * best : 0);
     sp.whole = (int32_t)(best > 1 ? units - rest : units);
     return sp;
+}
+
+enum class Route { vector, per_token, group, f32 };
+
+// The kernel that serves a cache's calls, unless the call itself asks for the vector kernel: 16-bit matrix cores for BF16
+// and head_dim 128, fp32 matrix cores for the other per-token caches.
+Route route_of(const kvq_cache_desc &d, const kvq::CacheView &cv)
+{
+    if (kvq::attention_mfma_group_supported(cv)) return Route::group;
+    if (d.io_dtype == KVQ_BF16 && d.head_dim == 128 && d.group_size == d.head_dim) return Route::per_token;
+    return d.key_axis == KVQ_KEYS_PER_TOKEN ? Route::f32 : Route::vector;
+}
+const KernelCost &cost_of(Route r, int head_dim)
+{
+    return r != Route::f32 ? kCost16 : head_dim == 64 ? kCostF32Dim64 : kCostF32Dim128;
 }
 
 // Tiles of a call's key range: cached tiles that the window touches and tiles of the current block.
@@ -378,30 +405,28 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
     }
     // (the matrix-core loaders do their ring arithmetic and their offsets inside a head in 32 bits)
     force_vector = force_vector || cache_len >= (int64_t(1) << 31) || cache->view.cap_tiles >= (int64_t(1) << 20);
-    const bool matrix_path = !force_vector && d.io_dtype == KVQ_BF16 && d.head_dim == 128 &&
-                             d.group_size == d.head_dim;   // one (scale, zero-point) per token, either format
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (diag) return kvq::launch_diagnostics_simt(a, k_ref, v_ref, diag, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
-    const bool group_matrix_path = !force_vector && kvq::attention_mfma_group_supported(cache->view);
-    kvq::SplitArgs sp = {};
-    if (matrix_path || group_matrix_path) {
-        const int64_t q_heads = (int64_t)d.num_heads * o.q_heads_per_kv_head;
-        if ((m + kvq::kSplitRows - 1) / kvq::kSplitRows * q_heads > 0x7fffffff) return KVQ_ERR_HIP;
-        sp = plan_split(m, q_heads, key_tiles(a.cache_start, cache_len, n_cur));
-        if (sp.pieces > 0 && workspace_bytes < kvq::split_workspace_bytes(sp)) {   // no room for partial results: whole units
-            sp.whole += sp.pieces / sp.splits;
-            sp.splits = 1;
-            sp.pieces = 0;
-        }
-        sp.part_o = static_cast<float *>(workspace);
-        sp.part_ml = reinterpret_cast<float4 *>(sp.part_o + (size_t)sp.pieces * sp.part_blocks * 32 * 128);
+    const Route route = force_vector ? Route::vector : route_of(d, cache->view);
+    if (route == Route::vector) return kvq::launch_attention_simt(a, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
+    const KernelCost &cost = cost_of(route, d.head_dim);
+    const int64_t q_heads = (int64_t)d.num_heads * o.q_heads_per_kv_head;
+    if ((m + cost.rows - 1) / cost.rows * q_heads > 0x7fffffff) return KVQ_ERR_HIP;
+    kvq::SplitArgs sp = plan_split(cost, m, q_heads, key_tiles(a.cache_start, cache_len, n_cur));
+    if (sp.pieces > 0 && workspace_bytes < kvq::split_workspace_bytes(sp, d.head_dim)) {   // no room for partial results: whole units
+        sp.whole += sp.pieces / sp.splits;
+        sp.splits = 1;
+        sp.pieces = 0;
     }
-    hipError_t e = matrix_path         ? kvq::launch_attention_mfma(a, sp, s)
-                   : group_matrix_path ? kvq::launch_attention_mfma_group(a, sp, s)
-                                       : kvq::launch_attention_simt(a, s);
+    sp.part_o = static_cast<float *>(workspace);
+    sp.part_ml = reinterpret_cast<float4 *>(sp.part_o + (size_t)sp.pieces * sp.part_blocks * 32 * d.head_dim);
+    if (route == Route::f32) a.status = nullptr;   // any zero-point will do
+    hipError_t e = route == Route::per_token ? kvq::launch_attention_mfma(a, sp, s)
+                   : route == Route::group   ? kvq::launch_attention_mfma_group(a, sp, s)
+                                             : kvq::launch_attention_f32(a, sp, s);
     if (e == hipSuccess && sp.pieces > 0) e = kvq::launch_attention_merge(a, sp, s);
-    if (e == hipSuccess && (matrix_path || group_matrix_path) && a.status) {
-        // A cache that has ever stored a zero-point beyond the matrix-core kernels' domain carries a flag: the launch
+    if (e == hipSuccess && a.status) {
+        // A cache that has ever stored a zero-point beyond the 16-bit kernels' domain carries a flag: the launch
         // above has then returned without writing anything, and this one, which otherwise returns at once, does the work.
         a.only_if_flagged = 1;
         e = kvq::launch_attention_simt(a, s);
@@ -444,10 +469,12 @@ size_t kvq_attention_workspace_bytes(const kvq_cache *cache, int64_t cache_start
 {
     if (!cache || m <= 0 || n_cur < 0 || cache_len < 0 || cache_start < 0 || q_heads_per_kv_head < 1 || q_heads_per_kv_head > 64) return 0;
     const kvq_cache_desc &d = cache->desc;
-    if (d.io_dtype != KVQ_BF16 || d.head_dim != 128 || cache_start + cache_len > cache->len) return 0;
+    const Route route = route_of(d, cache->view);
+    if (route == Route::vector || cache_start + cache_len > cache->len) return 0;
     if (m > ((int64_t)1 << 31) - 256 || n_cur > ((int64_t)1 << 31) - 256) return 0;
-    return kvq::split_workspace_bytes(plan_split(m, (int64_t)d.num_heads * q_heads_per_kv_head,
-                                                 key_tiles(cache->base + cache_start, cache_len, n_cur)));
+    const int64_t q_heads = (int64_t)d.num_heads * q_heads_per_kv_head;
+    return kvq::split_workspace_bytes(
+        plan_split(cost_of(route, d.head_dim), m, q_heads, key_tiles(cache->base + cache_start, cache_len, n_cur)), d.head_dim);
 }
 
 kvq_status kvq_chunk_attention_ws(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,

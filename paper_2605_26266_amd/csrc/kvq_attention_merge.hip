@@ -13,21 +13,22 @@
 namespace kvq {
 namespace {
 
-__global__ __launch_bounds__(256) void attention_merge_kernel(AttentionArgs a, SplitArgs sp)
+template <int DIM, typename T> __global__ __launch_bounds__(256) void attention_merge_kernel(AttentionArgs a, SplitArgs sp)
 {
     if (cache_flagged(a.status)) return;   // nothing has been computed: the vector kernel serves such a cache
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int n = lane & 31, hh = lane >> 5;
-    const int b = blockIdx.x & 3;
-    const int row_block = (int)((blockIdx.x >> 2) % sp.part_blocks), unit_rel = (int)((blockIdx.x >> 2) / sp.part_blocks);
+    constexpr int NB = DIM / 32;
+    const int b = blockIdx.x % NB;
+    const int row_block = (int)(blockIdx.x / NB % sp.part_blocks), unit_rel = (int)(blockIdx.x / NB / sp.part_blocks);
     const int unit = sp.whole + unit_rel;
     const int qhead = unit / sp.row_blocks, rblk = unit % sp.row_blocks;
-    const int64_t row = (int64_t)rblk * kSplitRows + 32 * row_block + n;
+    const int64_t row = (int64_t)rblk * sp.rows + 32 * row_block + n;
     if (row >= a.m) return;
     const int64_t block0 = (int64_t)unit_rel * sp.splits * sp.part_blocks + row_block;
     const float4 *ml = sp.part_ml + block0 * 32 + n;
-    const float4 *po = reinterpret_cast<const float4 *>(sp.part_o) + block0 * 1024 + (4 * b + g) * 64 + lane;
-    const int64_t ml_step = (int64_t)sp.part_blocks * 32, po_step = (int64_t)sp.part_blocks * 1024;
+    const float4 *po = reinterpret_cast<const float4 *>(sp.part_o) + block0 * (DIM * 8) + (4 * b + g) * 64 + lane;
+    const int64_t ml_step = (int64_t)sp.part_blocks * 32, po_step = (int64_t)sp.part_blocks * (DIM * 8);
 
     float top = -INFINITY;
 #pragma unroll 8
@@ -48,11 +49,15 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(AttentionArgs a, S
         acc.w = none ? acc.w : fmaf(w, v.w, acc.w);
     }
     const float inv = 1.0f / (ls + lr);
-    uint16_t *dst = static_cast<uint16_t *>(a.out) + (int64_t)qhead * a.q_stride_head + row * a.q_stride_token + 32 * b + 8 * g + 4 * hh;
-    uint2 w;
-    w.x = (uint32_t)float_to_bf16(acc.x * inv) | ((uint32_t)float_to_bf16(acc.y * inv) << 16);
-    w.y = (uint32_t)float_to_bf16(acc.z * inv) | ((uint32_t)float_to_bf16(acc.w * inv) << 16);
-    *reinterpret_cast<uint2 *>(dst) = w;
+    T *dst = static_cast<T *>(a.out) + (int64_t)qhead * a.q_stride_head + row * a.q_stride_token + 32 * b + 8 * g + 4 * hh;
+    if constexpr (sizeof(T) == 2) {
+        uint2 w;
+        w.x = (uint32_t)float_to_bf16(acc.x * inv) | ((uint32_t)float_to_bf16(acc.y * inv) << 16);
+        w.y = (uint32_t)float_to_bf16(acc.z * inv) | ((uint32_t)float_to_bf16(acc.w * inv) << 16);
+        *reinterpret_cast<uint2 *>(dst) = w;
+    } else {
+        *reinterpret_cast<float4 *>(dst) = float4{acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
+    }
     if (a.mass_cached && hh == 0 && b == 0 && g == 0) a.mass_cached[(int64_t)qhead * a.m + row] = ls * inv;
 }
 
@@ -60,8 +65,13 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(AttentionArgs a, S
 
 hipError_t launch_attention_merge(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
-    const int64_t units = sp.pieces / sp.splits;
-    return launch_kernel(attention_merge_kernel, dim3((unsigned)(units * sp.part_blocks * 4)), dim3(256), 0, stream, a, sp);
+    const int64_t blocks = (int64_t)(sp.pieces / sp.splits) * sp.part_blocks * (a.cv.head_dim / 32);
+    const dim3 grid((unsigned)blocks);
+    const bool bf16 = a.cv.io_dtype == KVQ_BF16;
+    if (a.cv.head_dim == 128 && bf16) return launch_kernel(attention_merge_kernel<128, uint16_t>, grid, dim3(256), 0, stream, a, sp);
+    if (a.cv.head_dim == 128) return launch_kernel(attention_merge_kernel<128, float>, grid, dim3(256), 0, stream, a, sp);
+    if (bf16) return launch_kernel(attention_merge_kernel<64, uint16_t>, grid, dim3(256), 0, stream, a, sp);
+    return launch_kernel(attention_merge_kernel<64, float>, grid, dim3(256), 0, stream, a, sp);
 }
 
 }  // namespace kvq

@@ -1,6 +1,7 @@
 // fp32 vector-ALU chunk attention: the reference-precision GPU path.
 //
-// Used for KVQ_FP32 caches, for head_dim 64, and by kvq_chunk_attention_fp32.  It follows
+// Used for the exact correction, for per-channel keys outside BF16 / head_dim 128, for caches whose status flag is set, and
+// by kvq_chunk_attention_fp32.  It follows
 // Alg. 1 of the paper literally in single precision, one workgroup of d threads per
 // (head, query row):
 //   * rotate the query (butterflies in LDS), nu_j = ||(Hn q)_j||^2 per group of channels that shares a
@@ -11,7 +12,7 @@
 //   * pass 2: scores again, p = exp(s - max); blocks of d weights go through LDS so that thread c
 //     accumulates output channel c; the cached part is accumulated in the rotated basis and
 //     rotated back before the current part is added.
-// Throughput is a few TFLOP/s at best; the matrix-core kernel is the fast path.
+// Throughput is a few TFLOP/s at best; the matrix-core kernels are the fast paths.
 // The same file holds the diagnostics kernel (quantized against unquantized attention per row).
 #include "kvq_internal.h"
 

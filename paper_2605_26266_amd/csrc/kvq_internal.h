@@ -213,23 +213,23 @@ struct AttentionArgs {
     const uint32_t *status;
     int32_t only_if_flagged;
 };
-// How the work of a matrix-core launch is laid over the grid.  A unit is one 256-row block of one query head over the
-// whole key range (cached tiles, then current tiles).  Units below `whole` have a workgroup each; the key range of every
+// How the work of a matrix-core launch is laid over the grid.  A unit is one block of `rows` query rows (256; 32 in the
+// fp32 kernel) of one query head over the whole key range (cached tiles, then current tiles).  Units below `whole` have a workgroup each; the key range of every
 // later unit is cut into `splits` pieces with a workgroup each, which leave unnormalised outputs, maxima and sums in
 // `part_o` / `part_ml` for the merge kernel that follows.
-constexpr int kSplitRows = 256;
 struct SplitArgs {
-    int32_t row_blocks;      // 256-row blocks per query head
+    int32_t rows;            // query rows of a unit
+    int32_t row_blocks;      // units per query head
     int32_t whole, splits;
     int32_t pieces;          // (units - whole) * splits
     int32_t part_blocks;     // 32-row blocks of a unit that hold rows of the call: what a piece has room for
-    float *part_o;           // [piece][part_blocks][channel block 4][register quad 4][lane 64][4]
+    float *part_o;           // [piece][part_blocks][channel block d / 32][register quad 4][lane 64][4]
     float4 *part_ml;         // [piece][part_blocks * 32]: reference maximum (log2 units), cached sum, current sum, 0
 };
 constexpr int kMaxPieces = 2048;
-inline size_t split_workspace_bytes(const SplitArgs &sp)
+inline size_t split_workspace_bytes(const SplitArgs &sp, int head_dim)
 {
-    return (size_t)sp.pieces * sp.part_blocks * 32 * (128 + 4) * sizeof(float);
+    return (size_t)sp.pieces * sp.part_blocks * 32 * (head_dim + 4) * sizeof(float);
 }
 __device__ inline bool cache_flagged(const uint32_t *status) { return status != nullptr && *status != 0u; }
 hipError_t launch_attention_simt(const AttentionArgs &a, hipStream_t stream);
@@ -240,6 +240,9 @@ hipError_t launch_attention_merge(const AttentionArgs &a, const SplitArgs &sp, h
 // ([cache_len][H][d], strides of k_cur); a.out and a.mass_cached are not used.
 hipError_t launch_diagnostics_simt(const AttentionArgs &a, const void *k_ref, const void *v_ref, float *diag,
                                    hipStream_t stream);
+// fp32 matrix-core kernel: per-token caches of either head_dim and I/O type, no or Taylor correction.
+constexpr int kF32Rows = 32;
+hipError_t launch_attention_f32(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
 // Matrix-core kernel for caches with several FP8/BF16 (scale, zero-point) groups per token.
 bool attention_mfma_group_supported(const CacheView &cv);
 hipError_t launch_attention_mfma_group(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
