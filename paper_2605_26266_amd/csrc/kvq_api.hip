@@ -95,24 +95,33 @@ struct KernelCost {
     double tile, fixed;
 };
 constexpr KernelCost kCost16{256, 1, 1.0, 30.0};
-constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 8, 0.45, 8.0}, kCostF32Dim128{kvq::kF32Rows, 8, 0.9, 10.0};
+constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 8, 0.64, 8.0}, kCostF32Dim128{kvq::kF32Rows, 8, 1.25, 10.0};
 
-kvq::SplitArgs plan_split(const KernelCost &k, int64_t m, int64_t q_heads, int64_t tiles)
+struct Plan {
+    kvq::SplitArgs sp;
+    double cost;
+};
+constexpr double kTooLarge = 1e300;   // more units than a grid holds
+
+Plan plan_split(const KernelCost &k, int64_t m, int64_t heads, int64_t ratio, int64_t tiles, bool may_split)
 {
     constexpr int kComputeUnits = 256, kMaxSplits = 64;
     constexpr double kMerge = 6.0, kMergePerSplit = 0.12, kMergePerBlock = 0.0025;
     kvq::SplitArgs sp = {};
     sp.rows = k.rows;
-    sp.row_blocks = (int32_t)((m + k.rows - 1) / k.rows);
-    sp.part_blocks = (int32_t)(m < k.rows ? (m + 31) / 32 : k.rows / 32);
-    const int64_t units = sp.row_blocks * q_heads, rest = units % kComputeUnits;
+    sp.pack = (int32_t)(k.rows == kvq::kF32Rows && m * ratio <= 0x7fffffff ? ratio : 1);
+    const int64_t rows = m * sp.pack;
+    sp.row_blocks = (int32_t)((rows + k.rows - 1) / k.rows);
+    sp.part_blocks = (int32_t)(rows < k.rows ? (rows + 31) / 32 : k.rows / 32);
+    const int64_t units = sp.row_blocks * heads * (ratio / sp.pack), rest = units % kComputeUnits;
     auto piece_cost = [&](int64_t s) {
         const int64_t steps = (tiles + s * k.tiles_step - 1) / (s * k.tiles_step);
         return (double)(steps * k.tiles_step) * k.tile + k.fixed;
     };
+    if (units > 0x7fffffff) return Plan{sp, kTooLarge};
     int64_t best = 1;
-    double best_cost = piece_cost(1);
-    for (int64_t s = 2; rest > 0 && s <= kMaxSplits && s <= tiles && rest * s <= kvq::kMaxPieces; ++s) {
+    double best_cost = rest > 0 ? piece_cost(1) : 0.0;
+    for (int64_t s = 2; may_split && rest > 0 && s <= kMaxSplits && s <= tiles && rest * s <= kvq::kMaxPieces; ++s) {
         const int64_t rounds = (rest * s + kComputeUnits - 1) / kComputeUnits;
         const double cost = (double)rounds * piece_cost(s) + kMerge + kMergePerSplit * (double)s +
                             kMergePerBlock * (double)(rest * s * sp.part_blocks);
@@ -121,10 +130,17 @@ kvq::SplitArgs plan_split(const KernelCost &k, int64_t m, int64_t q_heads, int64
             best = s;
         }
     }
+    // A split has to promise something: the estimate leaves out that a chip with idle compute units clocks higher, and
+    // that pieces of one unit compete for the same memory (31 heads x 1763 rows x 44075 keys, 217 units: 1451 us whole, 1549
+    // us in 7 pieces, estimated 1408 and 1399).
+    if (best > 1 && best_cost > 0.85 * piece_cost(1)) {
+        best = 1;
+        best_cost = piece_cost(1);
+    }
     sp.splits = (int32_t)best;
     sp.pieces = (int32_t)(best > 1 ? rest * best : 0);
     sp.whole = (int32_t)(best > 1 ? units - rest : units);
-    return sp;
+    return Plan{sp, best_cost + (double)(units / kComputeUnits) * piece_cost(1)};
 }
 
 enum class Route { vector, per_token, group, f32 };
@@ -140,6 +156,26 @@ Route route_of(const kvq_cache_desc &d, const kvq::CacheView &cv)
 const KernelCost &cost_of(Route r, int head_dim)
 {
     return r != Route::f32 ? kCost16 : head_dim == 64 ? kCostF32Dim64 : kCostF32Dim128;
+}
+
+// Kernel and grid of a call.  A call with a few rows per key/value head (the last tokens of a prompt, a decoded token)
+// fills a sliver of a 256-row block: where the fp32 kernel, with its 32-row units over all query heads of a key/value head,
+// is estimated to be clearly faster it takes such calls of the 16-bit kernels' caches too (8 key/value heads with 4 query
+// heads each, 1 row, 8192 + 64 keys, groups of 32: 70 us in the
+// group-wise kernel, 43 us here).
+struct Choice {
+    Route route;
+    kvq::SplitArgs sp;
+    bool fits;
+};
+Choice choose(Route route, const kvq_cache_desc &d, int64_t m, int64_t ratio, int64_t tiles, bool may_split)
+{
+    const Plan p = plan_split(cost_of(route, d.head_dim), m, d.num_heads, ratio, tiles, may_split);
+    if (route != Route::f32 && d.key_axis == KVQ_KEYS_PER_TOKEN) {
+        const Plan f = plan_split(cost_of(Route::f32, d.head_dim), m, d.num_heads, ratio, tiles, may_split);
+        if (f.cost < 0.8 * p.cost) return Choice{Route::f32, f.sp, true};
+    }
+    return Choice{route, p.sp, p.cost < kTooLarge};
 }
 
 // Tiles of a call's key range: cached tiles that the window touches and tiles of the current block.
@@ -407,17 +443,15 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
     force_vector = force_vector || cache_len >= (int64_t(1) << 31) || cache->view.cap_tiles >= (int64_t(1) << 20);
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (diag) return kvq::launch_diagnostics_simt(a, k_ref, v_ref, diag, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
-    const Route route = force_vector ? Route::vector : route_of(d, cache->view);
-    if (route == Route::vector) return kvq::launch_attention_simt(a, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
-    const KernelCost &cost = cost_of(route, d.head_dim);
-    const int64_t q_heads = (int64_t)d.num_heads * o.q_heads_per_kv_head;
-    if ((m + cost.rows - 1) / cost.rows * q_heads > 0x7fffffff) return KVQ_ERR_HIP;
-    kvq::SplitArgs sp = plan_split(cost, m, q_heads, key_tiles(a.cache_start, cache_len, n_cur));
-    if (sp.pieces > 0 && workspace_bytes < kvq::split_workspace_bytes(sp, d.head_dim)) {   // no room for partial results: whole units
-        sp.whole += sp.pieces / sp.splits;
-        sp.splits = 1;
-        sp.pieces = 0;
-    }
+    const Route own = force_vector ? Route::vector : route_of(d, cache->view);
+    if (own == Route::vector) return kvq::launch_attention_simt(a, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
+    const int64_t ratio = o.q_heads_per_kv_head, tiles = key_tiles(a.cache_start, cache_len, n_cur);
+    Choice c = choose(own, d, m, ratio, tiles, true);
+    if (workspace_bytes < kvq::split_workspace_bytes(c.sp, d.head_dim)) c = choose(own, d, m, ratio, tiles, false);
+    if (!c.fits && c.route == Route::f32) return kvq::launch_attention_simt(a, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
+    if (!c.fits) return KVQ_ERR_HIP;
+    const Route route = c.route;
+    kvq::SplitArgs &sp = c.sp;
     sp.part_o = static_cast<float *>(workspace);
     sp.part_ml = reinterpret_cast<float4 *>(sp.part_o + (size_t)sp.pieces * sp.part_blocks * 32 * d.head_dim);
     if (route == Route::f32) a.status = nullptr;   // any zero-point will do
@@ -472,9 +506,8 @@ size_t kvq_attention_workspace_bytes(const kvq_cache *cache, int64_t cache_start
     const Route route = route_of(d, cache->view);
     if (route == Route::vector || cache_start + cache_len > cache->len) return 0;
     if (m > ((int64_t)1 << 31) - 256 || n_cur > ((int64_t)1 << 31) - 256) return 0;
-    const int64_t q_heads = (int64_t)d.num_heads * q_heads_per_kv_head;
-    return kvq::split_workspace_bytes(
-        plan_split(cost_of(route, d.head_dim), m, q_heads, key_tiles(cache->base + cache_start, cache_len, n_cur)), d.head_dim);
+    const int64_t tiles = key_tiles(cache->base + cache_start, cache_len, n_cur);
+    return kvq::split_workspace_bytes(choose(route, d, m, q_heads_per_kv_head, tiles, true).sp, d.head_dim);
 }
 
 kvq_status kvq_chunk_attention_ws(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,

@@ -1,10 +1,12 @@
 // fp32 matrix-core chunk attention: every cache with one (scale, zero-point) per token or group of channels, head_dim 64
-// or 128, BF16 or FP32 tensors.  All inputs of the matrix instructions are fp32 and so is everything computed from them
+// or 128, BF16 or FP32 tensors: the caches that the 16-bit kernels do not serve, and calls with a few query rows, which
+// would leave most of their 256-row blocks empty.  All inputs of the matrix instructions are fp32 and so is everything computed from them
 // (v_mfma_f32_32x32x2_f32), so the results have the precision of the vector kernel, whose arithmetic this is: keys and
 // values are reconstructed as (code - zero) * scale, scored against the rotated query, corrected by
 // b = sigma^2 / 24 * sum_j step_j^2 nu_j.
 //
-// Work split.  A unit is 32 query rows of one query head; a workgroup of 8 wavefronts (two per SIMD: one unpacks while
+// Work split.  A unit is 32 query rows of one query head (or of the query heads that share a key/value head, one after
+// the other: four heads with a row each are one unit and read the cache once); a workgroup of 8 wavefronts (two per SIMD: one unpacks while
 // the other multiplies) takes a unit, or a piece of its key range, and deals its 32-key tiles to the wavefronts in turn.
 // Each wavefront keeps its own maximum, sums and output tile; they are put together through LDS at the end.  Few rows
 // (one token behind a long prefix) thereby still keep a compute unit busy, and no wavefront waits for another until then.
@@ -89,15 +91,25 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
         unit = sp.whole + piece / sp.splits;
         split = piece % sp.splits;
     }
-    const int qhead = unit / sp.row_blocks, rblk = unit % sp.row_blocks, head = qhead / a.q_per_kv;
-    const int64_t row = (int64_t)rblk * kFRows + n;
-    const int64_t row_ld = row < a.m ? row : a.m - 1;
+    // Rows of the query heads that share a key/value head follow one another where `pack` says so.
+    const int rblk = unit % sp.row_blocks, qhead0 = unit / sp.row_blocks * sp.pack, head = qhead0 / a.q_per_kv;
+    const int64_t rows = a.m * sp.pack, block_row0 = (int64_t)rblk * kFRows;
+    const int64_t packed_row = block_row0 + n < rows ? block_row0 + n : rows - 1;
+    const bool row_valid = block_row0 + n < rows;
+    int64_t row = packed_row;
+    int qhead = qhead0;
+    if (sp.pack > 1) {
+        qhead += (int)((uint32_t)packed_row / (uint32_t)a.m);
+        row = (uint32_t)packed_row % (uint32_t)a.m;
+    }
     // current keys this row sees, and some row of the block
     int64_t visible = a.n_cur, n_keys = a.n_cur;
     if (a.causal) {
-        int64_t last = (int64_t)rblk * kFRows + kFRows - 1;
-        last = last < a.m ? last : a.m - 1;
-        const int64_t upto = row_ld + (a.n_cur - a.m) + 1, upto_last = last + (a.n_cur - a.m) + 1;
+        // the last row of the block, or of a head that ends inside it
+        const int64_t end = block_row0 + kFRows < rows ? block_row0 + kFRows : rows;
+        int64_t last = end - 1;
+        if (sp.pack > 1) last = (uint32_t)block_row0 / (uint32_t)a.m != (uint32_t)(end - 1) / (uint32_t)a.m ? a.m - 1 : (uint32_t)(end - 1) % (uint32_t)a.m;
+        const int64_t upto = row + (a.n_cur - a.m) + 1, upto_last = last + (a.n_cur - a.m) + 1;
         visible = upto < visible ? upto : visible;
         n_keys = upto_last < n_keys ? upto_last : n_keys;
     }
@@ -109,7 +121,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
     const int first_off = (int)(a.cache_start - t_first * kTileTokens);
 
     // ---- query: lane (row, hh) holds channels 16 i + 8 hh + e in q[8 i + e]
-    const T *q_ptr = static_cast<const T *>(a.q) + row_ld * a.q_stride_token + (int64_t)qhead * a.q_stride_head + 8 * hh;
+    const T *q_ptr = static_cast<const T *>(a.q) + row * a.q_stride_token + (int64_t)qhead * a.q_stride_head + 8 * hh;
     const float c_log = a.softmax_scale * kLog2e;
     float q[8 * NI], corr[(G + 1) / 2];
     auto load_query = [&]() {
@@ -434,7 +446,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
         }
         __syncthreads();
     }
-    if (wave != 0 || row >= a.m) return;
+    if (wave != 0 || !row_valid) return;
     if (piece < 0) {
         const float inv = 1.0f / (l_s + l_r);
         T *dst = static_cast<T *>(a.out) + (int64_t)qhead * a.q_stride_head + row * a.q_stride_token + 4 * hh;

@@ -22,9 +22,14 @@ template <int DIM, typename T> __global__ __launch_bounds__(256) void attention_
     const int b = blockIdx.x % NB;
     const int row_block = (int)(blockIdx.x / NB % sp.part_blocks), unit_rel = (int)(blockIdx.x / NB / sp.part_blocks);
     const int unit = sp.whole + unit_rel;
-    const int qhead = unit / sp.row_blocks, rblk = unit % sp.row_blocks;
-    const int64_t row = (int64_t)rblk * sp.rows + 32 * row_block + n;
-    if (row >= a.m) return;
+    const int group = unit / sp.row_blocks, rblk = unit % sp.row_blocks;
+    int64_t row = (int64_t)rblk * sp.rows + 32 * row_block + n;
+    if (row >= a.m * sp.pack) return;
+    int qhead = group * sp.pack;
+    if (sp.pack > 1) {     // (the host packs heads only where the product fits 31 bits)
+        qhead += (int)((uint32_t)row / (uint32_t)a.m);
+        row = (uint32_t)row % (uint32_t)a.m;
+    }
     const int64_t block0 = (int64_t)unit_rel * sp.splits * sp.part_blocks + row_block;
     const float4 *ml = sp.part_ml + block0 * 32 + n;
     const float4 *po = reinterpret_cast<const float4 *>(sp.part_o) + block0 * (DIM * 8) + (4 * b + g) * 64 + lane;

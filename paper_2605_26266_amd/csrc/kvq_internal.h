@@ -219,7 +219,8 @@ struct AttentionArgs {
 // `part_o` / `part_ml` for the merge kernel that follows.
 struct SplitArgs {
     int32_t rows;            // query rows of a unit
-    int32_t row_blocks;      // units per query head
+    int32_t pack;            // query heads whose rows follow one another in the units (all of a key/value head's, or 1)
+    int32_t row_blocks;      // units per `pack` query heads
     int32_t whole, splits;
     int32_t pieces;          // (units - whole) * splits
     int32_t part_blocks;     // 32-row blocks of a unit that hold rows of the call: what a piece has room for

@@ -31,13 +31,15 @@ FORMATS = [(2, B.KVQ_META_FP32, 128, 0), (4, B.KVQ_META_FP32, 128, 0), (2, B.KVQ
            (4, B.KVQ_META_FP8_BF16, 64, 0), (2, B.KVQ_META_FP32, 128, 1)]
 # (heads, ratio, rows, current keys, causal, appended blocks, first cached token, cached tokens)
 SHAPES = [
-    (1, 1, 1, 1, True, [400], 0, 400),               # one row, one current key
+    (1, 1, 1, 1, True, [2000], 0, 2000),              # one row, one current key
     (2, 3, 33, 70, True, [500, 269], 45, 700),       # ragged window over two blocks, rows that see part of a piece only
-    (3, 1, 300, 300, True, [96], 0, 96),             # pieces that hold current tiles alone, some invisible to early rows
+    (2, 4, 3, 40, True, [700, 50], 3, 747),          # few rows, packed over the query heads (fp32 kernel) where it is per token
+    (3, 1, 300, 1000, True, [96], 0, 96),            # pieces that hold current tiles alone, some invisible to early rows
     (8, 1, 257, 1, False, [1024], 31, 993),          # a second row block with one row
     (5, 1, 64, 0, False, [2000], 1, 1999),           # no current block
     (2, 1, 600, 857, False, [], 0, 0),               # no cached tokens
-    (44, 1, 1600, 33, False, [900], 0, 900),         # 308 units: 256 whole, 52 split
+    (8, 1, 900, 1000, True, [3000], 5, 2990),        # 32 blocks of 256 rows in the 16-bit kernels
+    (44, 1, 1600, 33, False, [2000], 0, 2000),       # 308 blocks: 256 whole, 52 split
 ]
 
 
