@@ -235,12 +235,15 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
         float ssum = 0.0f, ssum_w = 0.0f;   // sum of q~ (true scale), sum of the weighted operand values
         if constexpr (kFp4) {
             static_assert(!kFp4 || kPrepLanes == 1, "one lane prepares a whole row");
-            // q~ = sum of four pieces n_k / 2 * 2^e_k, n_k integers of magnitude up to 15 (n / 2 is an E2M3 value),
-            // e_0 = e0 with the row maximum in (3.75, 7.5] * 2^e0, e_k = e0 - 4 k - 1 after that.  What piece 0
-            // leaves is at most a quarter of its scale, i.e. 16 half-steps of piece 1: five bits finer, and the one
-            // value in 33 that does not fit (16) is clamped to 15, which leaves the next piece a whole step of its
-            // predecessor instead of half a step -- again 16 of its own half-steps, clamped likewise.  The last
-            // step is 2^(e0 - 14); the error is a quarter of it, half of it after a clamp.
+            // q~ = sum of four FP6 (E2M3) pieces times 2^e_k, e_0 = e0 with the row maximum in (3.75, 7.5] * 2^e0,
+            // e_k = e0 - 4 k - 1 after that.  E2M3 holds every multiple of 1/2 up to 7.5 (and finer steps below 4), so what
+            // piece 0 leaves is at most a quarter of its scale, i.e. 8 scales of piece 1: five bits finer, and what lies
+            // above 7.5 is clamped there, which leaves the next piece half a scale of its predecessor -- again 8 of its
+            // own, clamped likewise.  The last step is at most 2^(e0 - 14); the error is a quarter of it, half of it
+            // after a clamp.  The pieces are made and read back by the 32-wide hardware conversions (a conversion, a
+            // conversion back and 32 subtractions per 32 channels and piece): rounding, clamping and assembling the
+            // codes by hand took eleven instructions per channel and piece (8 heads x 1024 rows x (4096 + 1024) keys in 8 pieces:
+            // 66 -> 54 us for the launch).
             float mx = 0.0f;
 #pragma unroll
             for (int c = 0; c < kPrepCh; ++c) {
@@ -249,36 +252,40 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             }
             int e0 = (int)((__float_as_uint(mx * (1.0f / 7.5f)) >> 23) & 0xffu) - 126;
             e0 = e0 < -100 ? -100 : e0 > 110 ? 110 : e0;
+            // The channels in operand order.  Element j of operand op (MFMA jm = op >> 1, lane half hw = op & 1) belongs to
+            // word 2 jm + (j >> 4), 2-bit field 2 (j & 7) + ((j >> 3) & 1) of the lane's key words (see key_pair); the
+            // conversion takes even elements from its first operand and odd ones from its second.
+            auto channel = [](int op, int j) {
+                const int jm = op >> 1, hw = op & 1, wd = 2 * jm + (j >> 4), f = 2 * (j & 7) + ((j >> 3) & 1);
+                const int pr = f & 7, slab = 2 * wd + (pr >> 2);
+                return 16 * slab + 8 * hw + 2 * (pr & 3) + (f >> 3);
+            };
+            f32x16 xe[4], xo[4];
+#pragma unroll
+            for (int op = 0; op < 4; ++op)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    xe[op][j] = x[channel(op, 2 * j)];
+                    xo[op][j] = x[channel(op, 2 * j + 1)];
+                }
             uint32_t scale_word = 0u;
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
                     const int ek = e0 - 4 * (2 * pass + kk) - (2 * pass + kk > 0 ? 1 : 0);
-                    const float half = __uint_as_float((uint32_t)(127 + ek - 1) << 23);
-                    const float inv = __uint_as_float((uint32_t)(127 - ek + 1) << 23);
+                    const float piece_scale = __uint_as_float((uint32_t)(127 + ek) << 23);
                     // the key operand holds code / 2: one more factor of two in the scale byte
                     scale_word |= (uint32_t)(127 + ek + 1) << (8 * (2 * pass + kk));
 #pragma unroll
                     for (int op = 0; op < 4; ++op) {       // MFMA jm = op >> 1, lane half hw = op & 1
                         const int jm = op >> 1, hw = op & 1;
-                        uint32_t d[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+                        const u32x6 d = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(xe[op], xo[op], piece_scale);
+                        const f32x32 held = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(d, piece_scale);
 #pragma unroll
-                        for (int j = 0; j < 32; ++j) {
-                            // element j of the lane's FP4 key operand: word 2 jm + (j >> 4), 2-bit field
-                            // 2 (j & 7) + ((j >> 3) & 1) of it; the channel that field holds (see key_pair)
-                            const int wd = 2 * jm + (j >> 4), f = 2 * (j & 7) + ((j >> 3) & 1);
-                            const int pr = f & 7, slab = 2 * wd + (pr >> 2);
-                            const int c = 16 * slab + 8 * hw + 2 * (pr & 3) + (f >> 3);
-                            const float nn = fminf(fmaxf(rintf(x[c] * inv), -15.0f), 15.0f);
-                            x[c] = fmaf(-nn, half, x[c]);
-                            // E2M3 code of |n| / 2: 4 n below 4, 2 n + 8 below 8, n + 16 from there on
-                            const float an = fabsf(nn);
-                            const uint32_t mag = (uint32_t)fminf(fminf(4.0f * an, fmaf(2.0f, an, 8.0f)), an + 16.0f);
-                            const uint32_t code = mag | ((__float_as_uint(nn) >> 26) & 32u);
-                            const int bit = 6 * j;
-                            d[bit >> 5] |= code << (bit & 31);
-                            if ((bit & 31) > 26) d[(bit >> 5) + 1] |= code >> (32 - (bit & 31));
+                        for (int j = 0; j < 16; ++j) {
+                            xe[op][j] -= held[2 * j];
+                            xo[op][j] -= held[2 * j + 1];
                         }
                         uint32_t *pd = q_stage + prow * kQRowWords + (2 * kk + jm) * 12 + hw * 6;
 #pragma unroll
@@ -301,7 +308,9 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             }
             // the row sum of what the pieces hold: the sum of q~ minus the sum of what is left of it
 #pragma unroll
-            for (int c = 0; c < kPrepCh; ++c) ssum -= x[c];
+            for (int op = 0; op < 4; ++op)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) ssum -= xe[op][j] + xo[op][j];
             row_scal[4 * prow + 3] = __uint_as_float(scale_word);
         } else if constexpr (kLoFp8) {
             static_assert(!kLoFp8 || kPrepLanes == 1, "one lane prepares a whole row");
