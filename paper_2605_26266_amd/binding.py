@@ -227,8 +227,8 @@ def kvq_quantize_append_static(cache: Cache, k: torch.Tensor, v: torch.Tensor,
 
 def _workspace(cache: Cache, nbytes: int, stream: Optional[torch.cuda.Stream]) -> Optional[torch.Tensor]:
     """Device memory for the partial results of one call, from the allocator pool of the stream that the call runs on: it
-    may be reused by later work on that stream as soon as the tensor is gone.  None where there is none to be had: the
-    call then runs unsplit."""
+    may be reused by later work on that stream as soon as the tensor is gone (under torch.cuda.graph it comes from the
+    graph's own pool).  None where there is none to be had: the call then runs unsplit."""
     dev = cache.storage.device
     on = torch.cuda.current_stream() if stream is None else stream
     if on.device != dev:

@@ -458,8 +458,10 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
     hipError_t e = route == Route::per_token ? kvq::launch_attention_mfma(a, sp, s)
                    : route == Route::group   ? kvq::launch_attention_mfma_group(a, sp, s)
                                              : kvq::launch_attention_f32(a, sp, s);
-    if (e == hipSuccess && sp.pieces > 0) e = kvq::launch_attention_merge(a, sp, s);
-    if (e == hipSuccess && a.status) {
+    if (e != hipSuccess) return KVQ_ERR_HIP;
+    if (sp.pieces > 0) {
+        e = route == Route::f32 ? kvq::launch_attention_merge(a, sp, s) : kvq::launch_attention_merge_or_vector(a, sp, s);
+    } else if (a.status) {
         // A cache that has ever stored a zero-point beyond the 16-bit kernels' domain carries a flag: the launch
         // above has then returned without writing anything, and this one, which otherwise returns at once, does the work.
         a.only_if_flagged = 1;

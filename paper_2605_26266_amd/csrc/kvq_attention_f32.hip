@@ -368,6 +368,8 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             f32x16 s;
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[v] = 0.0f;
+            const int tok_max = (int)(last - key0 < kTileTokens - 1 ? last - key0 : kTileTokens - 1);
+            const T *const v_tile = v_base + key0 * a.stride_token;
             const T *kp = k_base + key * a.stride_token;
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -383,9 +385,9 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             weigh(s, l_r);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int64_t tok = key0 + 8 * (v >> 2) + 4 * hh + (v & 3);
-                const bool in = tok < a.n_cur;     // a weight of 0 must not meet another token's infinity
-                const T *vp = v_base + (in ? tok : last) * a.stride_token;
+                const int tok = 8 * (v >> 2) + 4 * hh + (v & 3);
+                const bool in = tok <= tok_max;            // a weight of 0 must not meet another token's infinity
+                const T *vp = v_tile + (in ? tok : tok_max) * a.stride_token;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     const float vv = Io<T>::load(vp + 32 * b);

@@ -18,6 +18,7 @@
 
 namespace kvq {
 namespace {
+#include "kvq_merge.h"
 
 template <int D> __device__ inline void fwht_lds(float *buf, int c)
 {
@@ -211,22 +212,15 @@ __device__ inline SimtRow<D, BITS, T> prepare_row(const AttentionArgs &a, int qh
     return r;
 }
 
-template <int D, int BITS, typename T>
-__global__ __launch_bounds__(D) void attention_simt_kernel(AttentionArgs a)
+// One query row, by the D threads of a workgroup.
+template <int D, int BITS, typename T> __device__ inline void attend_row(const AttentionArgs &a, int qhead, int64_t row)
 {
     __shared__ float q_rot[D];   // Hn q
     __shared__ float q_raw[D];
     __shared__ float p_blk[D];
     __shared__ float scratch[D];
     __shared__ float corr_g[4];  // softmax_scale^2 / 24 * nu_j per group (at most 4 groups)
-    // Enqueued behind a matrix-core launch: there is work only if that launch has stood back (flagged cache).
-    if (a.only_if_flagged && !cache_flagged(a.status)) return;
     const int c = threadIdx.x;
-    const int qhead = blockIdx.y;               // query head
-    // One row per workgroup in an ordinary launch (gridDim.x = m); the gated launch behind a matrix-core kernel
-    // has fewer workgroups, which walk the rows (its usual fate is to return above, and a small grid does that
-    // in a few microseconds where one workgroup per row took 40 at 200 000 rows).
-    for (int64_t row = blockIdx.x; row < a.m; row += gridDim.x) {
     __syncthreads();   // the previous row's shared arrays are no longer read
     // current keys this row sees (all of them, or under the causal mask those up to its own position)
     int64_t n_vis = a.n_cur;
@@ -279,7 +273,31 @@ __global__ __launch_bounds__(D) void attention_simt_kernel(AttentionArgs a)
     T *op = static_cast<T *>(a.out) + row * a.q_stride_token + (int64_t)qhead * a.q_stride_head;
     Io<T>::store(op + c, acc * inv);
     if (a.mass_cached && c == 0) a.mass_cached[(int64_t)qhead * a.m + row] = sum_s * inv;
+}
+
+// One row per workgroup in an ordinary launch (gridDim.x = m); the gated launch behind a matrix-core kernel has fewer
+// workgroups, which walk the rows (its usual fate is to return at once, and a small grid does that in a few
+// microseconds where one workgroup per row took 40 at 200 000 rows).
+template <int D, int BITS, typename T>
+__global__ __launch_bounds__(D) void attention_simt_kernel(AttentionArgs a)
+{
+    // Enqueued behind a matrix-core launch: there is work only if that launch has stood back (flagged cache).
+    if (a.only_if_flagged && !cache_flagged(a.status)) return;
+    for (int64_t row = blockIdx.x; row < a.m; row += gridDim.x) attend_row<D, BITS, T>(a, blockIdx.y, row);
+}
+
+// Behind a 16-bit matrix-core launch with split units: puts the pieces together, or on a flagged cache, where that launch
+// has stood back, computes the call.  (One launch for both: with a gated vector launch of its own the step of 8 heads x
+// 1024 rows x (4096 + 1024) keys took 66.4 us, with this 64.0 us.)
+template <int BITS> __global__ __launch_bounds__(kMergeThreads) void attention_merge_or_vector_kernel(AttentionArgs a, SplitArgs sp)
+{
+    static_assert(kMergeThreads == 128, "a thread per channel of head_dim 128");
+    if (!cache_flagged(a.status)) {
+        merge_rows<128, uint16_t>(a, sp);
+        return;
     }
+    const int64_t rows = a.m * a.cv.num_heads * a.q_per_kv;
+    for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) attend_row<128, BITS, uint16_t>(a, (int)(i / a.m), i % a.m);
 }
 
 // Attention-level diagnostics (attention stealing; appendices on the Jensen-Shannon divergence of the
@@ -417,6 +435,13 @@ hipError_t launch_attention_simt(const AttentionArgs &a, hipStream_t stream)
     KVQ_A(64, 4)
 #undef KVQ_A
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_attention_merge_or_vector(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
+{
+    if (a.cv.head_dim != 128 || a.cv.io_dtype != KVQ_BF16) return hipErrorInvalidValue;
+    if (a.cv.bits == 2) return launch_kernel(attention_merge_or_vector_kernel<2>, merge_grid(a, sp), dim3(kMergeThreads), 0, stream, a, sp);
+    return launch_kernel(attention_merge_or_vector_kernel<4>, merge_grid(a, sp), dim3(kMergeThreads), 0, stream, a, sp);
 }
 
 hipError_t launch_diagnostics_simt(const AttentionArgs &a, const void *k_ref, const void *v_ref, float *diag,

@@ -235,8 +235,10 @@ inline size_t split_workspace_bytes(const SplitArgs &sp, int head_dim)
 __device__ inline bool cache_flagged(const uint32_t *status) { return status != nullptr && *status != 0u; }
 hipError_t launch_attention_simt(const AttentionArgs &a, hipStream_t stream);
 hipError_t launch_attention_mfma(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
-// Combines the pieces of the split units of the launch in front of it (sp.pieces > 0).
+// Combine the pieces of the split units of the launch in front (sp.pieces > 0): of an fp32 launch; of a 16-bit launch, or
+// in its place on a flagged cache.
 hipError_t launch_attention_merge(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
+hipError_t launch_attention_merge_or_vector(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
 // Per (head, row) [P_S unquantized, P_S quantized, JSD, output MSE] against the unquantized cached k_ref / v_ref
 // ([cache_len][H][d], strides of k_cur); a.out and a.mass_cached are not used.
 hipError_t launch_diagnostics_simt(const AttentionArgs &a, const void *k_ref, const void *v_ref, float *diag,

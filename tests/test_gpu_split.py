@@ -85,3 +85,26 @@ def test_too_small_a_workspace_means_no_split():
     ref, ref_mass = _call(cache, 0, 480, q, q, q, 1, False, None)
     assert torch.equal(out, ref) and torch.equal(mass, ref_mass)
     assert (short == 0x5A).all()
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+def test_split_call_on_a_flagged_cache_is_served_by_the_vector_kernel(bits):
+    """Zero-points beyond the 16-bit kernels' domain: the merge launch computes the call in place of the pieces."""
+    heads, tokens, rows = 8, 1500, 900
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    k = torch.randn((tokens, heads, 128), generator=gen, device=DEV) * 1e-5
+    k[..., 0] += 40.0                                  # a large offset after the rotation, a minute range
+    k = k.to(torch.bfloat16)
+    v, q, cur = (torch.randn((n, heads, 128), generator=gen, device=DEV).to(torch.bfloat16) for n in (tokens, rows, 64))
+    cache = B.Cache(B.make_desc(heads, 128, bits, tokens, B.KVQ_BF16), DEV)
+    B.kvq_quantize_append(cache, k, v)
+    assert float(B.export_all(cache, 0)[2].abs().max()) > 70000.0
+    q = q * 0.02
+    assert B.lib().kvq_attention_workspace_bytes(cache.handle, 0, tokens, rows, 64, 1) > 0
+    out, mass = torch.empty_like(q), torch.empty((heads, rows), dtype=torch.float32, device=DEV)
+    ref, ref_mass = torch.empty_like(out), torch.empty_like(mass)
+    B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass)
+    B.kvq_chunk_attention_fp32(cache, 0, tokens, q, cur, cur, ref, ref_mass)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and torch.equal(mass, ref_mass)
