@@ -94,8 +94,8 @@ struct KernelCost {
     int tiles_step;    // tiles that a workgroup works on side by side
     double tile, fixed;
 };
-constexpr KernelCost kCost16{256, 1, 1.0, 30.0};
-constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 8, 0.64, 8.0}, kCostF32Dim128{kvq::kF32Rows, 8, 1.25, 10.0};
+constexpr KernelCost kCostPerToken{256, 1, 1.0, 22.0}, kCostGroup{256, 1, 1.35, 26.0};
+constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 8, 0.64, 8.0}, kCostF32Dim128{kvq::kF32Rows, 8, 1.25, 14.0};
 
 struct Plan {
     kvq::SplitArgs sp;
@@ -155,7 +155,8 @@ Route route_of(const kvq_cache_desc &d, const kvq::CacheView &cv)
 }
 const KernelCost &cost_of(Route r, int head_dim)
 {
-    return r != Route::f32 ? kCost16 : head_dim == 64 ? kCostF32Dim64 : kCostF32Dim128;
+    if (r == Route::f32) return head_dim == 64 ? kCostF32Dim64 : kCostF32Dim128;
+    return r == Route::group ? kCostGroup : kCostPerToken;
 }
 
 // Kernel and grid of a call.  A call with a few rows per key/value head (the last tokens of a prompt, a decoded token)
