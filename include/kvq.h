@@ -162,7 +162,7 @@ kvq_status kvq_quantize_append(kvq_cache *cache, const void *k, const void *v, i
  * kvq_quantize_append for callers that cannot allocate device memory or bring a work space along: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same results.  The
  * difference is where an append to a KVQ_KEYS_PER_CHANNEL cache keeps its work space (per head and channel the
- * range of the block being appended, L / range and the zero-point: 32 bytes each): not in the cache storage but in
+ * range of the block being appended; 32 bytes are set aside for each): not in the cache storage but in
  * a static device array inside the library, 256 KiB per GPU, held until the process ends.  That array serves
  * num_heads * head_dim <= 8192; a larger cache gets KVQ_ERR_CAPACITY and nothing is enqueued.  The call allocates
  * and frees nothing, on the host side it only looks the array's device address up (once per device).  All calls

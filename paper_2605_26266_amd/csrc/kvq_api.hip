@@ -244,15 +244,13 @@ kvq_status kvq_cache_create(const kvq_cache_desc *desc, void *dev_mem, size_t by
     v.kc_scale = v.kc_zero = nullptr;
     v.k_block = nullptr;
     v.kc_range = nullptr;
-    v.kc_inv = v.kc_z = nullptr;
     if (desc->key_axis == KVQ_KEYS_PER_CHANNEL) {
         // p stands after the four fp32 arrays of KVQ_META_FP32: a multiple of 128 bytes from a 256-byte base
         p = static_cast<char *>(dev_mem) + 2 * code_bytes + 4 * meta_bytes;
         const int64_t hd = H * desc->head_dim;
         v.max_blocks = (int32_t)max_blocks_of(c->cap32);
         v.kc_range = reinterpret_cast<unsigned long long *>(p); p += hd * 16;   // 8-byte types first
-        v.kc_inv = reinterpret_cast<double *>(p); p += hd * 8;
-        v.kc_z = reinterpret_cast<double *>(p); p += hd * 8;
+        p += hd * 16;   // (not used: keeps the size and the order of the storage)
         v.kc_scale = reinterpret_cast<float *>(p); p += (int64_t)v.max_blocks * hd * 4;
         v.kc_zero = reinterpret_cast<float *>(p); p += (int64_t)v.max_blocks * hd * 4;
         v.k_block = reinterpret_cast<uint32_t *>(p);

@@ -56,7 +56,6 @@ struct CacheView {
     float *kc_scale, *kc_zero;       // [max_blocks][H][d]  per block slot
     uint32_t *k_block;               // [cap32]             block slot of the token at each ring position
     unsigned long long *kc_range;    // [H][d][2]           work space of the append in flight: min, max (ordered keys)
-    double *kc_inv, *kc_z;           // [H][d]              work space: L / range and the zero-point, per channel
     // Status block at the end of the storage (kStatusBytes).  Word 0: sticky, set by the quantize kernels when a stored
     // zero-point is too large for the matrix-core attention kernels (kMatrixZeroLimit), read by every attention launch.
     uint32_t *status;
@@ -158,7 +157,7 @@ hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t
 
 // Launchers implemented in the kernel translation units.  All return hipError_t of the launch.
 // block_slot: slot of the block this append creates (KVQ_KEYS_PER_CHANNEL caches only).
-// static_scratch: the per-channel work space of the append (ranges, L / range, zero-points per head and channel)
+// static_scratch: the per-channel work space of the append (the ranges per head and channel)
 // is taken from the library's static device array instead of the cache storage.
 hipError_t launch_quantize_append(const CacheView &cv, const void *k, const void *v, int64_t old_len,
                                   int64_t n_tokens, int64_t stride_token, int64_t stride_head, int block_slot,

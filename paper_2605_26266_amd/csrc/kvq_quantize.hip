@@ -24,7 +24,7 @@ namespace kvq {
 namespace {
 
 // Work space of kvq_quantize_append_static: per (head, channel) the range of the block being appended (two ordered
-// 64-bit keys), L / range and the zero-point -- 32 bytes each, for at most kStaticScratchChannels of them (256 KiB,
+// 64-bit keys; 32 bytes are set aside for each), for at most kStaticScratchChannels of them (256 KiB,
 // held by every GPU the library runs on until the process ends).  In host code this name is only a handle for
 // hipGetSymbolAddress: the device address is looked up once per device (static_scratch_pointer) and every launch
 // takes that pointer as an argument.
@@ -186,13 +186,15 @@ __global__ void channel_range_init_kernel(CacheView cv)
     }
 }
 
-// Per-channel keys, step 2 of an append: (scale, zero-point) of every (head, channel) from the range that
-// step 1 left, in the same sequence of double operations as the per-token quantizer; the block's
-// metadata slot and the work space of the quantizing pass are written.
-__global__ void channel_params_kernel(CacheView cv, int block_slot)
+// Per-channel keys: L / range and zero-point of a channel (index i = head * d + channel) from the range that the range pass
+// of an append left, in the same sequence of double operations as the per-token quantizer, and the fp32 step stored for
+// it.  Every workgroup of the quantizing pass works the channels of its head out for itself: a launch of its own for
+// them took 4.8 us of a 127 us step of 8 heads x 1024 tokens, two divisions per workgroup and channel take nothing.
+struct ChannelParams {
+    double inv, z, step;
+};
+__device__ inline ChannelParams channel_params(const CacheView &cv, int64_t i)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cv.num_heads * cv.head_dim) return;
     const double L = (double)((1 << cv.bits) - 1);
     const double norm = cv.head_dim == 64 ? 0.125 : 0.08838834764831845;
     double lo = order_value(cv.kc_range[2 * i]), hi = order_value(cv.kc_range[2 * i + 1]);
@@ -202,23 +204,19 @@ __global__ void channel_params_kernel(CacheView cv, int block_slot)
     }
     const bool degenerate = hi == lo;
     const double range = hi - lo;
-    const double inv = degenerate ? 0.0 : L / range;
-    const double step = degenerate ? 0.0 : range / L;
-    const double z = degenerate ? 0.0 : -__builtin_rint(lo * inv);
-    cv.kc_inv[i] = inv;
-    cv.kc_z[i] = z;
-    const int64_t slot = (int64_t)block_slot * cv.num_heads * cv.head_dim + i;
-    cv.kc_scale[slot] = (float)(step * norm);
-    cv.kc_zero[slot] = (float)z;
-    flag_large_zero(cv, (float)z);
+    ChannelParams p;
+    p.inv = degenerate ? 0.0 : L / range;
+    p.step = (degenerate ? 0.0 : range / L) * norm;
+    p.z = degenerate ? 0.0 : -__builtin_rint(lo * p.inv);
+    return p;
 }
 
 // GROUP == 0: one fp32 (scale, zero-point) per token.  GROUP > 0: one FP8 E4M3 scale and one BF16
 // zero-point per GROUP rotated channels; codes are taken with the stored values.
 // KMODE (per-channel keys, GROUP == 0 only): 0 = keys per token; 1 = range pass: the keys are rotated and
 // the minimum / maximum of every channel over the appended tokens goes to cv.kc_range, nothing else is
-// written; 2 = the keys take (L / range, zero-point) per channel from cv.kc_inv / cv.kc_z, the values are
-// quantized per token as always, and every token records its block slot.
+// written; 2 = the keys take (L / range, zero-point) per channel from cv.kc_range, which the first tile's workgroup of
+// a head also writes to the block's metadata slot, the values are quantized per token as always, and every token records its block slot.
 template <int D, int BITS, int GROUP, typename T, int KMODE = 0>
 __global__ __launch_bounds__(256) void quantize_append_kernel(CacheView cv, const T *__restrict__ k,
                                                              const T *__restrict__ v, int64_t old_len,
@@ -247,6 +245,21 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(CacheView cv, cons
     uint32_t *k_tile = cv.k_codes + ((int64_t)head * cv.cap_tiles + ptile) * (64 * WPL);
     uint32_t *v_tile = cv.v_codes + ((int64_t)head * cv.cap_tiles + ptile) * (64 * WPL);
     const double norm = D == 64 ? 0.125 : 0.08838834764831845;  // 1/sqrt(d) rounded to double
+    __shared__ double ch_inv[KMODE == 2 ? D : 1], ch_z[KMODE == 2 ? D : 1];
+    if constexpr (KMODE == 2) {
+        if (threadIdx.x < D) {
+            const ChannelParams p = channel_params(cv, (int64_t)head * D + threadIdx.x);
+            ch_inv[threadIdx.x] = p.inv;
+            ch_z[threadIdx.x] = p.z;
+            if (blockIdx.x == 0) {
+                const int64_t slot = ((int64_t)block_slot * cv.num_heads + head) * D + threadIdx.x;
+                cv.kc_scale[slot] = (float)p.step;
+                cv.kc_zero[slot] = (float)p.z;
+                flag_large_zero(cv, (float)p.z);
+            }
+        }
+        __syncthreads();
+    }
 
 #pragma unroll 1
     for (int pass = 0; pass < (KMODE == 1 ? 1 : 2); ++pass) {
@@ -365,8 +378,8 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(CacheView cv, cons
         for (int i = 0; i < EPL; ++i) {
             double inv_i = inv, z_i = z;
             if (KMODE == 2 && pass == 0) {   // per-channel keys: this lane's channels are EPL * l8 + i
-                inv_i = cv.kc_inv[head * D + l8 * EPL + i];
-                z_i = cv.kc_z[head * D + l8 * EPL + i];
+                inv_i = ch_inv[l8 * EPL + i];
+                z_i = ch_z[l8 * EPL + i];
             }
             double c = __builtin_rint(x[i] * inv_i) + z_i;
             c = c < 0.0 ? 0.0 : c;
@@ -786,14 +799,12 @@ hipError_t launch_q(const CacheView &cv, const void *k, const void *v, int64_t o
     const dim3 block(256);
     const T *kp = static_cast<const T *>(k), *vp = static_cast<const T *>(v);
     if (cv.key_axis == KVQ_KEYS_PER_CHANNEL) {
-        // ranges of the block -> per-channel parameters -> codes (keys per channel, values per token); the sequence
-        // stops at the first launch that fails (the cache's token count is only advanced when all four are enqueued)
+        // ranges of the block -> per-channel parameters and codes (keys per channel, values per token); the sequence
+        // stops at the first launch that fails (the cache's token count is only advanced when all three are enqueued)
         const dim3 nb((unsigned)((cv.num_heads * cv.head_dim + 255) / 256));
         hipError_t e = launch_kernel(channel_range_init_kernel, nb, block, 0, stream, cv);
         if (e != hipSuccess) return e;
         e = launch_kernel(quantize_append_kernel<D, BITS, 0, T, 1>, grid, block, 0, stream, cv, kp, vp, old_len, n, st, sh, block_slot);
-        if (e != hipSuccess) return e;
-        e = launch_kernel(channel_params_kernel, nb, block, 0, stream, cv, block_slot);
         if (e != hipSuccess) return e;
         return launch_kernel(quantize_append_kernel<D, BITS, 0, T, 2>, grid, block, 0, stream, cv, kp, vp, old_len, n, st, sh, block_slot);
     }
@@ -830,17 +841,14 @@ hipError_t launch_quantize_append(const CacheView &cv_in, const void *k, const v
 {
     CacheView cv = cv_in;
     if (static_scratch && cv.key_axis == KVQ_KEYS_PER_CHANNEL) {
-        // The three work arrays move to the static array; the first launch of the append fills the ranges with
+        // The work space moves to the static array; the first launch of the append fills the ranges with
         // their empty values, so what an earlier call left there does not matter.
         const int64_t hd = (int64_t)cv.num_heads * cv.head_dim;
         if (hd > kStaticScratchChannels) return hipErrorInvalidValue;   // (the entry point has refused this already)
         void *base = nullptr;
         const hipError_t e = static_scratch_pointer(&base);
         if (e != hipSuccess) return e;
-        unsigned char *p = static_cast<unsigned char *>(base);
-        cv.kc_range = reinterpret_cast<unsigned long long *>(p);
-        cv.kc_inv = reinterpret_cast<double *>(p + hd * 16);
-        cv.kc_z = reinterpret_cast<double *>(p + hd * 24);
+        cv.kc_range = static_cast<unsigned long long *>(base);
     }
     const bool bf16 = cv.io_dtype == KVQ_BF16;
 #define KVQ_Q(D, B)                                                                                                         \
