@@ -214,8 +214,8 @@ kvq_status kvq_chunk_attention(const kvq_cache *cache, int64_t cache_start, int6
  *   causal               1: current key j is visible to query row r only if j <= r + n_cur - m (the
  *                        queries are the last m positions of the current block; requires n_cur >= m).
  *                        Cached keys are always visible.  A value that is not finite reaches the rows that see its
- *                        token and no others; only in the 16-bit matrix-core kernels (BF16 caches with head_dim 128) a
- *                        row that sees part of that token's tile of 32 current keys may become NaN with them.
+ *                        token and no others; only in the 16-bit matrix-core kernels (BF16 caches with head_dim 128) an
+ *                        earlier row of the same block of 256 may become NaN with them.
  *   q_stride_token/head  element strides of q and out (stride_token / stride_head of the call are those
  *                        of k_cur and v_cur); 0, 0 = the same strides.
  * opts == NULL is kvq_chunk_attention.  mass_cached: [num_heads * q_heads_per_kv_head][m].

@@ -271,11 +271,22 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             f32x16 s;
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[v] = 0.0f;
+            // The square of an fp32 step overflows beyond 2^64, where the correction can be ordinary (tiny queries) or off:
+            // tiles with such a step take it factor by factor, as the vector kernel does.  (FP8 steps end at 448.)
+            if (!FP8 && __builtin_expect(__any(ks[0] >= 0x1p64f), 0)) {
+                const float upper = other_half(corr[0]), c = hh ? upper : corr[0];
 #pragma unroll
-            for (int j = 0; j < (G + 1) / 2; ++j) {
-                const float second = 2 * j + 1 < G ? ks[(2 * j + 1) % G] : 0.0f;
-                const float st = hh ? second : ks[2 * j];
-                s = mfma_f32(st * st, corr[j], s);
+                for (int v = 0; v < 16; ++v) {
+                    const float st = __shfl(ks[0], 8 * (v >> 2) + 4 * hh + (v & 3));
+                    s[v] = c * st * st;
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < (G + 1) / 2; ++j) {
+                    const float second = 2 * j + 1 < G ? ks[(2 * j + 1) % G] : 0.0f;
+                    const float st = hh ? second : ks[2 * j];
+                    s = mfma_f32(st * st, corr[j], s);
+                }
             }
 #pragma unroll
             for (int i = 0; i < NI; ++i) {

@@ -85,3 +85,28 @@ def test_what_the_window_leaves_out_does_not_reach_the_result():
     assert torch.isfinite(out).all() and torch.isfinite(ref).all()
     torch.testing.assert_close(out, ref, rtol=1e-4, atol=1e-5)
     torch.testing.assert_close(mass, ref_mass, rtol=5e-5, atol=1e-9)
+
+
+@pytest.mark.parametrize("correction", [0, 1])
+@pytest.mark.parametrize("dim,bits", [(64, 2), (128, 4)])
+def test_steps_whose_square_overflows(dim, bits, correction):
+    """Keys of about 1e19 .. 1e20 against queries as small: the scores and the correction are ordinary numbers."""
+    heads, tokens, rows = 2, 150, 40
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(2)
+    k = torch.randn((tokens, heads, dim), generator=gen, device=DEV)
+    k *= 10.0 ** (18.5 + 1.5 * torch.rand((tokens, 1, 1), generator=gen, device=DEV))      # steps on either side of 2^64
+    v, cur = (torch.randn((n, heads, dim), generator=gen, device=DEV) for n in (tokens, 20))
+    q = torch.randn((rows, heads, dim), generator=gen, device=DEV) * 4e-20
+    cache = B.Cache(B.make_desc(heads, dim, bits, 160, B.KVQ_FP32), DEV)
+    B.kvq_quantize_append(cache, k, v)
+    step = B.export_all(cache, 0)[1]
+    assert 0 < int((step >= 2.0 ** 64).sum()) < step.numel()
+    out, mass = torch.empty_like(q), torch.empty((heads, rows), device=DEV)
+    ref, ref_mass = torch.empty_like(out), torch.empty_like(mass)
+    B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass, correction=correction)
+    B.kvq_chunk_attention_fp32(cache, 0, tokens, q, cur, cur, ref, ref_mass, correction=correction)
+    assert torch.isfinite(ref).all() and torch.isfinite(out).all()
+    # |q|^2 sigma^2 / 24 is about 1e-41 here, 2^13 steps of the denormal grid: the correction (below 1) is good to 2^-13
+    torch.testing.assert_close(out, ref, rtol=1e-3, atol=1e-3)
+    torch.testing.assert_close(mass, ref_mass, rtol=1e-3, atol=1e-6)
