@@ -225,18 +225,30 @@ def kvq_quantize_append_static(cache: Cache, k: torch.Tensor, v: torch.Tensor,
                                             _stream(stream)), "kvq_quantize_append_static")
 
 
+def _allocator_takes_part_in_capture(dev: torch.device) -> bool:
+    """Whether torch's allocator gives out memory of a graph's own pool on the (capturing) current stream: it does in a capture
+    that torch.cuda.graph or CUDAGraph.capture_begin began, and knows nothing of one that was begun by other means."""
+    probe = torch.empty(1, dtype=torch.uint8, device=dev)
+    for segment in torch.cuda.memory_snapshot():
+        if 0 <= probe.data_ptr() - segment["address"] < segment["total_size"]:
+            return tuple(segment.get("segment_pool_id", (0, 0))) != (0, 0)
+    return False
+
+
 def _workspace(cache: Cache, nbytes: int, stream: Optional[torch.cuda.Stream]) -> Optional[torch.Tensor]:
     """Device memory for the partial results of one call, from the allocator pool of the stream that the call runs on: it
-    may be reused by later work on that stream as soon as the tensor is gone (under torch.cuda.graph it comes from the
-    graph's own pool).  None where there is none to be had: the call then runs unsplit."""
+    may be reused by later work on that stream as soon as the tensor is gone.  Under torch.cuda.graph it comes from the
+    graph's own pool, which lives as long as the graph.  None where there is none to be had, and in captures begun
+    outside torch, whose graph would go on writing to memory that the allocator has handed to others: the call then
+    runs unsplit and allocates nothing."""
     dev = cache.storage.device
     on = torch.cuda.current_stream() if stream is None else stream
     if on.device != dev:
         return None
     try:
-        if stream is None:
-            return torch.empty(nbytes, dtype=torch.uint8, device=dev)
-        with torch.cuda.stream(stream):
+        with torch.cuda.stream(stream):          # (None: the current stream stays)
+            if torch.cuda.is_current_stream_capturing() and not _allocator_takes_part_in_capture(dev):
+                return None
             return torch.empty(nbytes, dtype=torch.uint8, device=dev)
     except torch.OutOfMemoryError:
         return None

@@ -713,8 +713,8 @@ def test_attention_diagnostics(P, name, io, bits, group, fp8):
 
 
 def test_attention_replayed_from_a_graph(P):
-    """The launching calls only enqueue kernels on the stream they are given (no allocation, no memset,
-    no host synchronisation), so a serving loop can capture them: a captured quantize-free step (attention
+    """The launching calls only enqueue kernels on the stream they are given (no memset, no host synchronisation;
+    the work space of a split call comes from the graph's own pool), so a serving loop can capture them: a captured quantize-free step (attention
     over a filled cache) is replayed three times with new queries, eager work in between, and every replay
     must equal the eager result bit for bit and the oracle to the usual bar."""
     import oracle

@@ -108,3 +108,66 @@ def test_split_call_on_a_flagged_cache_is_served_by_the_vector_kernel(bits):
     B.kvq_chunk_attention_fp32(cache, 0, tokens, q, cur, cur, ref, ref_mass)
     torch.cuda.synchronize()
     assert torch.equal(out, ref) and torch.equal(mass, ref_mass)
+
+
+def _c_graph(stream, body):
+    """A graph recorded through the HIP runtime, without torch (the library's handle finds the runtime it is linked to)."""
+    hip, handle = B.lib(), ctypes.c_void_p(int(stream.cuda_stream))
+    graph, executable = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(handle, 0) == 0
+    with torch.cuda.stream(stream):
+        body()
+    assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert hip.hipGraphInstantiate(ctypes.byref(executable), graph, None, None, 0) == 0
+    return lambda: hip.hipGraphLaunch(executable, handle)
+
+
+def test_a_capture_begun_outside_torch_records_no_workspace():
+    """The replays of such a graph come at times when torch has given the memory of a work space to other tensors."""
+    heads, tokens, rows = 2, 2000, 300
+    x, q, cur = (torch.randn((n, heads, 128), device=DEV).to(torch.bfloat16) for n in (tokens, rows, 64))
+    cache = B.Cache(B.make_desc(heads, 128, 2, tokens, B.KVQ_BF16), DEV)
+    B.kvq_quantize_append(cache, x, x)
+    nbytes = B.lib().kvq_attention_workspace_bytes(cache.handle, 0, tokens, rows, 64, 1)
+    assert nbytes > 0
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    out, mass = torch.empty_like(q), torch.empty((heads, rows), dtype=torch.float32, device=DEV)
+    B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass, stream=stream)     # every kernel has run outside a capture
+    whole, whole_mass = _call(cache, 0, tokens, q, cur, cur, 1, False, None)
+    torch.cuda.synchronize()
+    held = torch.cuda.memory_allocated()
+    replay = _c_graph(stream, lambda: B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass, stream=stream))
+    assert torch.cuda.memory_allocated() == held
+    for _ in range(3):
+        with torch.cuda.stream(stream):          # takes the memory that a work space of this stream would have had
+            others = [torch.full((nbytes,), 0x5A, dtype=torch.uint8, device=DEV) for _ in range(2)]
+            out.fill_(float("nan"))
+            mass.fill_(float("nan"))
+        assert replay() == 0
+        torch.cuda.synchronize()
+        assert all(bool((o == 0x5A).all()) for o in others)
+        assert torch.equal(out.float(), whole) and torch.equal(mass, whole_mass)
+        del others
+
+
+def test_a_capture_by_torch_stays_split():
+    heads, tokens, rows = 2, 2000, 300
+    x, q, cur = (torch.randn((n, heads, 128), device=DEV).to(torch.bfloat16) for n in (tokens, rows, 64))
+    cache = B.Cache(B.make_desc(heads, 128, 2, tokens, B.KVQ_BF16), DEV)
+    B.kvq_quantize_append(cache, x, x)
+    out, mass = torch.empty_like(q), torch.empty((heads, rows), dtype=torch.float32, device=DEV)
+    B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass)
+    eager, eager_mass = out.clone(), mass.clone()
+    whole_mass = _call(cache, 0, tokens, q, cur, cur, 1, False, None)[1]
+    assert not torch.equal(eager_mass, whole_mass)          # the sums run in another order
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        mass.fill_(float("nan"))
+        torch.full((1 << 24,), 0x5A, dtype=torch.uint8, device=DEV)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager) and torch.equal(mass, eager_mass)
