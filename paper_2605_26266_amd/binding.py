@@ -235,12 +235,21 @@ def _allocator_takes_part_in_capture(dev: torch.device) -> bool:
     return False
 
 
-def _workspace(cache: Cache, nbytes: int, stream: Optional[torch.cuda.Stream]) -> Optional[torch.Tensor]:
-    """Device memory for the partial results of one call, from the allocator pool of the stream that the call runs on: it
-    may be reused by later work on that stream as soon as the tensor is gone.  Under torch.cuda.graph it comes from the
+# Calls over at most this many keys are never split (fewer tiles than any split repays), so the library is not asked about
+# them: the question costs 1 us of a 15 us call.
+_NEVER_SPLIT_KEYS = 256
+
+
+def _workspace(cache: Cache, cache_start: int, cache_len: int, rows: int, n_cur: int, ratio: int,
+               stream: Optional[torch.cuda.Stream]) -> Optional[torch.Tensor]:
+    """Device memory for the partial results of one call that is to be split, from the allocator pool of the stream that it
+    runs on: it may be reused by later work on that stream as soon as the tensor is gone.  Under torch.cuda.graph it comes from the
     graph's own pool, which lives as long as the graph.  None where there is none to be had, and in captures begun
     outside torch, whose graph would go on writing to memory that the allocator has handed to others: the call then
     runs unsplit and allocates nothing."""
+    nbytes = lib().kvq_attention_workspace_bytes(cache.handle, cache_start, cache_len, rows, n_cur, ratio)
+    if nbytes == 0:
+        return None
     dev = cache.storage.device
     on = torch.cuda.current_stream() if stream is None else stream
     if on.device != dev:
@@ -254,19 +263,16 @@ def _workspace(cache: Cache, nbytes: int, stream: Optional[torch.cuda.Stream]) -
         return None
 
 
-def _launch(cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
-            opts, out, mass_cached, stream, where: str) -> None:
-    nbytes = lib().kvq_attention_workspace_bytes(cache.handle, int(cache_start), int(cache_len), q.shape[0], n_cur,
-                                                 opts.q_heads_per_kv_head if opts is not None else 1)
-    ws = _workspace(cache, nbytes, stream) if nbytes else None
+def _launch_split(cache: Cache, ws: torch.Tensor, cache_start: int, cache_len: int, q, k_cur, v_cur, n_cur, st, sh,
+                  softmax_scale, correction, opts, out, mass_cached, stream, where: str) -> None:
     _check(lib().kvq_chunk_attention_ws(
         cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur), _ptr(v_cur), q.shape[0], n_cur, st, sh,
-        float(softmax_scale), int(correction), None if opts is None else ctypes.byref(opts), out.data_ptr(),
-        _ptr(mass_cached), _ptr(ws), 0 if ws is None else nbytes, _stream(stream)), where)
+        float(softmax_scale), int(correction), opts, out.data_ptr(), _ptr(mass_cached), ws.data_ptr(), ws.numel(),
+        _stream(stream)), where)
 
 
 def _attention(fn, cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_cur, softmax_scale, correction,
-               out, mass_cached, stream):
+               out, mass_cached, stream, may_split=False):
     st, sh = _tok_head_strides(q)
     n_cur = 0 if k_cur is None else k_cur.shape[0]
     H, d = cache.desc.num_heads, cache.desc.head_dim
@@ -283,9 +289,11 @@ def _attention(fn, cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_c
         raise ValueError("q must be in the cache's io dtype")
     if mass_cached is not None and (mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous()):
         raise ValueError("mass_cached must be a contiguous float32 [heads][m] tensor")
-    if fn is None:
-        return _launch(cache, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction, None, out,
-                       mass_cached, stream, "kvq_chunk_attention")
+    if may_split and cache_len + n_cur > _NEVER_SPLIT_KEYS:
+        ws = _workspace(cache, int(cache_start), int(cache_len), q.shape[0], n_cur, 1, stream)
+        if ws is not None:
+            return _launch_split(cache, ws, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
+                                 None, out, mass_cached, stream, "kvq_chunk_attention")
     _check(fn(cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur), _ptr(v_cur), q.shape[0],
               n_cur, st, sh, float(softmax_scale), int(correction), out.data_ptr(), _ptr(mass_cached),
               _stream(stream)), "kvq_chunk_attention")
@@ -295,8 +303,8 @@ def kvq_chunk_attention(cache: Cache, cache_start: int, cache_len: int, q: torch
                         k_cur: Optional[torch.Tensor], v_cur: Optional[torch.Tensor], out: torch.Tensor,
                         mass_cached: Optional[torch.Tensor] = None, softmax_scale: float = 0.0,
                         correction: int = 1, stream: Optional[torch.cuda.Stream] = None) -> None:
-    _attention(None, cache, cache_start, cache_len, q, k_cur, v_cur, softmax_scale, correction,
-               out, mass_cached, stream)
+    _attention(lib().kvq_chunk_attention, cache, cache_start, cache_len, q, k_cur, v_cur, softmax_scale, correction,
+               out, mass_cached, stream, may_split=True)
 
 
 def kvq_chunk_attention_ex(cache: Cache, cache_start: int, cache_len: int, q: torch.Tensor,
@@ -326,8 +334,15 @@ def kvq_chunk_attention_ex(cache: Cache, cache_start: int, cache_len: int, q: to
     st, sh = _tok_head_strides(kv) if kv is not None and kv.shape[0] > 0 else (cache.desc.num_heads * cache.desc.head_dim, cache.desc.head_dim)
     opts = kvq_attention_opts(q.shape[1] // cache.desc.num_heads, int(bool(causal)), qst, qsh)
     n_cur = 0 if k_cur is None else k_cur.shape[0]
-    _launch(cache, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction, opts, out,
-            mass_cached, stream, "kvq_chunk_attention_ex")
+    if cache_len + n_cur > _NEVER_SPLIT_KEYS:
+        ws = _workspace(cache, int(cache_start), int(cache_len), q.shape[0], n_cur, opts.q_heads_per_kv_head, stream)
+        if ws is not None:
+            return _launch_split(cache, ws, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
+                                 ctypes.byref(opts), out, mass_cached, stream, "kvq_chunk_attention_ex")
+    _check(lib().kvq_chunk_attention_ex(cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur),
+                                        _ptr(v_cur), q.shape[0], n_cur, st, sh, float(softmax_scale), int(correction),
+                                        ctypes.byref(opts), out.data_ptr(), _ptr(mass_cached), _stream(stream)),
+           "kvq_chunk_attention_ex")
 
 
 def kvq_attention_diagnostics(cache: Cache, cache_start: int, cache_len: int, q: torch.Tensor,

@@ -48,3 +48,17 @@ def test_calls_that_are_never_split_and_invalid_ones_need_none():
             == B.KVQ_ERR_INVALID_ARG
     B.lib().kvq_cache_destroy(per_channel)
     B.lib().kvq_cache_destroy(h)
+
+
+@pytest.mark.parametrize("args", [(128, 2, B.KVQ_BF16, None, B.KVQ_META_FP32), (128, 4, B.KVQ_BF16, 32, B.KVQ_META_FP8_BF16),
+                                  (64, 2, B.KVQ_BF16, None, B.KVQ_META_FP32), (128, 4, B.KVQ_FP32, 64, B.KVQ_META_FP8_BF16)])
+def test_calls_the_binding_does_not_ask_about_are_not_split(args):
+    dim, bits, io, group, meta = args
+    for heads in (1, 3, 8, 31, 64):
+        h = _cache(heads, dim, bits, 1024, io_dtype=io, group_size=group, meta_format=meta)
+        for rows in (1, 5, 32, 33, 256, 300, 1024, 5000):
+            for current in (1, 64, 250, B._NEVER_SPLIT_KEYS):
+                for ratio in (1, 4, 64):
+                    # two tiles more than the keys fill: a cached window may begin and end inside a tile
+                    assert _bytes(h, rows, current, ratio) == 0 and _bytes(h, rows, current + 64, ratio) == 0
+        B.lib().kvq_cache_destroy(h)
