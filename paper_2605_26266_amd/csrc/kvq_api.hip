@@ -91,11 +91,12 @@ bool tensor_ok(const void *p, int64_t stride_token, int64_t stride_head, int hea
 // units after a full round: 2182 / 2286 / 2146 / 2219 / 2331 us with 1 / 2 / 5 / 6 / 9.
 struct KernelCost {
     int rows;          // query rows of a unit
+    int threads;       // of its workgroup
     int tiles_step;    // tiles that a workgroup works on side by side
     double tile, fixed;
 };
-constexpr KernelCost kCostPerToken{256, 1, 1.0, 22.0}, kCostGroup{256, 1, 1.35, 26.0};
-constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 8, 0.64, 8.0}, kCostF32Dim128{kvq::kF32Rows, 8, 1.25, 14.0};
+constexpr KernelCost kCostPerToken{256, 256, 1, 1.0, 22.0}, kCostGroup{256, 256, 1, 1.35, 26.0};
+constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 512, 8, 0.64, 8.0}, kCostF32Dim128{kvq::kF32Rows, 512, 8, 1.25, 14.0};
 
 struct Plan {
     kvq::SplitArgs sp;
@@ -118,14 +119,15 @@ Plan plan_split(const KernelCost &k, int64_t m, int64_t heads, int64_t ratio, in
         const int64_t steps = (tiles + s * k.tiles_step - 1) / (s * k.tiles_step);
         return (double)(steps * k.tiles_step) * k.tile + k.fixed;
     };
-    if (units > 0x7fffffff) return Plan{sp, kTooLarge};
+    auto launchable = [&](int64_t workgroups) { return workgroups * k.threads <= 0xffffffffll; };   // threads of a grid: 32 bits
+    if (!launchable(units)) return Plan{sp, kTooLarge};
     int64_t best = 1;
     double best_cost = rest > 0 ? piece_cost(1) : 0.0;
     for (int64_t s = 2; may_split && rest > 0 && s <= kMaxSplits && s <= tiles && rest * s <= kvq::kMaxPieces; ++s) {
         const int64_t rounds = (rest * s + kComputeUnits - 1) / kComputeUnits;
         const double cost = (double)rounds * piece_cost(s) + kMerge + kMergePerSplit * (double)s +
                             kMergePerBlock * (double)(rest * s * sp.part_blocks);
-        if (cost < best_cost) {
+        if (cost < best_cost && launchable(units - rest + rest * s)) {
             best_cost = cost;
             best = s;
         }

@@ -62,3 +62,12 @@ def test_calls_the_binding_does_not_ask_about_are_not_split(args):
                     # two tiles more than the keys fill: a cached window may begin and end inside a tile
                     assert _bytes(h, rows, current, ratio) == 0 and _bytes(h, rows, current + 64, ratio) == 0
         B.lib().kvq_cache_destroy(h)
+
+
+def test_grids_beyond_the_launch_limit_go_to_the_vector_kernel():
+    """A grid has fewer than 2^32 threads.  The fp32 kernel has 512 for 32 rows, the vector kernel 64 or 128 for one row of one
+    head of its second grid dimension: 268 heads x 1003552 rows are 8404748 units, too many for the former only."""
+    h = _cache(268, 64, 2, 1024)
+    assert _bytes(h, 31233 * 32, 5120) > 0          # 8370444 units, the last 12 split
+    assert _bytes(h, 31361 * 32, 5120) == 0
+    B.lib().kvq_cache_destroy(h)
