@@ -238,7 +238,8 @@ kvq_status kvq_chunk_attention_ex(const kvq_cache *cache, int64_t cache_start, i
  * memory, which the library does not allocate.  workspace: device memory, 256-byte aligned, used by this call only until
  * its work on the stream is done (calls that overlap need a work space each); NULL with 0 bytes, or fewer bytes than
  * kvq_attention_workspace_bytes returns for the call: nothing is split.  Results agree within the tolerance of the path
- * either way.  kvq_attention_workspace_bytes returns 0 where a call is not split.
+ * either way.  kvq_attention_workspace_bytes returns 0 where a call is not split (it is not told the correction: calls with
+ * the exact one, 2, never are), and at most 2048 * 256 * (head_dim + 4) * 4 bytes: 277 MB for head_dim 128.
  */
 kvq_status kvq_chunk_attention_ws(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,
                                   const void *q, const void *k_cur, const void *v_cur,

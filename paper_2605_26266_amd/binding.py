@@ -289,7 +289,7 @@ def _attention(fn, cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_c
         raise ValueError("q must be in the cache's io dtype")
     if mass_cached is not None and (mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous()):
         raise ValueError("mass_cached must be a contiguous float32 [heads][m] tensor")
-    if may_split and cache_len + n_cur > _NEVER_SPLIT_KEYS:
+    if may_split and cache_len + n_cur > _NEVER_SPLIT_KEYS and correction != 2:
         ws = _workspace(cache, int(cache_start), int(cache_len), q.shape[0], n_cur, 1, stream)
         if ws is not None:
             return _launch_split(cache, ws, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
@@ -334,7 +334,7 @@ def kvq_chunk_attention_ex(cache: Cache, cache_start: int, cache_len: int, q: to
     st, sh = _tok_head_strides(kv) if kv is not None and kv.shape[0] > 0 else (cache.desc.num_heads * cache.desc.head_dim, cache.desc.head_dim)
     opts = kvq_attention_opts(q.shape[1] // cache.desc.num_heads, int(bool(causal)), qst, qsh)
     n_cur = 0 if k_cur is None else k_cur.shape[0]
-    if cache_len + n_cur > _NEVER_SPLIT_KEYS:
+    if cache_len + n_cur > _NEVER_SPLIT_KEYS and correction != 2:      # (2 runs on the vector kernel)
         ws = _workspace(cache, int(cache_start), int(cache_len), q.shape[0], n_cur, opts.q_heads_per_kv_head, stream)
         if ws is not None:
             return _launch_split(cache, ws, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,

@@ -181,6 +181,25 @@ Choice choose(Route route, const kvq_cache_desc &d, int64_t m, int64_t ratio, in
     return Choice{route, p.sp, p.cost < kTooLarge};
 }
 
+// The appended blocks of a per-channel cache that the window [w0, w1) overlaps, listed for the matrix-core kernel, which walks
+// the window block by block.  0: it cannot (no cached keys, or more blocks than the list holds).
+int list_key_blocks(const std::deque<kvq_block> &blocks, int64_t w0, int64_t w1, kvq::KeyBlock (&list)[kvq::kMaxKeyBlocks])
+{
+    int n = 0;
+    for (const kvq_block &b : blocks) {
+        const int64_t s0 = b.start > w0 ? b.start : w0, s1 = b.start + b.count < w1 ? b.start + b.count : w1;
+        if (s0 >= s1) continue;
+        if (n == kvq::kMaxKeyBlocks) return 0;
+        list[n++] = kvq::KeyBlock{(int32_t)b.slot, (int32_t)(s0 - w0), (int32_t)(s1 - w0)};
+    }
+    return n;
+}
+// (the matrix-core loaders do their ring arithmetic and their offsets inside a head in 32 bits)
+bool beyond_matrix_loaders(const kvq::CacheView &cv, int64_t cache_len)
+{
+    return cache_len >= (int64_t(1) << 31) || cv.cap_tiles >= (int64_t(1) << 20);
+}
+
 // Tiles of a call's key range: cached tiles that the window touches and tiles of the current block.
 int64_t key_tiles(int64_t start, int64_t cache_len, int64_t n_cur)
 {
@@ -426,22 +445,10 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
     // the exact (sinh) correction is a diagnostic mode: vector kernel only
     force_vector = force_vector || correction == 2;
     if (d.key_axis == KVQ_KEYS_PER_CHANNEL && !force_vector) {
-        // The matrix-core kernel walks the window block by block: list the appended blocks it overlaps.  A window
-        // without cached keys or with more blocks than the list holds goes to the vector kernel.
-        const int64_t w0 = a.cache_start, w1 = a.cache_start + cache_len;
-        int nb = 0;
-        bool fits = cache_len > 0;
-        for (const kvq_block &b : cache->blocks) {
-            const int64_t s0 = b.start > w0 ? b.start : w0, s1 = b.start + b.count < w1 ? b.start + b.count : w1;
-            if (s0 >= s1) continue;
-            if (nb == kvq::kMaxKeyBlocks) { fits = false; break; }
-            a.key_blocks[nb++] = kvq::KeyBlock{(int32_t)b.slot, (int32_t)(s0 - w0), (int32_t)(s1 - w0)};
-        }
-        a.n_key_blocks = nb;
-        force_vector = !fits || nb == 0;
+        a.n_key_blocks = list_key_blocks(cache->blocks, a.cache_start, a.cache_start + cache_len, a.key_blocks);
+        force_vector = a.n_key_blocks == 0;
     }
-    // (the matrix-core loaders do their ring arithmetic and their offsets inside a head in 32 bits)
-    force_vector = force_vector || cache_len >= (int64_t(1) << 31) || cache->view.cap_tiles >= (int64_t(1) << 20);
+    force_vector = force_vector || beyond_matrix_loaders(cache->view, cache_len);
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (diag) return kvq::launch_diagnostics_simt(a, k_ref, v_ref, diag, s) == hipSuccess ? KVQ_OK : KVQ_ERR_HIP;
     const Route own = force_vector ? Route::vector : route_of(d, cache->view);
@@ -507,9 +514,11 @@ size_t kvq_attention_workspace_bytes(const kvq_cache *cache, int64_t cache_start
     if (!cache || m <= 0 || n_cur < 0 || cache_len < 0 || cache_start < 0 || q_heads_per_kv_head < 1 || q_heads_per_kv_head > 64) return 0;
     const kvq_cache_desc &d = cache->desc;
     const Route route = route_of(d, cache->view);
-    if (route == Route::vector || cache_start + cache_len > cache->len) return 0;
+    if (route == Route::vector || cache_len > cache->len - cache_start || beyond_matrix_loaders(cache->view, cache_len)) return 0;
     if (m > ((int64_t)1 << 31) - 256 || n_cur > ((int64_t)1 << 31) - 256) return 0;
-    const int64_t tiles = key_tiles(cache->base + cache_start, cache_len, n_cur);
+    const int64_t start = cache->base + cache_start, tiles = key_tiles(start, cache_len, n_cur);
+    kvq::KeyBlock list[kvq::kMaxKeyBlocks];
+    if (d.key_axis == KVQ_KEYS_PER_CHANNEL && list_key_blocks(cache->blocks, start, start + cache_len, list) == 0) return 0;
     return kvq::split_workspace_bytes(choose(route, d, m, q_heads_per_kv_head, tiles, true).sp, d.head_dim);
 }
 

@@ -171,3 +171,31 @@ def test_a_capture_by_torch_stays_split():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, eager) and torch.equal(mass, eager_mass)
+
+
+def test_calls_of_the_vector_kernel_get_no_workspace():
+    """More appended blocks than the per-channel kernel lists; the exact correction."""
+    heads, rows, block = 2, 300, 64
+    cache = B.Cache(B.make_desc(heads, 128, 2, 64 * block, B.KVQ_BF16, key_axis=B.KVQ_KEYS_PER_CHANNEL), DEV)
+    x = torch.randn((block, heads, 128), device=DEV).to(torch.bfloat16)
+    q = torch.randn((rows, heads, 128), device=DEV).to(torch.bfloat16)
+    for blocks in range(1, 42):
+        B.kvq_quantize_append(cache, x, x)
+        wanted = B.lib().kvq_attention_workspace_bytes(cache.handle, 0, len(cache), rows, 0, 1)
+        if blocks >= 30:
+            assert (wanted > 0) == (blocks <= 40)
+    assert B.lib().kvq_attention_workspace_bytes(cache.handle, block, len(cache) - block, rows, 0, 1) > 0
+    per_token = B.Cache(B.make_desc(heads, 128, 2, 2000, B.KVQ_BF16), DEV)
+    k = torch.randn((2000, heads, 128), device=DEV).to(torch.bfloat16)
+    B.kvq_quantize_append(per_token, k, k)
+    out = torch.empty_like(q)
+    for correction, grouped, split in [(1, False, True), (2, False, False), (1, True, True), (2, True, False)]:
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        held = torch.cuda.memory_allocated()
+        if grouped:
+            B.kvq_chunk_attention_ex(per_token, 0, 2000, q[:8], None, None, out[:8], correction=correction)
+        else:
+            B.kvq_chunk_attention(per_token, 0, 2000, q[:8], None, None, out[:8], correction=correction)
+        assert (torch.cuda.max_memory_allocated() > held) == split
+    torch.cuda.synchronize()

@@ -37,6 +37,12 @@ def test_work_space_is_asked_for_where_a_call_is_split(heads, rows, current, rat
 def test_calls_that_are_never_split_and_invalid_ones_need_none():
     per_channel = _cache(8, 64, 2, 1024, key_axis=B.KVQ_KEYS_PER_CHANNEL)     # vector kernel
     assert _bytes(per_channel, 1024, 5120) == 0
+    no_cached_keys = _cache(8, 128, 2, 1024, key_axis=B.KVQ_KEYS_PER_CHANNEL)           # vector kernel
+    assert _bytes(no_cached_keys, 1024, 5120) == 0
+    B.lib().kvq_cache_destroy(no_cached_keys)
+    long_ring = _cache(8, 128, 2, 1 << 25)                                              # vector kernel
+    assert _bytes(long_ring, 1024, 5120) == 0
+    B.lib().kvq_cache_destroy(long_ring)
     h = _cache(8, 128, 2, 1024)
     for bad in [dict(rows=0, current=64), dict(rows=64, current=-1), dict(rows=64, current=64, ratio=0),
                 dict(rows=64, current=64, ratio=65), dict(rows=64, current=64, cached=1), dict(rows=64, current=64, start=-1)]:
