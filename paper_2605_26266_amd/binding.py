@@ -254,11 +254,17 @@ def _workspace(cache: Cache, cache_start: int, cache_len: int, rows: int, n_cur:
     on = torch.cuda.current_stream() if stream is None else stream
     if on.device != dev:
         return None
+    if stream is not None:
+        with torch.cuda.stream(stream):
+            return _allocate(nbytes, dev)
+    return _allocate(nbytes, dev)       # (a stream context for the current stream takes 1.5 us of the host's time)
+
+
+def _allocate(nbytes: int, dev: torch.device) -> Optional[torch.Tensor]:
     try:
-        with torch.cuda.stream(stream):          # (None: the current stream stays)
-            if torch.cuda.is_current_stream_capturing() and not _allocator_takes_part_in_capture(dev):
-                return None
-            return torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        if torch.cuda.is_current_stream_capturing() and not _allocator_takes_part_in_capture(dev):
+            return None
+        return torch.empty(nbytes, dtype=torch.uint8, device=dev)
     except torch.OutOfMemoryError:
         return None
 
