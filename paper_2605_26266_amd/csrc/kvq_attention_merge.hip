@@ -12,14 +12,15 @@ template <int DIM, typename T> __global__ __launch_bounds__(kMergeThreads) void 
 
 }  // namespace
 
+template <int DIM, typename T> static hipError_t launch_merge(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
+{
+    return launch_kernel(attention_merge_kernel<DIM, T>, dim3(merge_workgroups<DIM>(sp)), dim3(kMergeThreads), 0, stream, a, sp);
+}
 hipError_t launch_attention_merge(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
-    const dim3 grid = merge_grid(a, sp);
     const bool bf16 = a.cv.io_dtype == KVQ_BF16;
-    if (a.cv.head_dim == 128 && bf16) return launch_kernel(attention_merge_kernel<128, uint16_t>, grid, dim3(kMergeThreads), 0, stream, a, sp);
-    if (a.cv.head_dim == 128) return launch_kernel(attention_merge_kernel<128, float>, grid, dim3(kMergeThreads), 0, stream, a, sp);
-    if (bf16) return launch_kernel(attention_merge_kernel<64, uint16_t>, grid, dim3(kMergeThreads), 0, stream, a, sp);
-    return launch_kernel(attention_merge_kernel<64, float>, grid, dim3(kMergeThreads), 0, stream, a, sp);
+    if (a.cv.head_dim == 128) return bf16 ? launch_merge<128, uint16_t>(a, sp, stream) : launch_merge<128, float>(a, sp, stream);
+    return bf16 ? launch_merge<64, uint16_t>(a, sp, stream) : launch_merge<64, float>(a, sp, stream);
 }
 
 }  // namespace kvq

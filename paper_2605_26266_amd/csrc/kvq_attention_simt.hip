@@ -288,12 +288,15 @@ __global__ __launch_bounds__(D) void attention_simt_kernel(AttentionArgs a)
 
 // Behind a 16-bit matrix-core launch with split units: puts the pieces together, or on a flagged cache, where that launch
 // has stood back, computes the call.  (One launch for both: with a gated vector launch of its own the step of 8 heads x
-// 1024 rows x (4096 + 1024) keys took 66.4 us, with this 64.0 us.)
-template <int BITS> __global__ __launch_bounds__(kMergeThreads) void attention_merge_or_vector_kernel(AttentionArgs a, SplitArgs sp)
+// 1024 rows x (4096 + 1024) keys took 66.4 us, with this 64.0 us.)  The grid has room for both jobs: the merge may need a few
+// workgroups where the call has many rows (a small remainder split behind whole rounds), so there are at least as many as the
+// chip holds at once, if there are rows for them, and the ones past the merge return.
+constexpr int kResidentWorkgroups = 2048;   // two waves each; the registers of attend_row allow four waves per SIMD
+template <int BITS> __global__ __launch_bounds__(kMergeThreads) void attention_merge_or_vector_kernel(AttentionArgs a, SplitArgs sp, unsigned merge)
 {
     static_assert(kMergeThreads == 128, "a thread per channel of head_dim 128");
     if (!cache_flagged(a.status)) {
-        merge_rows<128, uint16_t>(a, sp);
+        if (blockIdx.x < merge) merge_rows<128, uint16_t>(a, sp);
         return;
     }
     const int64_t rows = a.m * a.cv.num_heads * a.q_per_kv;
@@ -440,8 +443,11 @@ hipError_t launch_attention_simt(const AttentionArgs &a, hipStream_t stream)
 hipError_t launch_attention_merge_or_vector(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
 {
     if (a.cv.head_dim != 128 || a.cv.io_dtype != KVQ_BF16) return hipErrorInvalidValue;
-    if (a.cv.bits == 2) return launch_kernel(attention_merge_or_vector_kernel<2>, merge_grid(a, sp), dim3(kMergeThreads), 0, stream, a, sp);
-    return launch_kernel(attention_merge_or_vector_kernel<4>, merge_grid(a, sp), dim3(kMergeThreads), 0, stream, a, sp);
+    const int64_t rows = a.m * a.cv.num_heads * a.q_per_kv, at_once = rows < kResidentWorkgroups ? rows : kResidentWorkgroups;
+    const unsigned merge = merge_workgroups<128>(sp);
+    const dim3 grid(merge > (unsigned)at_once ? merge : (unsigned)at_once);
+    if (a.cv.bits == 2) return launch_kernel(attention_merge_or_vector_kernel<2>, grid, dim3(kMergeThreads), 0, stream, a, sp, merge);
+    return launch_kernel(attention_merge_or_vector_kernel<4>, grid, dim3(kMergeThreads), 0, stream, a, sp, merge);
 }
 
 hipError_t launch_diagnostics_simt(const AttentionArgs &a, const void *k_ref, const void *v_ref, float *diag,

@@ -12,10 +12,11 @@
 #pragma once
 
 constexpr int kMergeThreads = 128;   // two register quads of one 32-row block and channel block
-inline dim3 merge_grid(const AttentionArgs &a, const SplitArgs &sp)
+template <int DIM> inline unsigned merge_workgroups(const SplitArgs &sp)
 {
-    return dim3((unsigned)((int64_t)(sp.pieces / sp.splits) * sp.part_blocks * (a.cv.head_dim / 32) * 2));
+    return (unsigned)(sp.pieces / sp.splits * sp.part_blocks) * (DIM / 32) * 2;   // at most 1024 units of 8 blocks
 }
+// (by workgroups below merge_workgroups)
 template <int DIM, typename T> __device__ inline void merge_rows(const AttentionArgs &a, const SplitArgs &sp)
 {
     const int lane = threadIdx.x & 63, g = 2 * (int)(blockIdx.x & 1) + (int)(threadIdx.x >> 6);

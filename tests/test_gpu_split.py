@@ -110,6 +110,33 @@ def test_split_call_on_a_flagged_cache_is_served_by_the_vector_kernel(bits):
     assert torch.equal(out, ref) and torch.equal(mass, ref_mass)
 
 
+# Few rows in many pieces; whole rounds with a small remainder: the merge takes 32 and 256 workgroups.
+@pytest.mark.parametrize("heads,ratio,tokens,rows,axis", [(2, 2, 4000, 51, 1), (65, 1, 1000, 1024, 0)])
+def test_a_flagged_cache_is_served_as_fast_split_as_unsplit(heads, ratio, tokens, rows, axis):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    k = torch.randn((tokens, heads, 128), generator=gen, device=DEV) * 1e-5
+    k[..., 0] += 40.0
+    v, q = (torch.randn((n, h, 128), generator=gen, device=DEV).to(torch.bfloat16) for n, h in ((tokens, heads), (rows, heads * ratio)))
+    cache = B.Cache(B.make_desc(heads, 128, 2, tokens, B.KVQ_BF16, key_axis=axis), DEV)
+    B.kvq_quantize_append(cache, k.to(torch.bfloat16), v)
+    assert float(B.export_all(cache, 0, 0, 1)[2].abs().max()) > 65500.0
+    q *= 0.02
+    nbytes = B.lib().kvq_attention_workspace_bytes(cache.handle, 0, tokens, rows, 0, ratio)
+    assert nbytes > 0
+    ws, times, results = torch.empty(nbytes, dtype=torch.uint8, device=DEV), {}, {}
+    for workspace in (ws, None, ws, None):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        results[workspace is None] = _call(cache, 0, tokens, q, None, None, ratio, False, workspace)
+        end.record()
+        end.synchronize()
+        times[workspace is None] = begin.elapsed_time(end)       # of the second round
+    assert torch.equal(results[True][0], results[False][0]) and torch.equal(results[True][1], results[False][1])
+    # both run the same rows on the same kernel code; with the grid of the merge alone the split call took 4 and 10 times as long
+    assert times[False] < 1.7 * times[True], times
+
+
 def _c_graph(stream, body):
     """A graph recorded through the HIP runtime, without torch (the library's handle finds the runtime it is linked to)."""
     hip, handle = B.lib(), ctypes.c_void_p(int(stream.cuda_stream))
