@@ -28,23 +28,26 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-
 # Sources with MFMAs written as inline assembly: the wait states around them are placed in the source, and every
 # build checks the device assembly for them (mfma_hazard_check) before the object is accepted.
 HAZARD_CHECKED = {"kvq_attention_mfma.hip"}
-SOURCES = {
-    "kvq_api.hip": [],
+# object: (source, flags of its own)
+OBJECTS = {
+    "kvq_api": ("kvq_api.hip", []),
     # the quantizer's rounding decisions follow a fixed sequence of IEEE operations: no contraction
-    "kvq_quantize.hip": ["-ffp-contract=off"],
-    "kvq_attention_simt.hip": [],
-    "kvq_attention_mfma.hip": [],
-    "kvq_attention_mfma_group.hip": [],
-    "kvq_attention_merge.hip": [],
-    "kvq_attention_f32.hip": [],
+    "kvq_quantize": ("kvq_quantize.hip", ["-ffp-contract=off"]),
+    "kvq_attention_simt": ("kvq_attention_simt.hip", []),
+    "kvq_attention_mfma": ("kvq_attention_mfma.hip", ["-DKVQ_SPLIT=0"]),
+    "kvq_attention_mfma_split": ("kvq_attention_mfma.hip", ["-DKVQ_SPLIT=1"]),
+    "kvq_attention_mfma_group": ("kvq_attention_mfma_group.hip", ["-DKVQ_SPLIT=0"]),
+    "kvq_attention_mfma_group_split": ("kvq_attention_mfma_group.hip", ["-DKVQ_SPLIT=1"]),
+    "kvq_attention_merge": ("kvq_attention_merge.hip", []),
+    "kvq_attention_f32": ("kvq_attention_f32.hip", []),
 }
 
 
 def _compile(item):
-    src, extra = item
-    obj = os.path.join(OBJ, src.replace(".hip", ".o"))
+    name, (src, extra) = item
+    obj = os.path.join(OBJ, name + ".o")
     cmd = ["hipcc", *COMMON, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
-    temps = os.path.join(OBJ, "asm_" + src.replace(".hip", ""))
+    temps = os.path.join(OBJ, "asm_" + name)
     if src in HAZARD_CHECKED:            # keep the intermediate files of this compile, among them the device assembly
         shutil.rmtree(temps, ignore_errors=True)
         os.makedirs(temps)
@@ -81,8 +84,8 @@ def build_microbench(verbose: bool = False) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as pool:
-        objs = list(pool.map(_compile, SOURCES.items()))
+    with ThreadPoolExecutor(max_workers=6) as pool:
+        objs = list(pool.map(_compile, OBJECTS.items()))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -463,11 +463,13 @@ static kvq_status attention_common(const kvq_cache *cache, int64_t cache_start, 
     sp.part_o = static_cast<float *>(workspace);
     sp.part_ml = reinterpret_cast<float4 *>(sp.part_o + (size_t)sp.pieces * sp.part_blocks * 32 * d.head_dim);
     if (route == Route::f32) a.status = nullptr;   // any zero-point will do
-    hipError_t e = route == Route::per_token ? kvq::launch_attention_mfma(a, sp, s)
-                   : route == Route::group   ? kvq::launch_attention_mfma_group(a, sp, s)
-                                             : kvq::launch_attention_f32(a, sp, s);
+    const bool split = sp.pieces > 0;
+    auto launch = route == Route::f32         ? kvq::launch_attention_f32
+                  : route == Route::per_token ? (split ? kvq::launch_attention_mfma_split : kvq::launch_attention_mfma)
+                                              : (split ? kvq::launch_attention_mfma_group_split : kvq::launch_attention_mfma_group);
+    hipError_t e = launch(a, sp, s);
     if (e != hipSuccess) return KVQ_ERR_HIP;
-    if (sp.pieces > 0) {
+    if (split) {
         e = route == Route::f32 ? kvq::launch_attention_merge(a, sp, s) : kvq::launch_attention_merge_or_vector(a, sp, s);
     } else if (a.status) {
         // A cache that has ever stored a zero-point beyond the 16-bit kernels' domain carries a flag: the launch

@@ -50,6 +50,12 @@
 //
 // Current keys/values (unquantized block, kvq_mfma_current_phase.inc).  K rows are staged through LDS one tile
 // ahead, V tiles are transposed through LDS (token-major operands); scores get no correction.
+// Compiled twice, for launches with split units (KVQ_SPLIT 1) and without: the code that finds a piece and writes its partial
+// result costs a launch without pieces 0.5 .. 1.2 us, and the 4-bit kernel with groups of 32, which has no register to spare,
+// 3 % of its loop as well (40 heads x 600 rows x 2000 keys: 119 us with it, 115 us without).
+#ifndef KVQ_SPLIT
+#error "KVQ_SPLIT: 0 or 1"
+#endif
 #include "kvq_internal.h"
 
 // 1: the rotated query enters the score MFMAs as an f16 high part plus an f16 low part (two MFMAs per
@@ -97,6 +103,8 @@ namespace {
 #define KVQ_INT4_KEY_SHARE 1   // 4-bit key pairs share their shifts two by two (kvq_mfma_common.h)
 #include "kvq_mfma_common.h"
 
+constexpr bool kSplit = KVQ_SPLIT != 0;
+
 constexpr int kBuffers = 4;    // power of two: buffer index = stage & 3
 
 // Word offsets inside one stage buffer.
@@ -141,7 +149,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
 
-    const Place place = locate(a, sp);
+    const Place place = locate<kSplit>(a, sp);
     const int head = place.head, qhead = place.qhead, rblk = place.rblk;   // key/value head, query head, 256-row block
     const int64_t wave_row0 = (int64_t)rblk * kRowsPerBlock + wave * kRowsPerWave;
     const int64_t head_off = (int64_t)head * a.stride_head;          // k_cur / v_cur
@@ -1512,7 +1520,11 @@ template <int BITS, bool CORR, bool FP8META, bool PERCH = false> hipError_t laun
 
 }  // namespace
 
+#if KVQ_SPLIT
+hipError_t launch_attention_mfma_split(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
+#else
 hipError_t launch_attention_mfma(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
+#endif
 {
     if (a.cv.head_dim != D || a.cv.io_dtype != KVQ_BF16) return hipErrorInvalidValue;
     if (a.cv.meta_format != KVQ_META_FP32 && a.cv.group_size != D) return hipErrorInvalidValue;

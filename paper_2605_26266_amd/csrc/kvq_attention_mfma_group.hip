@@ -18,6 +18,12 @@
 //     maximum shifted by 2^7 to keep small weights out of the denormals), and the zero-point term of
 //     each group is one more row of a small A operand, so tau_j comes out of two MFMAs per tile
 //     instead of vector dot products.
+// Compiled twice, for launches with split units (KVQ_SPLIT 1) and without: the code that finds a piece and writes its partial
+// result costs a launch without pieces 0.5 .. 1.2 us, and the 4-bit kernel with groups of 32, which has no register to spare,
+// 3 % of its loop as well (40 heads x 600 rows x 2000 keys: 119 us with it, 115 us without).
+#ifndef KVQ_SPLIT
+#error "KVQ_SPLIT: 0 or 1"
+#endif
 #include "kvq_internal.h"
 
 #include <type_traits>
@@ -26,6 +32,8 @@ namespace kvq {
 namespace {
 
 #include "kvq_mfma_common.h"
+
+constexpr bool kSplit = KVQ_SPLIT != 0;
 
 #ifndef KVQ_FREE_LAST_ROWOP
 #define KVQ_FREE_LAST_ROWOP 1
@@ -149,7 +157,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_group_kernel(Atten
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
 
-    const Place place = locate(a, sp);
+    const Place place = locate<kSplit>(a, sp);
     const int head = place.head, qhead = place.qhead, rblk = place.rblk;   // key/value head, query head, 256-row block
     const int64_t wave_row0 = (int64_t)rblk * kRowsPerBlock + wave * kRowsPerWave;
     const int64_t head_off = (int64_t)head * a.stride_head;          // k_cur / v_cur
@@ -883,13 +891,19 @@ template <int BITS, bool CORR, int G> hipError_t launch_group(const AttentionArg
 
 }  // namespace
 
+#if !KVQ_SPLIT
 bool attention_mfma_group_supported(const CacheView &cv)
 {
     return cv.head_dim == D && cv.io_dtype == KVQ_BF16 && cv.meta_format == KVQ_META_FP8_BF16 &&
            (cv.bits == 2 || cv.bits == 4) && (cv.group_size == 32 || cv.group_size == 64);
 }
+#endif
 
+#if KVQ_SPLIT
+hipError_t launch_attention_mfma_group_split(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
+#else
 hipError_t launch_attention_mfma_group(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream)
+#endif
 {
     if (!attention_mfma_group_supported(a.cv)) return hipErrorInvalidValue;
     if (a.cache_len > (int64_t)0x3fffffff * kTileTokens) return hipErrorInvalidValue;

@@ -233,7 +233,9 @@ inline size_t split_workspace_bytes(const SplitArgs &sp, int head_dim)
 }
 __device__ inline bool cache_flagged(const uint32_t *status) { return status != nullptr && *status != 0u; }
 hipError_t launch_attention_simt(const AttentionArgs &a, hipStream_t stream);
+// 16-bit matrix-core kernels: without split units (sp.pieces == 0) and with them.
 hipError_t launch_attention_mfma(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
+hipError_t launch_attention_mfma_split(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
 // Combine the pieces of the split units of the launch in front (sp.pieces > 0): of an fp32 launch; of a 16-bit launch, or
 // in its place on a flagged cache.
 hipError_t launch_attention_merge(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
@@ -248,5 +250,6 @@ hipError_t launch_attention_f32(const AttentionArgs &a, const SplitArgs &sp, hip
 // Matrix-core kernel for caches with several FP8/BF16 (scale, zero-point) groups per token.
 bool attention_mfma_group_supported(const CacheView &cv);
 hipError_t launch_attention_mfma_group(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
+hipError_t launch_attention_mfma_group_split(const AttentionArgs &a, const SplitArgs &sp, hipStream_t stream);
 
 }  // namespace kvq

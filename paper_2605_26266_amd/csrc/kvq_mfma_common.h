@@ -240,12 +240,13 @@ __device__ inline int xcd_contiguous(int b, int total)
     const int x = b & 7, rest = total & 7;
     return x * (total >> 3) + (x < rest ? x : rest) + (b >> 3);
 }
-__device__ inline Place locate(const AttentionArgs &a, const SplitArgs &sp)
+// SPLIT: the launch has pieces (sp.pieces > 0).
+template <bool SPLIT> __device__ inline Place locate(const AttentionArgs &a, const SplitArgs &sp)
 {
     Place w;
     const int bid = blockIdx.x;
     int unit, split = 0;
-    if (bid < sp.whole) {
+    if (!SPLIT || bid < sp.whole) {
         unit = xcd_contiguous(bid, sp.whole);
         w.piece = -1;
     } else {
@@ -269,7 +270,7 @@ __device__ inline Place locate(const AttentionArgs &a, const SplitArgs &sp)
     w.phys_first = (int)a.phys_tile_first;
     w.cur0 = 0;
     w.cur1 = (int)((n_keys + kTileTokens - 1) / kTileTokens);
-    if (w.piece >= 0) {
+    if (SPLIT && w.piece >= 0) {
         const int64_t t_first = w.cs / kTileTokens;
         const int tc = a.cache_len > 0 ? (int)((w.ce - 1) / kTileTokens - t_first) + 1 : 0, all = tc + w.cur1;
         const int x0 = (int)((int64_t)all * split / sp.splits), x1 = (int)((int64_t)all * (split + 1) / sp.splits);
