@@ -29,7 +29,7 @@
  *     cache (length, window, blocks) change at call time, not at replay.
  *   - Errors are returned as kvq_status; nothing aborts or throws.  On any error the
  *     cache object is unchanged; nothing has been enqueued, except that an append to a
- *     KVQ_KEYS_PER_CHANNEL cache, which is four launches, may have enqueued the first ones
+ *     KVQ_KEYS_PER_CHANNEL cache, which is three launches, may have enqueued the first ones
  *     when the runtime refuses a later one (they write work space and slots that no
  *     live token refers to).
  *   - Tensors are [token][head][channel] with element strides `stride_token`,
@@ -86,8 +86,7 @@ typedef struct {
     int32_t bits;            /* 2 or 4 */
     int32_t group_size;      /* channels of a token sharing one (scale, zero-point): 32, 64 or head_dim */
     int32_t rotate;          /* must be 1: normalised Sylvester-Hadamard rotation before quantization */
-    int32_t io_dtype;        /* kvq_dtype of q/k/v/out.  KVQ_BF16 with head_dim 128 runs on the matrix cores (every
-                                format); fp32 I/O, head_dim 64 and the exact correction run an fp32 vector kernel */
+    int32_t io_dtype;        /* kvq_dtype of q/k/v/out.  Which kernel runs: see kvq_chunk_attention */
     int32_t meta_format;     /* kvq_meta_format */
     int32_t key_axis;        /* kvq_key_axis */
     int64_t capacity_tokens; /* >= 1; storage is sized for this many tokens per head */
@@ -192,13 +191,15 @@ kvq_status kvq_quantize_append_static(kvq_cache *cache, const void *k, const voi
  * mode that always runs the fp32 vector kernel).
  * cache_len == 0 (first chunk) and n_cur == 0 are allowed, not both; m == 0 is a no-op.
  * `out` must not alias the inputs.
- * Which kernel runs: 16-bit matrix cores for BF16 caches with head_dim 128 (every format), fp32 matrix cores for the
- * other caches with per-token keys (all arithmetic in fp32), the fp32 vector kernel for per-channel keys outside
- * BF16 / head_dim 128 and for the exact correction.  The 16-bit matrix-core kernels carry a zero-point as two 16-bit pieces, exact
- * below 2^16.  A cache that has stored a larger one since it was created or last reset (vectors whose offset is
- * tens of thousands of times their range) is marked by the append; for such a cache the matrix-core launch
- * returns without writing and a vector-kernel launch enqueued behind it does the work, with the same results as
- * kvq_chunk_attention_fp32.  The mark is only cleared by kvq_cache_reset followed by an append.
+ * Which kernel runs: 16-bit matrix cores for BF16 caches with head_dim 128 (every format), fp32 matrix cores (all
+ * arithmetic in fp32) for the other caches with per-token keys and for those calls of the former whose estimated time is
+ * clearly shorter there (few query rows, or few keys), the fp32 vector kernel for per-channel keys outside BF16 / head_dim
+ * 128, for the exact correction and for calls beyond what the matrix kernels index.  The 16-bit kernels carry a zero-point as
+ * two 16-bit pieces, exact below 2^16.  A cache that has stored a larger one since it was created or last reset (vectors
+ * whose offset is tens of thousands of times their range) is marked by the append; for such a cache the launch of a 16-bit
+ * kernel returns without writing and the launch enqueued behind it computes the call with the vector kernel's arithmetic
+ * (the results of kvq_chunk_attention_fp32).  Calls on the fp32 matrix cores take any zero-point: the same expressions,
+ * summed in another order.  The mark is only cleared by kvq_cache_reset followed by an append.
  */
 kvq_status kvq_chunk_attention(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,
                                const void *q, const void *k_cur, const void *v_cur,

@@ -85,10 +85,12 @@ bool tensor_ok(const void *p, int64_t stride_token, int64_t stride_head, int hea
 // How a matrix-core call is laid over the 256 compute units (one workgroup each).  The units (row blocks) that fill whole
 // rounds of the chip stay whole; the key ranges of the rest are cut into the number of pieces with the shortest estimated
 // time: rounds * (tiles per piece + what a workgroup pays once: query preparation, rotation back, writing its result) + the
-// merge.  The constants (microseconds) follow measurements of the 16-bit kernels: 8 heads x 1024 rows x (4096 + 1024)
-// keys, 32 units: 208 / 133 / 96 / 77.5 / 112 / 180 us with 1 / 2 / 4 / 8 / 12 / 32 pieces; 32 query heads x 1 row x (8192
-// + 64) keys: 366 / 112 / 70 / 90 / 130 us with 1 / 4 / 8 / 16 / 32; 24 heads x 4680 rows x (28080 + 4680) keys, 200
-// units after a full round: 2182 / 2286 / 2146 / 2219 / 2331 us with 1 / 2 / 5 / 6 / 9.
+// merge.  The constants (microseconds) follow measurements, estimates in brackets.  8 heads x 1024 rows x (4096 + 1024) keys,
+// 32 units of the per-token kernel: 175 (182) / 111 (110) / 82 (71) / 61 (54) / 84 (87) / 134 (138) us with 1 / 2 / 4 / 8 /
+// 12 / 32 pieces.  32 query heads x 1 row x (8192 + 64) keys, group-wise kernel: 361 (374) / 114 (121) / 70 (78) / 87 (107) /
+// 122 (165) us with 1 / 4 / 8 / 16 / 32; fp32 kernel, 8 units: 325 (344) / 101 (111) / 61 (71) / 39 (42) / 35 (43) / 36 (44) /
+// 53 (63) us with 1 / 4 / 8 / 17 / 24 / 32 / 64.  24 heads x 4680 rows x (28080 + 4680) keys, 200 units after a full round: 2043
+// (2094) / 2133 (2131) / 2044 (1982) / 2089 (2043) / 2110 (2178) us with 1 / 2 / 5 / 6 / 9.
 struct KernelCost {
     int rows;          // query rows of a unit
     int threads;       // of its workgroup
@@ -133,8 +135,8 @@ Plan plan_split(const KernelCost &k, int64_t m, int64_t heads, int64_t ratio, in
         }
     }
     // A split has to promise something: the estimate leaves out that a chip with idle compute units clocks higher, and
-    // that pieces of one unit compete for the same memory (31 heads x 1763 rows x 44075 keys, 217 units: 1451 us whole, 1549
-    // us in 7 pieces, estimated 1408 and 1399).
+    // that pieces of one unit compete for the same memory (31 heads x 1763 rows x 44075 keys, 217 units: 1319 us whole, 1393
+    // us in 7 pieces, estimated 1401 and 1351).
     if (best > 1 && best_cost > 0.85 * piece_cost(1)) {
         best = 1;
         best_cost = piece_cost(1);
@@ -161,11 +163,13 @@ const KernelCost &cost_of(Route r, int head_dim)
     return r == Route::group ? kCostGroup : kCostPerToken;
 }
 
-// Kernel and grid of a call.  A call with a few rows per key/value head (the last tokens of a prompt, a decoded token)
-// fills a sliver of a 256-row block: where the fp32 kernel, with its 32-row units over all query heads of a key/value head,
-// is estimated to be clearly faster it takes such calls of the 16-bit kernels' caches too (8 key/value heads with 4 query
-// heads each, 1 row, 8192 + 64 keys, groups of 32: 70 us in the
-// group-wise kernel, 43 us here).
+// Kernel and grid of a call.  A call that fills a sliver of the 256-row blocks (the last tokens of a prompt, a decoded token),
+// or that has a few tiles of keys behind the 16-bit kernels' longer preparation, takes the fp32 kernel with its 32-row units
+// over all query heads of a key/value head, where that is estimated to be clearly faster (8 key/value heads with 4 query heads
+// each, 1 row, 8192 + 64 keys, groups of 32: 70 us in the group-wise kernel, 39 us here).  Where the line lies: of 220 random
+// calls of these caches with estimates near each other, timed on both kernels, the fp32 one took 0.85 of the other's time on
+// average where the estimate promised less than 0.8 (none of 37 was slower by more than 1 %), 0.92 between 0.8 and 0.95 (9 of
+// 106 slower), and as long beyond.
 struct Choice {
     Route route;
     kvq::SplitArgs sp;
