@@ -237,7 +237,8 @@ kvq_status kvq_chunk_attention_ex(const kvq_cache *cache, int64_t cache_start, i
  * kvq_chunk_attention_ex with a work space.  Calls whose row blocks do not fill the GPU (few heads, few query rows, a
  * partly filled last round) split the key range of a row block over several workgroups; their partial results need device
  * memory, which the library does not allocate.  workspace: device memory, 256-byte aligned, used by this call only until
- * its work on the stream is done (calls that overlap need a work space each); NULL with 0 bytes, or fewer bytes than
+ * its work on the stream is done (calls that overlap need a work space each; a call recorded into a graph uses it at every
+ * replay); NULL with 0 bytes, or fewer bytes than
  * kvq_attention_workspace_bytes returns for the call: nothing is split.  Results agree within the tolerance of the path
  * either way.  kvq_attention_workspace_bytes returns 0 where a call is not split (it is not told the correction: calls with
  * the exact one, 2, never are), and at most 2048 * 256 * (head_dim + 4) * 4 bytes: 277 MB for head_dim 128.
