@@ -88,17 +88,18 @@ bool tensor_ok(const void *p, int64_t stride_token, int64_t stride_head, int hea
 // merge.  The constants (microseconds) follow measurements, estimates in brackets.  8 heads x 1024 rows x (4096 + 1024) keys,
 // 32 units of the per-token kernel: 175 (182) / 111 (110) / 82 (71) / 61 (54) / 84 (87) / 134 (138) us with 1 / 2 / 4 / 8 /
 // 12 / 32 pieces.  32 query heads x 1 row x (8192 + 64) keys, group-wise kernel: 361 (374) / 114 (121) / 70 (78) / 87 (107) /
-// 122 (165) us with 1 / 4 / 8 / 16 / 32; fp32 kernel, 8 units: 325 (344) / 101 (111) / 61 (71) / 39 (42) / 35 (43) / 36 (44) /
-// 53 (63) us with 1 / 4 / 8 / 17 / 24 / 32 / 64.  24 heads x 4680 rows x (28080 + 4680) keys, 200 units after a full round: 2043
+// 122 (165) us with 1 / 4 / 8 / 16 / 32; fp32 kernel, 8 units: 108 (108) / 39 (40) / 26 (29) / 21 (22) / 20 (23) / 21 (24) /
+// 32 (42) us with 1 / 4 / 8 / 17 / 24 / 32 / 64; head_dim 64, 2 heads x 300 rows x (4000 + 300) keys, 20 units: 38 (44) / 26 (30) /
+// 20 (23) / 16 (20) / 17 (18) / 30 (47) us with 1 / 2 / 4 / 8 / 12 / 32 (0.19 us a tile; fp32 tensors and groups take 0.3).  24 heads x 4680 rows x (28080 + 4680) keys, 200 units after a full round: 2043
 // (2094) / 2133 (2131) / 2044 (1982) / 2089 (2043) / 2110 (2178) us with 1 / 2 / 5 / 6 / 9.
 struct KernelCost {
     int rows;          // query rows of a unit
     int threads;       // of its workgroup
     int tiles_step;    // tiles that a workgroup works on side by side
-    double tile, fixed;
+    double tile, fixed, merge;
 };
-constexpr KernelCost kCostPerToken{256, 256, 1, 1.0, 22.0}, kCostGroup{256, 256, 1, 1.35, 26.0};
-constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 512, 8, 0.64, 8.0}, kCostF32Dim128{kvq::kF32Rows, 512, 8, 1.25, 14.0};
+constexpr KernelCost kCostPerToken{256, 256, 1, 1.0, 22.0, 6.0}, kCostGroup{256, 256, 1, 1.35, 26.0, 6.0};
+constexpr KernelCost kCostF32Dim64{kvq::kF32Rows, 512, 8, 0.24, 11.0, 1.5}, kCostF32Dim128{kvq::kF32Rows, 512, 8, 0.36, 12.5, 1.5};
 
 struct Plan {
     kvq::SplitArgs sp;
@@ -109,7 +110,7 @@ constexpr double kTooLarge = 1e300;   // more units than a grid holds
 Plan plan_split(const KernelCost &k, int64_t m, int64_t heads, int64_t ratio, int64_t tiles, bool may_split)
 {
     constexpr int kComputeUnits = 256, kMaxSplits = 64;
-    constexpr double kMerge = 6.0, kMergePerSplit = 0.12, kMergePerBlock = 0.0025;
+    constexpr double kMergePerSplit = 0.12, kMergePerBlock = 0.0025;
     kvq::SplitArgs sp = {};
     sp.rows = k.rows;
     sp.pack = (int32_t)(k.rows == kvq::kF32Rows && m * ratio <= 0x7fffffff ? ratio : 1);
@@ -127,7 +128,7 @@ Plan plan_split(const KernelCost &k, int64_t m, int64_t heads, int64_t ratio, in
     double best_cost = rest > 0 ? piece_cost(1) : 0.0;
     for (int64_t s = 2; may_split && rest > 0 && s <= kMaxSplits && s <= tiles && rest * s <= kvq::kMaxPieces; ++s) {
         const int64_t rounds = (rest * s + kComputeUnits - 1) / kComputeUnits;
-        const double cost = (double)rounds * piece_cost(s) + kMerge + kMergePerSplit * (double)s +
+        const double cost = (double)rounds * piece_cost(s) + k.merge + kMergePerSplit * (double)s +
                             kMergePerBlock * (double)(rest * s * sp.part_blocks);
         if (cost < best_cost && launchable(units - rest + rest * s)) {
             best_cost = cost;

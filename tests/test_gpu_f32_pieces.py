@@ -1,0 +1,95 @@
+"""The fp32 matrix-core attention kernel where its bf16 pieces do not carry the operands (zero-points beyond them, queries, keys
+and values near the ends of the fp32 range or not finite) and where the runs of its eight waves are short or change from cached
+to current tiles, against the vector kernel, which computes the same expressions in fp32."""
+import math
+
+import pytest
+import torch
+
+from paper_2605_26266_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# (dim, bits, io, meta, group)
+FORMATS = [(64, 2, B.KVQ_FP32, B.KVQ_META_FP32, 64), (64, 4, B.KVQ_FP32, B.KVQ_META_FP8_BF16, 32), (64, 4, B.KVQ_BF16, B.KVQ_META_FP32, 64),
+           (128, 4, B.KVQ_FP32, B.KVQ_META_FP32, 128), (128, 2, B.KVQ_FP32, B.KVQ_META_FP8_BF16, 32), (64, 2, B.KVQ_BF16, B.KVQ_META_FP8_BF16, 64)]
+
+
+def _attend(fmt, rows, current, cached, q_scale=1.0, k_scale=1.0, v_scale=1.0, offset=None, poison=None):
+    dim, bits, io, meta, group = fmt
+    heads = 2
+    dtype = torch.bfloat16 if io == B.KVQ_BF16 else torch.float32
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(4)
+
+    def t(tokens, scale):
+        return torch.randn((tokens, heads, dim), generator=gen, device=DEV) * scale
+
+    cache = B.Cache(B.make_desc(heads, dim, bits, max(cached, 32), io, group, 1, meta), DEV)
+    if cached:
+        k, v = t(cached, k_scale), t(cached, v_scale)
+        if offset:                    # every third token: all rotated channels far from 0, next to a small range
+            for x in (k, v):
+                x[::3] *= 1e-2 / offset
+                x[::3, :, 0] += 2.0
+        B.kvq_quantize_append(cache, k.to(dtype), v.to(dtype))
+    q = t(rows, q_scale).to(dtype)
+    k, v = (t(current, k_scale).to(dtype), t(current, v_scale).to(dtype)) if current else (None, None)
+    if poison:
+        poison(q, k, v)
+    got, mass = torch.full_like(q, float("nan")), torch.full((heads, rows), float("nan"), device=DEV)
+    ref, ref_mass = torch.empty_like(got), torch.empty_like(mass)
+    B.kvq_chunk_attention(cache, 0, cached, q, k, v, got, mass)
+    B.kvq_chunk_attention_fp32(cache, 0, cached, q, k, v, ref, ref_mass)
+    torch.cuda.synchronize()
+    return cache, got, mass, ref, ref_mass
+
+
+def _close(got, mass, ref, ref_mass, score_error=1e-5):
+    """score_error: absolute error of a score, which weights, outputs and masses follow relatively; BF16 outputs may round the
+    other way besides (2^-9 of the result)."""
+    tol = score_error + (2.0 ** -9 if got.dtype == torch.bfloat16 else 0.0)
+    assert torch.isfinite(ref).all() and torch.isfinite(got).all()
+    assert float((got.double() - ref.double()).norm()) <= tol * float(ref.double().norm())
+    torch.testing.assert_close(mass, ref_mass, rtol=10 * score_error, atol=1e-9)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("cached,current", [(32, 0), (0, 33), (7 * 32, 1), (8 * 32, 0), (5 * 32 + 3, 4 * 32), (9 * 32, 31), (40, 300), (20 * 32 + 1, 7 * 32 + 1)])
+def test_runs_of_waves(fmt, cached, current):
+    """Fewer tiles than waves, as many, one more; waves that go from cached to current tiles, and none that do."""
+    _close(*_attend(fmt, 37, current, cached)[1:])
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_zero_points_beyond_the_pieces(fmt):
+    cache, *results = _attend(fmt, 40, 20, 300, offset=40.0)
+    zero = B.export_all(cache, 0)[2].abs()
+    assert (240.0 if fmt[3] == B.KVQ_META_FP32 else 15.0) < float(zero.max()) < 8192.0 and float(zero.min()) < 15.0
+    # such a token's score and output are sums of terms zero / (2^bits - 1) times larger than their result: |zero| < 2^13,
+    # 2^13 * 2^-24 relative to scores of a few units
+    _close(*results, score_error=1e-3)
+
+
+@pytest.mark.parametrize("fmt", [f for f in FORMATS if f[3] == B.KVQ_META_FP32])
+@pytest.mark.parametrize("scales", [dict(q_scale=1e-32, k_scale=1e32), dict(q_scale=2.0 ** 105, k_scale=2.0 ** -105), dict(v_scale=1e-32),
+                                    dict(v_scale=1e32)])
+def test_ends_of_the_range(fmt, scales):
+    # ordinary scores and weights throughout
+    _close(*_attend(fmt, 40, 70, 200, **scales)[1:], score_error=2e-5)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
+@pytest.mark.parametrize("where", ["q", "k", "v"])
+def test_not_finite(fmt, value, where):
+    def poison(q, k, v):
+        {"q": q, "k": k, "v": v}[where][5, 0, 7] = value
+
+    _, got, mass, ref, ref_mass = _attend(fmt, 40, 70, 200, poison=poison)
+    for a, b in ((got, ref), (mass, ref_mass)):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isposinf(a), torch.isposinf(b))
+        ok = torch.isfinite(b)
+        assert torch.equal(torch.isneginf(a), torch.isneginf(b)) and ok.any()
+        torch.testing.assert_close(a[ok], b[ok], rtol=2.0 ** -7 if a.dtype == torch.bfloat16 else 1e-4, atol=1e-2 if a.dtype == torch.bfloat16 else 1e-5)
