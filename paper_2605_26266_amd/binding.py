@@ -102,8 +102,10 @@ def _check(status: int, where: str) -> None:
 
 
 def _stream(stream: Optional[torch.cuda.Stream]) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # (what torch.cuda.current_stream().cuda_stream says, without the two objects that it makes on the way)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -184,44 +186,53 @@ def kvq_cache_set_rotation_signs(cache: Cache, negate) -> None:
     _check(lib().kvq_cache_set_rotation_signs(cache.handle, buf), "kvq_cache_set_rotation_signs")
 
 
+_UNIT_STRIDE = "expected a [token][head][channel] tensor with unit channel stride"
+
+
 def _tok_head_strides(t: torch.Tensor):
-    if t.dim() != 3 or t.stride(2) != 1:
-        raise ValueError("expected a [token][head][channel] tensor with unit channel stride")
-    return t.stride(0), t.stride(1)
+    s = t.stride()
+    if len(s) != 3 or s[2] != 1:
+        raise ValueError(_UNIT_STRIDE)
+    return s[0], s[1]
 
 
-def _check_shape(t: Optional[torch.Tensor], heads: int, head_dim: int, what: str, tokens: Optional[int] = None) -> None:
+# A call over a few rows is as long as its marshalling: shapes and strides are asked for once per tensor (a question to a tensor
+# takes 0.2 us, and there were forty in an attention call).
+def _check_shape(t: Optional[torch.Tensor], heads: int, head_dim: int, what: str, tokens: Optional[int] = None) -> int:
     """The kernels index [token][head][channel] by the cache's head count and head_dim: a tensor with fewer heads
-    or channels would be read or written out of bounds on the device, so the shape is checked here."""
+    or channels would be read or written out of bounds on the device, so the shape is checked here.  Returns the tokens."""
     if t is None:
-        return
-    if t.dim() != 3 or t.shape[1] != heads or t.shape[2] != head_dim or (tokens is not None and t.shape[0] != tokens):
+        return 0
+    shape = t.shape
+    if len(shape) != 3 or shape[1] != heads or shape[2] != head_dim or (tokens is not None and shape[0] != tokens):
         raise ValueError("%s must be [%s][%d][%d], got %s" % (what, "tokens" if tokens is None else tokens, heads,
-                                                              head_dim, tuple(t.shape)))
+                                                              head_dim, tuple(shape)))
+    return shape[0]
+
+
+def _check_append(cache: Cache, k: torch.Tensor, v: torch.Tensor):
+    """Tokens and strides of an append's tensors."""
+    if k.dtype != cache.torch_dtype or v.dtype != cache.torch_dtype or k.shape != v.shape:
+        raise ValueError("k and v must share the cache's io dtype and one shape")
+    tokens = _check_shape(k, cache.desc.num_heads, cache.desc.head_dim, "k and v")
+    strides = _tok_head_strides(k)
+    if _tok_head_strides(v) != strides:
+        raise ValueError("k and v must share strides")
+    return tokens, strides
 
 
 def kvq_quantize_append(cache: Cache, k: torch.Tensor, v: torch.Tensor,
                         stream: Optional[torch.cuda.Stream] = None) -> None:
-    if k.dtype != cache.torch_dtype or v.dtype != cache.torch_dtype or k.shape != v.shape:
-        raise ValueError("k and v must share the cache's io dtype and one shape")
-    _check_shape(k, cache.desc.num_heads, cache.desc.head_dim, "k and v")
-    st, sh = _tok_head_strides(k)
-    if _tok_head_strides(v) != (st, sh):
-        raise ValueError("k and v must share strides")
-    _check(lib().kvq_quantize_append(cache.handle, k.data_ptr(), v.data_ptr(), k.shape[0], st, sh, _stream(stream)),
+    tokens, (st, sh) = _check_append(cache, k, v)
+    _check(lib().kvq_quantize_append(cache.handle, k.data_ptr(), v.data_ptr(), tokens, st, sh, _stream(stream)),
            "kvq_quantize_append")
 
 
 def kvq_quantize_append_static(cache: Cache, k: torch.Tensor, v: torch.Tensor,
                                stream: Optional[torch.cuda.Stream] = None) -> None:
     """kvq_quantize_append with the per-channel work space in the library's static device array."""
-    if k.dtype != cache.torch_dtype or v.dtype != cache.torch_dtype or k.shape != v.shape:
-        raise ValueError("k and v must share the cache's io dtype and one shape")
-    _check_shape(k, cache.desc.num_heads, cache.desc.head_dim, "k and v")
-    st, sh = _tok_head_strides(k)
-    if _tok_head_strides(v) != (st, sh):
-        raise ValueError("k and v must share strides")
-    _check(lib().kvq_quantize_append_static(cache.handle, k.data_ptr(), v.data_ptr(), k.shape[0], st, sh,
+    tokens, (st, sh) = _check_append(cache, k, v)
+    _check(lib().kvq_quantize_append_static(cache.handle, k.data_ptr(), v.data_ptr(), tokens, st, sh,
                                             _stream(stream)), "kvq_quantize_append_static")
 
 
@@ -250,59 +261,54 @@ def _workspace(cache: Cache, cache_start: int, cache_len: int, rows: int, n_cur:
     nbytes = lib().kvq_attention_workspace_bytes(cache.handle, cache_start, cache_len, rows, n_cur, ratio)
     if nbytes == 0:
         return None
-    dev = cache.storage.device
-    on = torch.cuda.current_stream() if stream is None else stream
-    if on.device != dev:
-        return None
     if stream is not None:
-        with torch.cuda.stream(stream):
-            return _allocate(nbytes, dev)
-    return _allocate(nbytes, dev)       # (a stream context for the current stream takes 1.5 us of the host's time)
-
-
-def _allocate(nbytes: int, dev: torch.device) -> Optional[torch.Tensor]:
-    try:
-        if torch.cuda.is_current_stream_capturing() and not _allocator_takes_part_in_capture(dev):
+        if stream.device != cache.storage.device:
             return None
-        return torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        with torch.cuda.stream(stream):
+            return _allocate(nbytes, cache.storage)
+    if torch._C._cuda_getDevice() != cache.storage.get_device():      # the current stream belongs to the current device
+        return None
+    return _allocate(nbytes, cache.storage)       # (a stream context for the current stream takes 1.5 us of the host's time)
+
+
+def _allocate(nbytes: int, like: torch.Tensor) -> Optional[torch.Tensor]:
+    try:
+        if torch._C._cuda_isCurrentStreamCapturing() and not _allocator_takes_part_in_capture(like.device):
+            return None
+        return like.new_empty(nbytes)
     except torch.OutOfMemoryError:
         return None
 
 
-def _launch_split(cache: Cache, ws: torch.Tensor, cache_start: int, cache_len: int, q, k_cur, v_cur, n_cur, st, sh,
-                  softmax_scale, correction, opts, out, mass_cached, stream, where: str) -> None:
-    _check(lib().kvq_chunk_attention_ws(
-        cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur), _ptr(v_cur), q.shape[0], n_cur, st, sh,
-        float(softmax_scale), int(correction), opts, out.data_ptr(), _ptr(mass_cached), ws.data_ptr(), ws.numel(),
-        _stream(stream)), where)
-
-
 def _attention(fn, cache: Cache, cache_start: int, cache_len: int, q, k_cur, v_cur, softmax_scale, correction,
                out, mass_cached, stream, may_split=False):
-    st, sh = _tok_head_strides(q)
-    n_cur = 0 if k_cur is None else k_cur.shape[0]
-    H, d = cache.desc.num_heads, cache.desc.head_dim
-    _check_shape(q, H, d, "q")
-    _check_shape(out, H, d, "out", q.shape[0])
-    _check_shape(k_cur, H, d, "k_cur")
+    st, sh = strides = _tok_head_strides(q)
+    H, d, dtype = cache.desc.num_heads, cache.desc.head_dim, cache.torch_dtype
+    rows = _check_shape(q, H, d, "q")
+    _check_shape(out, H, d, "out", rows)
+    n_cur = _check_shape(k_cur, H, d, "k_cur")
     _check_shape(v_cur, H, d, "v_cur", n_cur)
-    if mass_cached is not None and mass_cached.numel() != H * q.shape[0]:
-        raise ValueError("mass_cached must hold heads * m values")
-    for t in (k_cur, v_cur, out):
-        if t is not None and (t.dtype != cache.torch_dtype or (t.shape[0] > 0 and _tok_head_strides(t) != (st, sh))):
+    for t, tokens in ((k_cur, n_cur), (v_cur, n_cur), (out, rows)):
+        if t is not None and (t.dtype != dtype or (tokens > 0 and _tok_head_strides(t) != strides)):
             raise ValueError("q, k_cur, v_cur and out must share dtype and strides")
-    if q.dtype != cache.torch_dtype:
+    if q.dtype != dtype:
         raise ValueError("q must be in the cache's io dtype")
-    if mass_cached is not None and (mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous()):
-        raise ValueError("mass_cached must be a contiguous float32 [heads][m] tensor")
+    if mass_cached is not None:
+        if mass_cached.numel() != H * rows:
+            raise ValueError("mass_cached must hold heads * m values")
+        if mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous():
+            raise ValueError("mass_cached must be a contiguous float32 [heads][m] tensor")
+    cache_start, cache_len = int(cache_start), int(cache_len)
+    args = (cache.handle, cache_start, cache_len, q.data_ptr(), _ptr(k_cur), _ptr(v_cur), rows, n_cur, st, sh,
+            float(softmax_scale), int(correction))
+    mass = _ptr(mass_cached)
     if may_split and cache_len + n_cur > _NEVER_SPLIT_KEYS and correction != 2:
-        ws = _workspace(cache, int(cache_start), int(cache_len), q.shape[0], n_cur, 1, stream)
+        ws = _workspace(cache, cache_start, cache_len, rows, n_cur, 1, stream)
         if ws is not None:
-            return _launch_split(cache, ws, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
-                                 None, out, mass_cached, stream, "kvq_chunk_attention")
-    _check(fn(cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur), _ptr(v_cur), q.shape[0],
-              n_cur, st, sh, float(softmax_scale), int(correction), out.data_ptr(), _ptr(mass_cached),
-              _stream(stream)), "kvq_chunk_attention")
+            _check(lib().kvq_chunk_attention_ws(*args, None, out.data_ptr(), mass, ws.data_ptr(), ws.numel(), _stream(stream)),
+                   "kvq_chunk_attention")
+            return
+    _check(fn(*args, out.data_ptr(), mass, _stream(stream)), "kvq_chunk_attention")
 
 
 def kvq_chunk_attention(cache: Cache, cache_start: int, cache_len: int, q: torch.Tensor,
@@ -319,36 +325,36 @@ def kvq_chunk_attention_ex(cache: Cache, cache_start: int, cache_len: int, q: to
                            correction: int = 1, causal: bool = False,
                            stream: Optional[torch.cuda.Stream] = None) -> None:
     """Grouped-query heads (q has a multiple of the cache's head count) and / or a causal current block."""
-    kv = k_cur if k_cur is not None else v_cur
-    if q.shape[1] % cache.desc.num_heads != 0:
+    heads, d, dtype = cache.desc.num_heads, cache.desc.head_dim, cache.torch_dtype
+    qst, qsh = q_strides = _tok_head_strides(q)
+    q_heads = q.shape[1]
+    if q_heads % heads != 0:
         raise ValueError("query heads must be a multiple of the cache's heads")
-    for t in (k_cur, v_cur):
-        if t is not None and (t.dtype != cache.torch_dtype or (kv.shape[0] > 0 and _tok_head_strides(t) != _tok_head_strides(kv))):
-            raise ValueError("k_cur and v_cur must share dtype and strides")
-    if q.dtype != cache.torch_dtype or out.dtype != cache.torch_dtype or _tok_head_strides(out) != _tok_head_strides(q):
+    rows = _check_shape(q, q_heads, d, "q")
+    _check_shape(out, q_heads, d, "out", rows)
+    if q.dtype != dtype or out.dtype != dtype or _tok_head_strides(out) != q_strides:
         raise ValueError("q and out must be in the cache's io dtype and share strides")
-    if mass_cached is not None and (mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous()):
-        raise ValueError("mass_cached must be a contiguous float32 [query heads][m] tensor")
-    n_cur_tokens = 0 if k_cur is None else k_cur.shape[0]
-    _check_shape(q, q.shape[1], cache.desc.head_dim, "q")
-    _check_shape(out, q.shape[1], cache.desc.head_dim, "out", q.shape[0])
-    _check_shape(k_cur, cache.desc.num_heads, cache.desc.head_dim, "k_cur")
-    _check_shape(v_cur, cache.desc.num_heads, cache.desc.head_dim, "v_cur", n_cur_tokens)
-    if mass_cached is not None and mass_cached.numel() != q.shape[1] * q.shape[0]:
-        raise ValueError("mass_cached must hold query heads * m values")
-    qst, qsh = _tok_head_strides(q)
-    st, sh = _tok_head_strides(kv) if kv is not None and kv.shape[0] > 0 else (cache.desc.num_heads * cache.desc.head_dim, cache.desc.head_dim)
-    opts = kvq_attention_opts(q.shape[1] // cache.desc.num_heads, int(bool(causal)), qst, qsh)
-    n_cur = 0 if k_cur is None else k_cur.shape[0]
+    n_cur = _check_shape(k_cur, heads, d, "k_cur")
+    _check_shape(v_cur, heads, d, "v_cur", n_cur)
+    st, sh = kv_strides = _tok_head_strides(v_cur if k_cur is None else k_cur) if n_cur > 0 else (heads * d, d)
+    for t in (k_cur, v_cur):
+        if t is not None and (t.dtype != dtype or (n_cur > 0 and _tok_head_strides(t) != kv_strides)):
+            raise ValueError("k_cur and v_cur must share dtype and strides")
+    if mass_cached is not None:
+        if mass_cached.dtype != torch.float32 or not mass_cached.is_contiguous():
+            raise ValueError("mass_cached must be a contiguous float32 [query heads][m] tensor")
+        if mass_cached.numel() != q_heads * rows:
+            raise ValueError("mass_cached must hold query heads * m values")
+    ratio, cache_start, cache_len = q_heads // heads, int(cache_start), int(cache_len)
+    args = (cache.handle, cache_start, cache_len, q.data_ptr(), _ptr(k_cur), _ptr(v_cur), rows, n_cur, st, sh,
+            float(softmax_scale), int(correction), ctypes.byref(kvq_attention_opts(ratio, int(bool(causal)), qst, qsh)),
+            out.data_ptr(), _ptr(mass_cached))
     if cache_len + n_cur > _NEVER_SPLIT_KEYS and correction != 2:      # (2 runs on the vector kernel)
-        ws = _workspace(cache, int(cache_start), int(cache_len), q.shape[0], n_cur, opts.q_heads_per_kv_head, stream)
+        ws = _workspace(cache, cache_start, cache_len, rows, n_cur, ratio, stream)
         if ws is not None:
-            return _launch_split(cache, ws, cache_start, cache_len, q, k_cur, v_cur, n_cur, st, sh, softmax_scale, correction,
-                                 ctypes.byref(opts), out, mass_cached, stream, "kvq_chunk_attention_ex")
-    _check(lib().kvq_chunk_attention_ex(cache.handle, int(cache_start), int(cache_len), q.data_ptr(), _ptr(k_cur),
-                                        _ptr(v_cur), q.shape[0], n_cur, st, sh, float(softmax_scale), int(correction),
-                                        ctypes.byref(opts), out.data_ptr(), _ptr(mass_cached), _stream(stream)),
-           "kvq_chunk_attention_ex")
+            _check(lib().kvq_chunk_attention_ws(*args, ws.data_ptr(), ws.numel(), _stream(stream)), "kvq_chunk_attention_ex")
+            return
+    _check(lib().kvq_chunk_attention_ex(*args, _stream(stream)), "kvq_chunk_attention_ex")
 
 
 def kvq_attention_diagnostics(cache: Cache, cache_start: int, cache_len: int, q: torch.Tensor,
