@@ -17,9 +17,9 @@
 // and a shift per one to three registers: the code lands in mantissa bits of a 16-bit float whose
 // exponent makes the value BASE + weight * code (see "Unpacking" below).  Key codes and the rotated
 // query use f16 (same MFMA rate as bf16, three more significant bits; codes are exact either way) and
-// the query is carried as an f16 high part plus a low part (f16, or FP8 where the switches below say so);
-// value codes and probabilities use bf16 (its range is needed for p * value-scale).  The 2-bit keys of
-// per-token caches take a shorter way (KVQ_KEYS_FP4 below): the codes are FP4 values as they stand and the query
+// the query is carried as an f16 high part plus an f16 low part;
+// value codes and probabilities use bf16 (its range is needed for p * value-scale).  2-bit keys
+// take a shorter way (KVQ_KEYS_FP4 below): the codes are FP4 values as they stand and the query
 // is four FP6 pieces, multiplied by the block-scaled 64-channel MFMA at twice the FP8 rate.  Per-token scale and zero-point never touch the operands: with one
 // (scale, zero) per token
 //     s_mi = scale_i * ( q~_m . (BASE + code_i)  -  z_i * sum_c q~_mc  -  BASE * W_m  -  scale_i * nu'_m )
@@ -70,21 +70,18 @@
 #ifndef KVQ_Q_LOW_RESIDENT_SLABS
 #define KVQ_Q_LOW_RESIDENT_SLABS 2
 #endif
-// 1 (2-bit caches only): the low query part is an FP8 E4M3 operand with one power-of-two scale per row and
-// meets the key codes in v_mfma_scale_f32_32x32x64_f8f6f4 (64 channels per instruction at twice the
-// 16-bit rate): 4 MFMAs per key tile instead of 16, the whole low part resident in 32 accumulation
-// registers.  0: f16 low part as for 4-bit caches.
-// 1 (2-bit caches, not the per-channel path): the key codes are the MFMA operand.  E2M1 encodes 0, 0.5, 1, 1.5 as
+// 1 (2-bit caches): the key codes are the MFMA operand.  E2M1 encodes 0, 0.5, 1, 1.5 as
 // 0..3, so a packed word is two FP4 operand registers (w & 0x33333333, (w >> 2) & 0x33333333); the query is four
 // FP6 (E2M3) pieces n_k / 2 with one power-of-two scale per row and piece, n_k integers of at most four bits plus
 // sign, each piece four bits finer than the one before.  16 v_mfma_scale_f32_32x32x64_f8f6f4 (FP4 x FP6) per key
-// tile replace 16 f16 and 4 FP8 MFMAs, 12 unpacking instructions replace 64, the BASE term vanishes (W = 0), and
-// the 96 piece registers live where the 64 + 32 registers of the high and low parts lived.  0: high + low pair.
+// tile replace 32 f16 MFMAs, 12 unpacking instructions replace 64, the BASE term vanishes (W = 0), and
+// the 96 piece registers live where the high and low parts lived.  0: high + low pair.
+// Per-channel caches too: 8 heads x 1024 rows x (4 blocks of 1024 + 1024) keys, append included, 122 -> 105 us, with the
+// preparation below; with a preparation through LDS it was 153 us, slower than the pair.  Against 64 bits the masses' relative
+// error (256 rows x 1024 keys, normal values) is 5e-8; with the pair of an f16 and an FP8 part, queries three times larger,
+// 7.1e-7 became 1.5e-7, and with one channel that dwarfs the others 1.7e-6 became 3.2e-7.
 #ifndef KVQ_KEYS_FP4
 #define KVQ_KEYS_FP4 1
-#endif
-#ifndef KVQ_Q_LOW_FP8
-#define KVQ_Q_LOW_FP8 1
 #endif
 // 1 (kernels with FP4 key operands): the score MFMAs are written out with vector-register destinations, so that no
 // score has to be copied out of an accumulation register before the vector ALU can scale it (32 copies per key tile).
@@ -134,7 +131,8 @@ template <int BITS> constexpr size_t lds_bytes()
 // the channel steps go into the query operand, q'_c = q~_c * step_c, after which the block looks like a
 // per-token cache with step 1 and zero-point 0 whose rows carry two constants: Z = sum_c q'_c z_c and the
 // block's correction sigma^2 / 24 * sum_c (q^_c step_c)^2.  The cached keys are therefore processed block by
-// block, the query operands prepared anew for each.
+// block, the query operands prepared anew for each (the output tile stays in registers meanwhile: about a hundred registers go
+// to scratch around the preparation, none inside the loops over tiles).
 template <int BITS, bool CORR, bool FP8META, bool PERCH = false>
 __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionArgs a, SplitArgs sp)
 {
@@ -159,251 +157,28 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
     const UnpackConsts uc = make_unpack_consts<BITS>();
 
     // ---------------------------------------------------------------- query preparation ----
-    // kPrepLanes adjacent lanes rotate one query row of the block: q~ = Hn q * softmax_scale * log2(e),
-    // split into an f16 high and low part; nu = ||q||^2; the row sum of the (high + low) parts.
-    constexpr bool kFp4 = KVQ_KEYS_FP4 && BITS == 2 && !PERCH;
+    // q~ = Hn q * softmax_scale * log2(e), split into operand parts; nu = ||q||^2; the row sum of the parts.
+    // 4-bit keys: kPrepLanes adjacent lanes rotate one query row of the block, f16 high and low part.
+    constexpr bool kFp4 = KVQ_KEYS_FP4 && BITS == 2;
     constexpr bool kVs = KVQ_SCORES_IN_VGPRS && kFp4;   // score tile in vector registers (written-out MFMAs)
-    constexpr bool kLoFp8 = KVQ_Q_LOW_PART && KVQ_Q_LOW_FP8 && BITS == 2 && !kFp4;
-    constexpr bool kLoF16 = KVQ_Q_LOW_PART && !kLoFp8 && !kFp4;
+    constexpr bool kLoF16 = KVQ_Q_LOW_PART && !kFp4;
     constexpr int kPrepLanes = kThreads / kRowsPerBlock;   // 1 or 2
     constexpr int kPrepCh = D / kPrepLanes;                 // channels per lane
     // FP4 keys: the query as four FP6 (E2M3) pieces, B operands of the 64-channel MFMAs: [row block][piece][MFMA]
     i32x6 qp[kRB][4][2];
     u32x4 qop[kRB][8];  // B operands of the score MFMA: lane (n, hh) holds channels 16*slab + 8*hh .. +7 of rows n + 32 rb
-    {
-        const int prow = tid / kPrepLanes, ppart = tid % kPrepLanes;
-        int64_t row = (int64_t)rblk * kRowsPerBlock + prow;
-        row = row < a.m ? row : a.m - 1;
-        const uint4 *src = reinterpret_cast<const uint4 *>(q_base + row * a.q_stride_token + ppart * kPrepCh);
-        float x[kPrepCh];
-#pragma unroll
-        for (int i = 0; i < kPrepCh / 8; ++i) {
-            const uint4 w = src[i];
-            const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                x[8 * i + 2 * j] = __uint_as_float(ws[j] << 16);
-                x[8 * i + 2 * j + 1] = __uint_as_float(ws[j] & 0xffff0000u);
-            }
-        }
-        float nu = 0.0f;
-#pragma unroll
-        for (int i = 0; i < kPrepCh; ++i) nu = fmaf(x[i], x[i], nu);
-        // Randomised rotation: the channel signs come before the Hadamard matrix.
-        if (has_signs(a.cv))
-#pragma unroll
-        for (int w = 0; w < kPrepCh / 32; ++w) {
-            const uint32_t sg = sign_bits_from(a.cv, ppart * kPrepCh + 32 * w);
-#pragma unroll
-            for (int i = 0; i < 32; ++i) x[32 * w + i] = flip_sign(x[32 * w + i], sg >> i);
-        }
-#pragma unroll
-        for (int h = 1; h < kPrepCh; h <<= 1) {
-#pragma unroll
-            for (int i = 0; i < kPrepCh; ++i) {
-                if ((i & h) == 0) {
-                    const float p = x[i], q2 = x[i + h];
-                    x[i] = p + q2;
-                    x[i + h] = p - q2;
-                }
-            }
-        }
-        if constexpr (kPrepLanes == 2) {   // last butterfly stage: between the two lanes of the row
-            nu += __shfl_xor(nu, 1);
-#pragma unroll
-            for (int i = 0; i < kPrepCh; ++i) {
-                const float other = __shfl_xor(x[i], 1);
-                x[i] = ppart ? other - x[i] : x[i] + other;
-            }
-        }
-        // Channel c of the operand carries 4^g(c) (the inverse of the weight its key codes are unpacked with).
-        const float cq = c_log * 0.088388347648318f;
-#pragma unroll
-        for (int i = 0; i < kPrepCh; ++i) x[i] *= cq * (kFp4 ? 1.0f : (float)(1 << (Unpack<BITS>::kClassBits * key_channel_class<BITS>(i))));
-        // The staging rows hold the high parts first (read into registers below), then the low parts,
-        // which stay in LDS for the whole cached-key loop.
-        uint32_t *dst = q_stage + prow * kQRowWords + ppart * (kPrepCh / 2);
-        if constexpr (!kFp4) {
-#pragma unroll
-        for (int i = 0; i < kPrepCh / 8; ++i) {
-            u32x4 w;
-            w.x = pack_f16(x[8 * i], x[8 * i + 1]); w.y = pack_f16(x[8 * i + 2], x[8 * i + 3]);
-            w.z = pack_f16(x[8 * i + 4], x[8 * i + 5]); w.w = pack_f16(x[8 * i + 6], x[8 * i + 7]);
-            *reinterpret_cast<u32x4 *>(dst + 4 * i) = w;
-        }
-        __syncthreads();
-        const uint32_t *hsrc = q_stage + (wave * kRowsPerWave + n) * kQRowWords + 4 * hh;
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                qop[rb][s] = *reinterpret_cast<const u32x4 *>(hsrc + 32 * rb * kQRowWords + 8 * s);
-        __syncthreads();
-        }
-        float ssum = 0.0f, ssum_w = 0.0f;   // sum of q~ (true scale), sum of the weighted operand values
-        if constexpr (kFp4) {
-            static_assert(!kFp4 || kPrepLanes == 1, "one lane prepares a whole row");
-            // q~ = sum of four FP6 (E2M3) pieces times 2^e_k, e_0 = e0 with the row maximum in (3.75, 7.5] * 2^e0,
-            // e_k = e0 - 4 k - 1 after that.  E2M3 holds every multiple of 1/2 up to 7.5 (and finer steps below 4), so what
-            // piece 0 leaves is at most a quarter of its scale, i.e. 8 scales of piece 1: five bits finer, and what lies
-            // above 7.5 is clamped there, which leaves the next piece half a scale of its predecessor -- again 8 of its
-            // own, clamped likewise.  The last step is at most 2^(e0 - 14); the error is a quarter of it, half of it
-            // after a clamp.  The pieces are made and read back by the 32-wide hardware conversions (a conversion, a
-            // conversion back and 32 subtractions per 32 channels and piece): rounding, clamping and assembling the
-            // codes by hand took eleven instructions per channel and piece (8 heads x 1024 rows x (4096 + 1024) keys in 8 pieces:
-            // 66 -> 54 us for the launch).
-            float mx = 0.0f;
-#pragma unroll
-            for (int c = 0; c < kPrepCh; ++c) {
-                mx = fmaxf(mx, fabsf(x[c]));
-                ssum += x[c];
-            }
-            int e0 = (int)((__float_as_uint(mx * (1.0f / 7.5f)) >> 23) & 0xffu) - 126;
-            e0 = e0 < -100 ? -100 : e0 > 110 ? 110 : e0;
-            // The channels in operand order.  Element j of operand op (MFMA jm = op >> 1, lane half hw = op & 1) belongs to
-            // word 2 jm + (j >> 4), 2-bit field 2 (j & 7) + ((j >> 3) & 1) of the lane's key words (see key_pair); the
-            // conversion takes even elements from its first operand and odd ones from its second.
-            auto channel = [](int op, int j) {
-                const int jm = op >> 1, hw = op & 1, wd = 2 * jm + (j >> 4), f = 2 * (j & 7) + ((j >> 3) & 1);
-                const int pr = f & 7, slab = 2 * wd + (pr >> 2);
-                return 16 * slab + 8 * hw + 2 * (pr & 3) + (f >> 3);
-            };
-            f32x16 xe[4], xo[4];
-#pragma unroll
-            for (int op = 0; op < 4; ++op)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    xe[op][j] = x[channel(op, 2 * j)];
-                    xo[op][j] = x[channel(op, 2 * j + 1)];
-                }
-            uint32_t scale_word = 0u;
-#pragma unroll
-            for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
-                    const int ek = e0 - 4 * (2 * pass + kk) - (2 * pass + kk > 0 ? 1 : 0);
-                    const float piece_scale = __uint_as_float((uint32_t)(127 + ek) << 23);
-                    // the key operand holds code / 2: one more factor of two in the scale byte
-                    scale_word |= (uint32_t)(127 + ek + 1) << (8 * (2 * pass + kk));
-#pragma unroll
-                    for (int op = 0; op < 4; ++op) {       // MFMA jm = op >> 1, lane half hw = op & 1
-                        const int jm = op >> 1, hw = op & 1;
-                        const u32x6 d = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(xe[op], xo[op], piece_scale);
-                        const f32x32 held = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(d, piece_scale);
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) {
-                            xe[op][j] -= held[2 * j];
-                            xo[op][j] -= held[2 * j + 1];
-                        }
-                        uint32_t *pd = q_stage + prow * kQRowWords + (2 * kk + jm) * 12 + hw * 6;
-#pragma unroll
-                        for (int i = 0; i < 6; i += 2) *reinterpret_cast<u32x2 *>(pd + i) = u32x2{d[i], d[i + 1]};
-                    }
-                }
-                __syncthreads();
-#pragma unroll
-                for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                        for (int jm = 0; jm < 2; ++jm) {
-                            const uint32_t *ps = q_stage + (wave * kRowsPerWave + 32 * rb + n) * kQRowWords + (2 * kk + jm) * 12 + hh * 6;
-                            const u32x2 p0 = *reinterpret_cast<const u32x2 *>(ps), p1 = *reinterpret_cast<const u32x2 *>(ps + 2),
-                                        p2 = *reinterpret_cast<const u32x2 *>(ps + 4);
-                            qp[rb][2 * pass + kk][jm] = i32x6{(int)p0.x, (int)p0.y, (int)p1.x, (int)p1.y, (int)p2.x, (int)p2.y};
-                        }
-                __syncthreads();
-            }
-            // the row sum of what the pieces hold: the sum of q~ minus the sum of what is left of it
-#pragma unroll
-            for (int op = 0; op < 4; ++op)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) ssum -= xe[op][j] + xo[op][j];
-            row_scal[4 * prow + 3] = __uint_as_float(scale_word);
-        } else if constexpr (kLoFp8) {
-            static_assert(!kLoFp8 || kPrepLanes == 1, "one lane prepares a whole row");
-            // Low parts at true scale (the weight 4^g of the high operand taken out again: exact), their
-            // largest magnitude, and from it the row's power-of-two scale: the largest low part lands in
-            // [128, 256), inside the E4M3 range.
-            float lo_t[kPrepCh], mx = 0.0f;
-#pragma unroll
-            for (int c = 0; c < kPrepCh; c += 2) {
-                const uint32_t hi = pack_f16(x[c], x[c + 1]);
-                const float wgt = 1.0f / (float)(1 << (Unpack<BITS>::kClassBits * key_channel_class<BITS>(c)));   // both channels share a class
-                lo_t[c] = (x[c] - f16_lo(hi)) * wgt;
-                lo_t[c + 1] = (x[c + 1] - f16_hi(hi)) * wgt;
-                mx = fmaxf(mx, fmaxf(fabsf(lo_t[c]), fabsf(lo_t[c + 1])));
-                ssum_w += f16_lo(hi) + f16_hi(hi);
-                ssum += (f16_lo(hi) + f16_hi(hi)) * wgt;
-            }
-            const int ex = mx > 0.0f ? (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127 - 7 : 0;   // floor(log2 mx) - 7
-            const float down = __uint_as_float((uint32_t)(127 - ex) << 23), up = __uint_as_float((uint32_t)(127 + ex) << 23);
-            // Operand order: MFMA j (channels of key words 2 j, 2 j + 1), lane half hh, register r8, byte b hold
-            // the channel whose code the key unpacking puts into the same byte.
-#pragma unroll
-            for (int w = 0; w < 32; ++w) {
-                const int j = w >> 4, hw = (w >> 3) & 1, r8 = w & 7;
-                float v[4];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int slab = 2 * (2 * j + (r8 >> 2)) + (b & 1);
-                    v[b] = lo_t[16 * slab + 8 * hw + 2 * (r8 & 3) + (b >> 1)] * down;
-                }
-                int word = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], 0, false);
-                word = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], word, true);
-                dst[w] = (uint32_t)word;
-                float dec = 0.0f;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) dec += e4m3_to_float((uint8_t)((uint32_t)word >> (8 * b)));
-                ssum += dec * up;      // the sums follow the operands the MFMAs will see
-                ssum_w += 2.0f * (dec * up);   // FP8 key values are 8 + code, twice the BASE the constant term takes off
-            }
-            row_scal[4 * prow + 3] = __int_as_float(127 + ex);
-        } else {
-#pragma unroll
-        for (int i = 0; i < kPrepCh / 8; ++i) {
-            uint32_t lo[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v0 = x[8 * i + 2 * j], v1 = x[8 * i + 2 * j + 1];
-                const uint32_t hi = pack_f16(v0, v1);
-                const float h0 = f16_lo(hi), h1 = f16_hi(hi);
-                lo[j] = pack_f16(v0 - h0, v1 - h1);
-#if KVQ_Q_LOW_PART
-                const float pair = (h0 + f16_lo(lo[j])) + (h1 + f16_hi(lo[j]));   // both channels share a class
-#else
-                const float pair = h0 + h1;
-#endif
-                ssum_w += pair;
-                ssum += pair * (1.0f / (float)(1 << (Unpack<BITS>::kClassBits * key_channel_class<BITS>(8 * i + 2 * j))));
-            }
-            u32x4 w;
-            w.x = lo[0]; w.y = lo[1]; w.z = lo[2]; w.w = lo[3];
-            *reinterpret_cast<u32x4 *>(dst + 4 * i) = w;
-        }
-        }
-        if constexpr (kPrepLanes == 2) {
-            ssum += __shfl_xor(ssum, 1);
-            ssum_w += __shfl_xor(ssum_w, 1);
-        }
-        if (ppart == 0) {
-            row_scal[4 * prow] = ssum;
-            row_scal[4 * prow + 1] = ssum_w;
-            row_scal[4 * prow + 2] = CORR ? -a.softmax_scale * a.softmax_scale * kLog2e * nu * (1.0f / 24.0f) : 0.0f;
-        }
-    }
-    __syncthreads();
-    // B operand of the constant-term MFMA, per 32-row block.  The raw score is sum_c (q~_c 4^g) (BASE +
-    // 4^-g code_c) = q~ . code + BASE * W with W the sum of the weighted operand values, so what has to
-    // come off is z * S + BASE * W (S = sum_c q~_c).  Lane half 0 multiplies the key's -z pieces and the
-    // mask bias, lane half 1 the key's scale pieces and the constant -BASE:
-    //   hh = 0: [S_h, S_m, S_l, S_h, S_m, S_l, 1, 0]     S in three bf16 pieces
-    //   hh = 1: [N_h, N_l, N_h, N_l, W_h, W_m, W_l, 0]   N = -nu' in two pieces, W in three
-    u32x4 rowop[kRB];
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-        const float *rs = row_scal + 4 * (wave * kRowsPerWave + 32 * rb + n);
-        const float ssum = rs[0], wsum = rs[1], nnu = rs[2];
+    u32x4 rowop[kRB];   // B operand of the constant-term MFMA, per 32-row block
+    int qp_scale[kRB] = {};
+    constexpr int kLoRes = kLoF16 ? KVQ_Q_LOW_RESIDENT_SLABS : 0;
+    u32x4 lo_res[kRB][kLoRes > 0 ? kLoRes : 1];
+    const uint32_t lo_off = (uint32_t)((wave * kRowsPerWave + n) * kQRowWords + 4 * hh);  // words into q_stage
+    // The constant terms.  The raw score is sum_c (q~_c 4^g) (BASE + 4^-g code_c) = q~ . code + BASE * W with W the sum of the
+    // weighted operand values, so what has to come off is z * S + BASE * W (S = sum_c q~_c; W = 0 where the codes themselves
+    // are the operand).  Lane half 0 multiplies the key's -z pieces and the mask bias, lane half 1 the key's scale pieces and
+    // the constant -BASE:
+    //   hh = 0: [S_h, S_m, S_l, S_h, S_m, S_l, 1, 1]     S in three bf16 pieces
+    //   hh = 1: [N_h, N_l, N_h, N_l, W_h, W_m, W_l, 1]   N = -nu' in two pieces, W in three
+    auto row_operand = [&](float ssum, float wsum, float nnu) {
         const uint16_t s_h = bf16_bits(ssum);
         const float r1 = ssum - bf16_val(s_h);
         const uint16_t s_m = bf16_bits(r1);
@@ -420,22 +195,143 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
         w0.z = s_m | ((uint32_t)s_l << 16); w0.w = one | (one << 16);
         w1.x = n_h | ((uint32_t)n_l << 16); w1.y = w1.x;
         w1.z = w_h | ((uint32_t)w_m << 16); w1.w = w_l | (one << 16);
-        rowop[rb] = hh ? w1 : w0;
-    }
-    const uint32_t lo_off = (uint32_t)((wave * kRowsPerWave + n) * kQRowWords + 4 * hh);  // words into q_stage
-    // The 64 registers of query operands live in accumulation registers (MFMA reads them from there
-    // directly), which leaves the vector registers to the score tile in flight.
-    if constexpr (!kFp4) {
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-        for (int s = 0; s < 8; ++s) asm volatile("" : "+a"(qop[rb][s]));
-    }
-    // FP4 keys: the 96 registers of query pieces likewise, and the four scale bytes of each row
-    int qp_scale[kRB] = {};
+        return hh ? w1 : w0;
+    };
+    // Once per workgroup; per-channel caches: for each block of keys, whose steps and zero-points of the rotated channels
+    // are ch_step and ch_zero.
+    auto prepare = [&](const float *ch_step, const float *ch_zero) {
     if constexpr (kFp4) {
+        // q~ = sum of four FP6 (E2M3) pieces times 2^e_k, e_0 = e0 with the row maximum in (3.75, 7.5] * 2^e0,
+        // e_k = e0 - 4 k - 1 after that.  E2M3 holds every multiple of 1/2 up to 7.5 (and finer steps below 4), so what
+        // piece 0 leaves is at most a quarter of its scale, i.e. 8 scales of piece 1: five bits finer, and what lies
+        // above 7.5 is clamped there, which leaves the next piece half a scale of its predecessor -- again 8 of its
+        // own, clamped likewise.  The last step is at most 2^(e0 - 14); the error is a quarter of it, half of it
+        // after a clamp.  The pieces are made and read back by the 32-wide hardware conversions (a conversion, a
+        // conversion back and 32 subtractions per 32 channels and piece).
+        //
+        // The rotation leaves every lane (row n, half hh) with the 64 channels of its B operands (bit 3 = hh), so nothing goes
+        // through LDS: channel bits 0 .. 3 by one MFMA per 16 channels against the signs of a 16 x 16 Hadamard matrix (bf16
+        // products are exact, sums fp32), bits 4 .. 6 by butterflies between registers.  With a lane per row and all seven
+        // stages in its registers the preparation was 3200 instructions and five barriers instead of 1500 and none (8 heads x
+        // 1024 rows x (4096 + 1024) keys, append included: 64.1 -> 61.4 us).
+        int ln = lane;
+        asm volatile("" : "+v"(ln));     // (per-channel caches: `had` and the signs are made anew for each block, not kept in scratch)
+        const int hp = ln >> 5;
+        u32x4 had;
+        {
+            const int low = 4 * ((ln >> 3) & 1) + (ln & 3), both = (ln >> 2) & hp & 1;     // row ln & 31 of the product: channel 8 ((ln >> 2) & 1) + low
+            uint32_t w[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const uint32_t even = (uint32_t)(__popc(low & (2 * p)) + both) & 1u, odd = (uint32_t)(__popc(low & (2 * p + 1)) + both) & 1u;
+                w[p] = 0x3f803f80u ^ (even << 15) ^ (odd << 31);
+            }
+            had = u32x4{w[0], w[1], w[2], w[3]};
+        }
+        const float cq = c_log * 0.088388347648318f;
+        // The channels in operand order.  Element j of MFMA jm belongs to word 2 jm + (j >> 4), 2-bit field
+        // 2 (j & 7) + ((j >> 3) & 1) of the lane's key words (see key_pair); the conversion takes even elements from
+        // its first operand and odd ones from its second.  Here: 8 * slab + channel within the half slab.
+        auto place_of = [](int jm, int j) {
+            const int wd = 2 * jm + (j >> 4), f = 2 * (j & 7) + ((j >> 3) & 1), pr = f & 7, slab = 2 * wd + (pr >> 2);
+            return 8 * slab + 2 * (pr & 3) + (f >> 3);
+        };
 #pragma unroll
         for (int rb = 0; rb < kRB; ++rb) {
+            int64_t row = wave_row0 + 32 * rb + (ln & 31);
+            row = row < a.m ? row : a.m - 1;
+            const uint16_t *src = q_base + row * a.q_stride_token + 8 * hp;
+            float x[64];        // [slab][channel within the half]
+#pragma unroll
+            for (int sl = 0; sl < 8; ++sl) {
+                u32x4 w = *reinterpret_cast<const u32x4 *>(src + 16 * sl);
+                if (has_signs(a.cv)) {     // randomised rotation: the channel signs come before the Hadamard matrix
+                    const uint32_t sg = sign_bits_from(a.cv, 16 * sl) >> (8 * hp);
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) w[p] ^= ((sg >> (2 * p)) & 1u) << 15 | ((sg >> (2 * p + 1)) & 1u) << 31;
+                }
+                f32x16 z;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) z[v] = 0.0f;
+                z = mfma_bf16(had, w, z);
+#pragma unroll
+                for (int v = 0; v < 8; ++v) x[8 * sl + v] = z[v];
+                if (PERCH && (sl & 1)) KVQ_CHUNK_FENCE();     // (the output tile is live here: registers)
+            }
+#pragma unroll
+            for (int h = 8; h < 64; h <<= 1)
+#pragma unroll
+                for (int i = 0; i < 64; ++i)
+                    if ((i & h) == 0) {
+                        const float p = x[i], q2 = x[i + h];
+                        x[i] = p + q2;
+                        x[i + h] = p - q2;
+                    }
+            float nu = 0.0f, ssum = 0.0f, mx = 0.0f;
+            if constexpr (PERCH) {   // q^_c step_c
+#pragma unroll
+                for (int sl = 0; sl < 8; ++sl)
+#pragma unroll
+                    for (int v = 0; v < 8; v += 4) {
+                        const float4 st = *reinterpret_cast<const float4 *>(ch_step + 16 * sl + 8 * hp + v);
+                        x[8 * sl + v] *= st.x; x[8 * sl + v + 1] *= st.y; x[8 * sl + v + 2] *= st.z; x[8 * sl + v + 3] *= st.w;
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < 64; ++i) {
+                nu = fmaf(x[i], x[i], nu);
+                x[i] *= cq;
+                mx = fmaxf(mx, fabsf(x[i]));
+            }
+            // sum of q~ (per-channel keys: weighted by the channels' zero-points), less what the pieces leave of it
+            auto add_sum = [&](float sign) {
+#pragma unroll
+                for (int sl = 0; sl < 8; ++sl)
+#pragma unroll
+                    for (int v = 0; v < 8; v += 4) {
+                        float4 zc = {1.0f, 1.0f, 1.0f, 1.0f};
+                        if constexpr (PERCH) zc = *reinterpret_cast<const float4 *>(ch_zero + 16 * sl + 8 * hp + v);
+                        ssum = fmaf(sign * x[8 * sl + v], zc.x, ssum); ssum = fmaf(sign * x[8 * sl + v + 1], zc.y, ssum);
+                        ssum = fmaf(sign * x[8 * sl + v + 2], zc.z, ssum); ssum = fmaf(sign * x[8 * sl + v + 3], zc.w, ssum);
+                    }
+            };
+            add_sum(1.0f);
+            if (PERCH) KVQ_CHUNK_FENCE();
+            mx = max_halves(mx);
+            int e0 = (int)((__float_as_uint(mx * (1.0f / 7.5f)) >> 23) & 0xffu) - 126;
+            e0 = e0 < -100 ? -100 : e0 > 110 ? 110 : e0;
+            uint32_t scale_word = 0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int ek = e0 - 4 * k - (k > 0 ? 1 : 0);
+                const float piece_scale = __uint_as_float((uint32_t)(127 + ek) << 23);
+                scale_word |= (uint32_t)(127 + ek + 1) << (8 * k);   // the key operand holds code / 2: one more factor of two
+#pragma unroll
+                for (int jm = 0; jm < 2; ++jm) {
+                    f32x16 xe, xo;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        xe[j] = x[place_of(jm, 2 * j)];
+                        xo[j] = x[place_of(jm, 2 * j + 1)];
+                    }
+                    const u32x6 d = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(xe, xo, piece_scale);
+                    const f32x32 held = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(d, piece_scale);
+#pragma unroll
+                    for (int j = 0; j < 32; ++j) x[place_of(jm, j)] -= held[j];
+                    qp[rb][k][jm] = i32x6{(int)d[0], (int)d[1], (int)d[2], (int)d[3], (int)d[4], (int)d[5]};
+                }
+            }
+            add_sum(-1.0f);
+            if (PERCH) KVQ_CHUNK_FENCE();
+            qp_scale[rb] = (int)scale_word;
+            ssum += xhalf(ssum);
+            nu += xhalf(nu);
+            rowop[rb] = row_operand(ssum, 0.0f, CORR ? -a.softmax_scale * a.softmax_scale * kLog2e * nu * (1.0f / (24.0f * D)) : 0.0f);
+        }
+        // The 96 registers of query pieces live in accumulation registers (MFMA reads them from there directly), which leaves
+        // the vector registers to the score tile in flight.
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb)
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -443,175 +339,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
                     if (kVs && k == 3 && j == 1) asm volatile("" : "+v"(qp[rb][k][j]));
                     else asm volatile("" : "+a"(qp[rb][k][j]));
                 }
-            qp_scale[rb] = __float_as_int(row_scal[4 * (wave * kRowsPerWave + 32 * rb + n) + 3]);
-        }
-    }
-    // 2-bit codes are FP4 (E2M1) values as they stand, 0, 0.5, 1, 1.5: a packed word is two operand registers, the
-    // even and the odd fields, each in the low half of a nibble.  Four pieces x two 64-channel MFMAs per row block,
-    // FP4 x FP6 at twice the FP8 rate; opsel picks the piece's byte of the row's scale word.
-    uint32_t f4_mask = 0x33333333u;
-    asm volatile("" : "+s"(f4_mask));
-    auto fp4_operand = [&](auto j_, const uint32_t (&kw)[WPL]) {   // key words 2 J, 2 J + 1
-        constexpr int J = decltype(j_)::value;
-        const uint32_t w0 = kw[(2 * J) % WPL], w1 = kw[(2 * J + 1) % WPL];
-        return i32x8{(int)(w0 & f4_mask), (int)((w0 >> 2) & f4_mask), (int)(w1 & f4_mask), (int)((w1 >> 2) & f4_mask), 0, 0, 0, 0};
-    };
-    auto fp4_mfma = [&](auto j_, auto k_, const i32x8 &a4, f32x16 (&sn)[kRB]) {   // piece K against key words 2 J, 2 J + 1
-        constexpr int J = decltype(j_)::value, K = decltype(k_)::value;
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb) {
-            const i32x6 b6 = qp[rb][K][J];
-            const i32x8 b8 = {b6[0], b6[1], b6[2], b6[3], b6[4], b6[5], 0, 0};
-            sn[rb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a4, b8, sn[rb], 4, 2, 0, 0x7f, K, qp_scale[rb]);
-        }
-    };
-    auto score_fp4 = [&](auto j_, const uint32_t (&kw)[WPL], f32x16 (&sn)[kRB]) {
-        const i32x8 a4 = fp4_operand(j_, kw);
-        static_for<4>([&](auto k_) { fp4_mfma(j_, k_, a4, sn); });
-    };
-    // The same MFMAs with the score tile in vector registers (kVs).  The compiler keeps every MFMA result of this
-    // kernel in accumulation registers, from where each score would have to be copied before the vector ALU can
-    // touch it; written out, the instruction takes a vector-register tuple as C and D.  What the compiler no longer
-    // sees it no longer guards, so the wait states the hardware asks for are placed here, as the compiler places them
-    // for MFMAs of its own: two between a vector write of an operand and the MFMA that reads it (`fresh`: the A
-    // operand has just been made), and twelve between the last MFMA of a chain and the first vector instruction
-    // that reads the tile (KVQ_SCORE_TILE_READY).  Dependent MFMAs on one tile need none.
-    int f4_scale_one = 0x7f;
-    asm volatile("" : "+v"(f4_scale_one));
-    auto fp4_operand4 = [&](auto j_, const uint32_t (&kw)[WPL]) {
-        constexpr int J = decltype(j_)::value;
-        const uint32_t w0 = kw[(2 * J) % WPL], w1 = kw[(2 * J + 1) % WPL];
-        return i32x4{(int)(w0 & f4_mask), (int)((w0 >> 2) & f4_mask), (int)(w1 & f4_mask), (int)((w1 >> 2) & f4_mask)};
-    };
-    auto fp4_mfma_v = [&](auto j_, auto k_, auto fresh_, const i32x4 &a4, f32x16 &s, int rb) {
-        constexpr int J = decltype(j_)::value, K = decltype(k_)::value;
-        constexpr bool FRESH = decltype(fresh_)::value != 0;
-        const i32x6 b6 = qp[rb][K][J];
-        const int sb = qp_scale[rb];
-        // (the accumulation registers hold the output tile and all but two of the sixteen piece operands; those two
-        // stay in vector registers, which leaves the register allocator a few accumulation registers)
-#define KVQ_FP4_MFMA_V(NOP, SEL)                                                                                      \
-        {                                                                                                             \
-            if constexpr (K == 3 && J == 1)                                                                           \
-                asm(NOP "v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:4 blgp:2"           \
-                    : "+v"(s) : "v"(a4), "v"(b6), "v"(f4_scale_one), "v"(sb));                                        \
-            else                                                                                                      \
-                asm(NOP "v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:4 blgp:2"           \
-                    : "+v"(s) : "v"(a4), "a"(b6), "v"(f4_scale_one), "v"(sb));                                        \
-        }
-        if constexpr (K == 0 && FRESH) KVQ_FP4_MFMA_V("s_nop 1\n\t", "op_sel_hi:[0,0,0]")
-        if constexpr (K == 0 && !FRESH) KVQ_FP4_MFMA_V("", "op_sel_hi:[0,0,0]")
-        if constexpr (K == 1) KVQ_FP4_MFMA_V("", "op_sel:[0,1,0] op_sel_hi:[0,0,0]")
-        if constexpr (K == 2) KVQ_FP4_MFMA_V("", "op_sel_hi:[0,1,0]")
-        if constexpr (K == 3) KVQ_FP4_MFMA_V("", "op_sel:[0,1,0] op_sel_hi:[0,1,0]")
-#undef KVQ_FP4_MFMA_V
-    };
-    // first MFMA of a score tile: the constant terms, C = 0
-    auto const_mfma_v = [&](f32x16 &s, const u32x4 &cop, const u32x4 &rop) {
-        asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(cop), "v"(rop));
-    };
-    // every vector read of the tile goes through here: NOP completes the twelve wait states after the last MFMA
-#define KVQ_SCORE_TILE_READY(NOP, S) asm volatile(NOP : "+v"((S)[0]), "+v"((S)[kRB - 1]))
-
-    // FP8 low part: B operands of the two 64-channel MFMAs per 32-row block, and the rows' scale bytes
-    i32x8 lo8[kRB][2];
-    int lo_scale[kRB];
-    if constexpr (kLoFp8) {
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb) {
-            const uint32_t *src = q_stage + (wave * kRowsPerWave + 32 * rb + n) * kQRowWords + 8 * hh;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const u32x4 w0 = *reinterpret_cast<const u32x4 *>(src + 16 * j);
-                const u32x4 w1 = *reinterpret_cast<const u32x4 *>(src + 16 * j + 4);
-                lo8[rb][j] = i32x8{(int)w0.x, (int)w0.y, (int)w0.z, (int)w0.w, (int)w1.x, (int)w1.y, (int)w1.z, (int)w1.w};
-                asm volatile("" : "+a"(lo8[rb][j]));
-            }
-            lo_scale[rb] = __float_as_int(row_scal[4 * (wave * kRowsPerWave + 32 * rb + n) + 3]);
-        }
-    }
-    // Low-part MFMAs of 64 channels (key words 2 J and 2 J + 1): the codes become FP8 values 8 + code, four to
-    // a register, in the byte order the low operand was written in.
-    // (mask in a scalar, base in a vector register: the form v_and_or_b32 can encode)
-    uint32_t f8_mask = 0x03030303u, f8_base = 0x50505050u;
-    asm volatile("" : "+s"(f8_mask));
-    asm volatile("" : "+v"(f8_base));
-    auto low_part_fp8 = [&](auto j_, const uint32_t (&kw)[WPL], f32x16 (&sn)[kRB]) {
-        constexpr int J = decltype(j_)::value;
-        i32x8 a8;
-#pragma unroll
-        for (int r8 = 0; r8 < 8; ++r8) {
-            const uint32_t w = kw[(2 * J + (r8 >> 2)) % WPL];
-            const uint32_t sh = w >> (2 * (r8 & 3));   // no shift for the first code; w >> 2 is shared with the f16 unpacking
-            a8[r8] = (int)((sh & f8_mask) | f8_base);
-        }
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb)
-            sn[rb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, lo8[rb][J], sn[rb], 0, 0, 0, 0x7f, 0, lo_scale[rb]);
-    };
-    constexpr int kLoRes = kLoF16 ? KVQ_Q_LOW_RESIDENT_SLABS : 0;
-    u32x4 lo_res[kRB][kLoRes > 0 ? kLoRes : 1];
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-        for (int s = 0; s < kLoRes; ++s) {
-            lo_res[rb][s] = *reinterpret_cast<const u32x4 *>(q_stage + lo_off + 32 * rb * kQRowWords + 8 * s);
-            asm volatile("" : "+a"(lo_res[rb][s]));
-        }
-
-    f32x16 o[4][kRB];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[b][rb][v] = 0.0f;
-    // Keeps the 128 output accumulators in accumulation registers at the points where the fast loops
-    // are entered, so that the loops carry them there instead of copying them around.
-    auto pin_accumulators = [&]() {
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int rb = 0; rb < kRB; ++rb) asm volatile("" : "+a"(o[b][rb]));
-    };
-    float m_ref[kRB] = {};              // reference maximum (log2 domain); set by the first tile
-    float l_s[kRB] = {}, l_r[kRB] = {}, tau[kRB] = {};
-    bool first = true;                  // no tile has set the reference yet
-
-    // Leaves the fast loops: move the reference of the rows whose pending tile maximum `tmax` (relative
-    // to the old reference) is too large, and rescale what has been accumulated so far.
-    auto move_reference = [&](float (&e)[kRB][16], const float (&tmax)[kRB]) {
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb) {
-            const bool mv = first || tmax[rb] > kRescaleThreshold;
-            const float delta = mv ? tmax[rb] : 0.0f;
-            const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta);
-            m_ref[rb] += delta;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) e[rb][v] -= delta;
-            l_s[rb] *= alpha;
-            l_r[rb] *= alpha;
-            tau[rb] *= alpha;
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[b][rb][v] *= alpha;
-        }
-        first = false;
-        pin_accumulators();
-    };
-
-    auto over_threshold = [&](const float (&tmax)[kRB]) {
-        bool over = false;
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb) over = over || tmax[rb] > kRescaleThreshold;
-        return over;
-    };
-
-    // The query preparation once more, for one block of a per-channel cache (the operands above are replaced):
-    // ch_step, ch_zero are the steps and zero-points of the rotated channels of that block.
-    auto reprepare = [&](const float *ch_step, const float *ch_zero) {
-    if constexpr (PERCH) {
+    } else {
     {
         const int prow = tid / kPrepLanes, ppart = tid % kPrepLanes;
         int64_t row = (int64_t)rblk * kRowsPerBlock + prow;
@@ -690,54 +418,6 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
                 qop[rb][s] = *reinterpret_cast<const u32x4 *>(hsrc + 32 * rb * kQRowWords + 8 * s);
         __syncthreads();
         float ssum = 0.0f, ssum_w = 0.0f;   // sum of q~ (true scale), sum of the weighted operand values
-        if constexpr (kLoFp8) {
-            static_assert(!kLoFp8 || kPrepLanes == 1, "one lane prepares a whole row");
-            // Low parts at true scale (the weight 4^g of the high operand taken out again: exact), their
-            // largest magnitude, and from it the row's power-of-two scale: the largest low part lands in
-            // [128, 256), inside the E4M3 range.
-            float lo_t[kPrepCh], mx = 0.0f;
-#pragma unroll
-            for (int c = 0; c < kPrepCh; c += 2) {
-                const uint32_t hi = pack_f16(x[c], x[c + 1]);
-                const float wgt = 1.0f / (float)(1 << (Unpack<BITS>::kClassBits * key_channel_class<BITS>(c)));   // both channels share a class
-                lo_t[c] = (x[c] - f16_lo(hi)) * wgt;
-                lo_t[c + 1] = (x[c + 1] - f16_hi(hi)) * wgt;
-                mx = fmaxf(mx, fmaxf(fabsf(lo_t[c]), fabsf(lo_t[c + 1])));
-                ssum_w += f16_lo(hi) + f16_hi(hi);
-                if constexpr (PERCH) ssum += (f16_lo(hi) * ch_zero[c] + f16_hi(hi) * ch_zero[c + 1]) * wgt;
-                else ssum += (f16_lo(hi) + f16_hi(hi)) * wgt;
-            }
-            const int ex = mx > 0.0f ? (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127 - 7 : 0;   // floor(log2 mx) - 7
-            const float down = __uint_as_float((uint32_t)(127 - ex) << 23), up = __uint_as_float((uint32_t)(127 + ex) << 23);
-            // Operand order: MFMA j (channels of key words 2 j, 2 j + 1), lane half hh, register r8, byte b hold
-            // the channel whose code the key unpacking puts into the same byte.
-#pragma unroll
-            for (int w = 0; w < 32; ++w) {
-                const int j = w >> 4, hw = (w >> 3) & 1, r8 = w & 7;
-                float v[4];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int slab = 2 * (2 * j + (r8 >> 2)) + (b & 1);
-                    v[b] = lo_t[16 * slab + 8 * hw + 2 * (r8 & 3) + (b >> 1)] * down;
-                }
-                int word = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], 0, false);
-                word = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], word, true);
-                dst[w] = (uint32_t)word;
-                float dec = 0.0f, dec_z = 0.0f;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const float d8 = e4m3_to_float((uint8_t)((uint32_t)word >> (8 * b)));
-                    dec += d8;
-                    if constexpr (PERCH) {
-                        const int slab = 2 * (2 * j + (r8 >> 2)) + (b & 1);
-                        dec_z = fmaf(d8, ch_zero[16 * slab + 8 * hw + 2 * (r8 & 3) + (b >> 1)], dec_z);
-                    }
-                }
-                ssum += (PERCH ? dec_z : dec) * up;      // the sums follow the operands the MFMAs will see
-                ssum_w += 2.0f * (dec * up);   // FP8 key values are 8 + code, twice the BASE the constant term takes off
-            }
-            row_scal[4 * prow + 3] = __int_as_float(127 + ex);
-        } else {
 #pragma unroll
         for (int i = 0; i < kPrepCh / 8; ++i) {
             uint32_t lo[4];
@@ -765,7 +445,6 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             w.x = lo[0]; w.y = lo[1]; w.z = lo[2]; w.w = lo[3];
             *reinterpret_cast<u32x4 *>(dst + 4 * i) = w;
         }
-        }
         if constexpr (kPrepLanes == 2) {
             ssum += __shfl_xor(ssum, 1);
             ssum_w += __shfl_xor(ssum_w, 1);
@@ -777,54 +456,14 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
         }
     }
     __syncthreads();
-    // B operand of the constant-term MFMA, per 32-row block.  The raw score is sum_c (q~_c 4^g) (BASE +
-    // 4^-g code_c) = q~ . code + BASE * W with W the sum of the weighted operand values, so what has to
-    // come off is z * S + BASE * W (S = sum_c q~_c).  Lane half 0 multiplies the key's -z pieces and the
-    // mask bias, lane half 1 the key's scale pieces and the constant -BASE:
-    //   hh = 0: [S_h, S_m, S_l, S_h, S_m, S_l, 1, 0]     S in three bf16 pieces
-    //   hh = 1: [N_h, N_l, N_h, N_l, W_h, W_m, W_l, 0]   N = -nu' in two pieces, W in three
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-        const float *rs = row_scal + 4 * (wave * kRowsPerWave + 32 * rb + n);
-        const float ssum = rs[0], wsum = rs[1], nnu = rs[2];
-        const uint16_t s_h = bf16_bits(ssum);
-        const float r1 = ssum - bf16_val(s_h);
-        const uint16_t s_m = bf16_bits(r1);
-        const uint16_t s_l = bf16_bits(r1 - bf16_val(s_m));
-        const uint16_t w_h = bf16_bits(wsum);
-        const float r2 = wsum - bf16_val(w_h);
-        const uint16_t w_m = bf16_bits(r2);
-        const uint16_t w_l = bf16_bits(r2 - bf16_val(w_m));
-        const uint16_t n_h = bf16_bits(nnu);
-        const uint16_t n_l = bf16_bits(nnu - bf16_val(n_h));
-        const uint32_t one = 0x3f80u;
-        u32x4 w0, w1;
-        w0.x = s_h | ((uint32_t)s_m << 16); w0.y = s_l | ((uint32_t)s_h << 16);
-        w0.z = s_m | ((uint32_t)s_l << 16); w0.w = one | (one << 16);
-        w1.x = n_h | ((uint32_t)n_l << 16); w1.y = w1.x;
-        w1.z = w_h | ((uint32_t)w_m << 16); w1.w = w_l | (one << 16);
-        rowop[rb] = hh ? w1 : w0;
-    }
     // The 64 registers of query operands live in accumulation registers (MFMA reads them from there
     // directly), which leaves the vector registers to the score tile in flight.
 #pragma unroll
-    for (int rb = 0; rb < kRB; ++rb)
+    for (int rb = 0; rb < kRB; ++rb) {
+        const float *rs = row_scal + 4 * (wave * kRowsPerWave + 32 * rb + n);
+        rowop[rb] = row_operand(rs[0], rs[1], rs[2]);
 #pragma unroll
         for (int s = 0; s < 8; ++s) asm volatile("" : "+a"(qop[rb][s]));
-
-    if constexpr (kLoFp8) {
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb) {
-            const uint32_t *src = q_stage + (wave * kRowsPerWave + 32 * rb + n) * kQRowWords + 8 * hh;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const u32x4 w0 = *reinterpret_cast<const u32x4 *>(src + 16 * j);
-                const u32x4 w1 = *reinterpret_cast<const u32x4 *>(src + 16 * j + 4);
-                lo8[rb][j] = i32x8{(int)w0.x, (int)w0.y, (int)w0.z, (int)w0.w, (int)w1.x, (int)w1.y, (int)w1.z, (int)w1.w};
-                asm volatile("" : "+a"(lo8[rb][j]));
-            }
-            lo_scale[rb] = __float_as_int(row_scal[4 * (wave * kRowsPerWave + 32 * rb + n) + 3]);
-        }
     }
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb)
@@ -834,6 +473,123 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             asm volatile("" : "+a"(lo_res[rb][s]));
         }
     }
+    };
+    if constexpr (!PERCH) prepare(nullptr, nullptr);
+    // 2-bit codes are FP4 (E2M1) values as they stand, 0, 0.5, 1, 1.5: a packed word is two operand registers, the
+    // even and the odd fields, each in the low half of a nibble.  Four pieces x two 64-channel MFMAs per row block,
+    // FP4 x FP6 at twice the FP8 rate; opsel picks the piece's byte of the row's scale word.
+    uint32_t f4_mask = 0x33333333u;
+    asm volatile("" : "+s"(f4_mask));
+    auto fp4_operand = [&](auto j_, const uint32_t (&kw)[WPL]) {   // key words 2 J, 2 J + 1
+        constexpr int J = decltype(j_)::value;
+        const uint32_t w0 = kw[(2 * J) % WPL], w1 = kw[(2 * J + 1) % WPL];
+        return i32x8{(int)(w0 & f4_mask), (int)((w0 >> 2) & f4_mask), (int)(w1 & f4_mask), (int)((w1 >> 2) & f4_mask), 0, 0, 0, 0};
+    };
+    auto fp4_mfma = [&](auto j_, auto k_, const i32x8 &a4, f32x16 (&sn)[kRB]) {   // piece K against key words 2 J, 2 J + 1
+        constexpr int J = decltype(j_)::value, K = decltype(k_)::value;
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) {
+            const i32x6 b6 = qp[rb][K][J];
+            const i32x8 b8 = {b6[0], b6[1], b6[2], b6[3], b6[4], b6[5], 0, 0};
+            sn[rb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a4, b8, sn[rb], 4, 2, 0, 0x7f, K, qp_scale[rb]);
+        }
+    };
+    auto score_fp4 = [&](auto j_, const uint32_t (&kw)[WPL], f32x16 (&sn)[kRB]) {
+        const i32x8 a4 = fp4_operand(j_, kw);
+        static_for<4>([&](auto k_) { fp4_mfma(j_, k_, a4, sn); });
+    };
+    // The same MFMAs with the score tile in vector registers (kVs).  The compiler keeps every MFMA result of this
+    // kernel in accumulation registers, from where each score would have to be copied before the vector ALU can
+    // touch it; written out, the instruction takes a vector-register tuple as C and D.  What the compiler no longer
+    // sees it no longer guards, so the wait states the hardware asks for are placed here, as the compiler places them
+    // for MFMAs of its own: two between a vector write of an operand and the MFMA that reads it (`fresh`: the A
+    // operand has just been made), and twelve between the last MFMA of a chain and the first vector instruction
+    // that reads the tile (KVQ_SCORE_TILE_READY).  Dependent MFMAs on one tile need none.
+    int f4_scale_one = 0x7f;
+    asm volatile("" : "+v"(f4_scale_one));
+    auto fp4_operand4 = [&](auto j_, const uint32_t (&kw)[WPL]) {
+        constexpr int J = decltype(j_)::value;
+        const uint32_t w0 = kw[(2 * J) % WPL], w1 = kw[(2 * J + 1) % WPL];
+        return i32x4{(int)(w0 & f4_mask), (int)((w0 >> 2) & f4_mask), (int)(w1 & f4_mask), (int)((w1 >> 2) & f4_mask)};
+    };
+    auto fp4_mfma_v = [&](auto j_, auto k_, auto fresh_, const i32x4 &a4, f32x16 &s, int rb) {
+        constexpr int J = decltype(j_)::value, K = decltype(k_)::value;
+        constexpr bool FRESH = decltype(fresh_)::value != 0;
+        const i32x6 b6 = qp[rb][K][J];
+        const int sb = qp_scale[rb];
+        // (the accumulation registers hold the output tile and all but two of the sixteen piece operands; those two
+        // stay in vector registers, which leaves the register allocator a few accumulation registers)
+#define KVQ_FP4_MFMA_V(NOP, SEL)                                                                                      \
+        {                                                                                                             \
+            if constexpr (K == 3 && J == 1)                                                                           \
+                asm(NOP "v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:4 blgp:2"           \
+                    : "+v"(s) : "v"(a4), "v"(b6), "v"(f4_scale_one), "v"(sb));                                        \
+            else                                                                                                      \
+                asm(NOP "v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:4 blgp:2"           \
+                    : "+v"(s) : "v"(a4), "a"(b6), "v"(f4_scale_one), "v"(sb));                                        \
+        }
+        if constexpr (K == 0 && FRESH) KVQ_FP4_MFMA_V("s_nop 1\n\t", "op_sel_hi:[0,0,0]")
+        if constexpr (K == 0 && !FRESH) KVQ_FP4_MFMA_V("", "op_sel_hi:[0,0,0]")
+        if constexpr (K == 1) KVQ_FP4_MFMA_V("", "op_sel:[0,1,0] op_sel_hi:[0,0,0]")
+        if constexpr (K == 2) KVQ_FP4_MFMA_V("", "op_sel_hi:[0,1,0]")
+        if constexpr (K == 3) KVQ_FP4_MFMA_V("", "op_sel:[0,1,0] op_sel_hi:[0,1,0]")
+#undef KVQ_FP4_MFMA_V
+    };
+    // first MFMA of a score tile: the constant terms, C = 0
+    auto const_mfma_v = [&](auto fresh_, f32x16 &s, const u32x4 &cop, const u32x4 &rop) {
+        if constexpr (decltype(fresh_)::value) asm("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(cop), "v"(rop));
+        else asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(cop), "v"(rop));
+    };
+    // every vector read of the tile goes through here: NOP completes the twelve wait states after the last MFMA
+#define KVQ_SCORE_TILE_READY(NOP, S) asm volatile(NOP : "+v"((S)[0]), "+v"((S)[kRB - 1]))
+
+    f32x16 o[4][kRB];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[b][rb][v] = 0.0f;
+    // Keeps the 128 output accumulators in accumulation registers at the points where the fast loops
+    // are entered, so that the loops carry them there instead of copying them around.
+    auto pin_accumulators = [&]() {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int rb = 0; rb < kRB; ++rb) asm volatile("" : "+a"(o[b][rb]));
+    };
+    float m_ref[kRB] = {};              // reference maximum (log2 domain); set by the first tile
+    float l_s[kRB] = {}, l_r[kRB] = {}, tau[kRB] = {};
+    bool first = true;                  // no tile has set the reference yet
+
+    // Leaves the fast loops: move the reference of the rows whose pending tile maximum `tmax` (relative
+    // to the old reference) is too large, and rescale what has been accumulated so far.
+    auto move_reference = [&](float (&e)[kRB][16], const float (&tmax)[kRB]) {
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) {
+            const bool mv = first || tmax[rb] > kRescaleThreshold;
+            const float delta = mv ? tmax[rb] : 0.0f;
+            const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta);
+            m_ref[rb] += delta;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) e[rb][v] -= delta;
+            l_s[rb] *= alpha;
+            l_r[rb] *= alpha;
+            tau[rb] *= alpha;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[b][rb][v] *= alpha;
+        }
+        first = false;
+        pin_accumulators();
+    };
+
+    auto over_threshold = [&](const float (&tmax)[kRB]) {
+        bool over = false;
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) over = over || tmax[rb] > kRescaleThreshold;
+        return over;
     };
 
     // ---------------------------------------------------------------------- cached keys ----
@@ -849,8 +605,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             if (cs >= ce) continue;
             phys_first = (int)((a.phys_tile_first + (cs / kTileTokens - a.cache_start / kTileTokens)) % cv.cap_tiles);
             __syncthreads();   // every wave has left the previous block's tiles and staging rows
-            reprepare(cv.kc_scale + ((int64_t)kb.slot * cv.num_heads + head) * D,
-                      cv.kc_zero + ((int64_t)kb.slot * cv.num_heads + head) * D);
+            prepare(cv.kc_scale + ((int64_t)kb.slot * cv.num_heads + head) * D,
+                    cv.kc_zero + ((int64_t)kb.slot * cv.num_heads + head) * D);
         }
         const int64_t t_first = cs / kTileTokens, t_last = (ce - 1) / kTileTokens;
         const int n_tiles = (int)(t_last - t_first + 1);
@@ -1025,7 +781,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             const u32x4 cop = *reinterpret_cast<const u32x4 *>(buf + St::kCop + (tl * 64 + lane) * 4);
             if constexpr (kVs) {
 #pragma unroll
-                for (int rb = 0; rb < kRB; ++rb) const_mfma_v(sn[rb], cop, rowop[rb]);
+                for (int rb = 0; rb < kRB; ++rb) const_mfma_v(IntC<1>{}, sn[rb], cop, rowop[rb]);
                 static_for<2>([&](auto j_) {
                     const i32x4 a4 = fp4_operand4(j_, kw);
                     static_for<4>([&](auto k_) {
@@ -1068,10 +824,6 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
                     }
                 }
             });
-            if constexpr (kLoFp8) {
-                low_part_fp8(IntC<0>{}, kw, sn);
-                low_part_fp8(IntC<1>{}, kw, sn);
-            }
         };
         // e = scale_i * raw - reference; returns the tile maximum of e per row block.
         auto finalize_tile = [&](int t, const f32x16 (&sn)[kRB], float (&e)[kRB][16], float (&tmax)[kRB]) {
@@ -1223,7 +975,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             for (int v = 0; v < 16; ++v) zero[v] = 0.0f;
 #pragma unroll
             for (int rb = 0; rb < kRB; ++rb) {
-                if constexpr (kVs) const_mfma_v(sn[rb], pf.cop, rowop[rb]);
+                if constexpr (kVs) const_mfma_v(IntC<0>{}, sn[rb], pf.cop, rowop[rb]);
                 else sn[rb] = mfma_bf16(pf.cop, rowop[rb], zero);
             }
             float lsum[kRB] = {}, tacc[kRB] = {};
@@ -1290,7 +1042,6 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
                             else sn[rb] = mfma_f16(kop_prev, lo_cur[rb], sn[rb]);
                         }
                     }
-                    if constexpr (kLoFp8 && SLAB == 4) low_part_fp8(IntC<0>{}, pf.kw, sn);   // key words 0, 1: slabs 0..3
                     exp_chunk(IntC<SLAB - 1>{});
                 }
                 if constexpr (kLoF16) {
@@ -1309,7 +1060,6 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
                     else sn[rb] = mfma_f16(kop_prev, lo_cur[rb], sn[rb]);
                 }
             }
-            if constexpr (kLoFp8) low_part_fp8(IntC<1>{}, pf.kw, sn);
             exp_chunk(IntC<7>{});
             // Four exponentials and two conversions have been issued since the last score MFMA: six more wait
             // states make the twelve that a vector read of its result needs.
