@@ -7,7 +7,7 @@ namespace {
 
 template <int DIM, typename T> __global__ __launch_bounds__(kMergeThreads) void attention_merge_kernel(AttentionArgs a, SplitArgs sp)
 {
-    merge_rows<DIM, T>(a, sp);
+    merge_rows<DIM, T, false>(a, sp);
 }
 
 }  // namespace

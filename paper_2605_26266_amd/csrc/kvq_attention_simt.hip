@@ -295,10 +295,7 @@ constexpr int kResidentWorkgroups = 2048;   // two waves each; the registers of 
 template <int BITS> __global__ __launch_bounds__(kMergeThreads) void attention_merge_or_vector_kernel(AttentionArgs a, SplitArgs sp, unsigned merge)
 {
     static_assert(kMergeThreads == 128, "a thread per channel of head_dim 128");
-    if (!cache_flagged(a.status)) {
-        if (blockIdx.x < merge) merge_rows<128, uint16_t>(a, sp);
-        return;
-    }
+    if (blockIdx.x < merge ? merge_rows<128, uint16_t, true>(a, sp) : !cache_flagged(a.status)) return;
     const int64_t rows = a.m * a.cv.num_heads * a.q_per_kv;
     for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) attend_row<128, BITS, uint16_t>(a, (int)(i / a.m), i % a.m);
 }
