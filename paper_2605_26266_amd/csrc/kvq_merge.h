@@ -19,7 +19,8 @@ template <int DIM> inline unsigned merge_workgroups(const SplitArgs &sp)
 // CHUNK pieces' references, sums and outputs are asked for together; more pieces, CHUNK at a time under a running maximum.
 // Looking for the maximum over all pieces first and for the outputs then is two waits one behind the other, each about as long as
 // the transfer: calls of 16 to 23 us whose fp32 kernel is split took 1 to 3 us more (17.1 -> 14.1, 17.7 -> 15.7, 22.7 -> 21.4).
-// 64 pieces of one row block are the other end, 20.5 -> 20.7 us; 16 at a time were 23.1, two times 8 in flight 20.7.
+// One token behind 8192 keys, with more than 8 pieces, is the other end: 20.5 -> 20.7 us; 16 at a time were 23.1, two times 8 in
+// flight 20.7.
 template <int DIM, typename T, bool GATED, int CHUNK> __device__ inline bool merge_pieces(const AttentionArgs &a, const SplitArgs &sp)
 {
     const int lane = threadIdx.x & 63, g = 2 * (int)(blockIdx.x & 1) + (int)(threadIdx.x >> 6);
