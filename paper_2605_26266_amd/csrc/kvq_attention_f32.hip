@@ -334,8 +334,11 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
 
     // ---- query in pieces, once for the eight waves: rotated for the cached keys, as it is for current ones in fp32
     uint32_t *const pieces = reinterpret_cast<uint32_t *>(lds);
-    // A query so small that its third pieces may be lost, so large that sums of pieces may overflow, or not finite: fp32 products.
-    auto in_range = [](float sum) { return sum == 0.0f || (sum >= 0x1p-90f && sum <= 0x1p100f); };
+    // Operands so small that their third pieces may be lost, so large that sums of pieces may overflow, or not finite: fp32 products.
+    // Queries and current keys meet each other: below 2^63 each, where no product of pieces overflows that the score itself does not
+    // (high times middle piece may be +inf beside -inf of the high ones).
+    constexpr float kTop = 0x1p100f, kTopFactor = 0x1p63f;
+    auto in_range = [](float sum, float top) { return sum == 0.0f || (sum >= 0x1p-90f && sum <= top); };
     bool unfit = false;
     if (x0 < tc || !kBf16) {               // (the same for all waves)
         if (has_octet) {
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                     y[e] *= c_log;
                     sum += fabsf(y[e]);
                 }
-                unfit = !in_range(sum);
+                unfit = !in_range(sum, kTopFactor);
                 leave_pieces(pieces + L::kPlain);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) y[e] = x8[e];
@@ -391,7 +394,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             for (int p = 0; p < 2; ++p)
                 *reinterpret_cast<float4 *>(lds + L::kQuery + 4 * (((g8 >> 1) * 2 + p) * 64 + 32 * (g8 & 1) + r8)) =
                     float4{y[4 * p], y[4 * p + 1], y[4 * p + 2], y[4 * p + 3]};
-            unfit = unfit || !in_range(sum);
+            unfit = unfit || !in_range(sum, kTop);
         }
         const bool any_unfit = __any(unfit);
         if (lane == 0) pieces[L::kFlags + wave] = any_unfit;
@@ -840,7 +843,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                 }
 #pragma unroll
                 for (int v = 0; v < 16; ++v) s[v] -= base;
-                if (__builtin_expect(unfit || !__all(in_range(size)), 0)) fp32_scores(s);
+                if (__builtin_expect(unfit || !__all(in_range(size, kTopFactor)), 0)) fp32_scores(s);
             }
             if (a.causal || key0 + kTileTokens > a.n_cur) {
 #pragma unroll
@@ -910,7 +913,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                         float size = 0.0f;
 #pragma unroll
                         for (int e = 0; e < 8; ++e) size += fabsf(x8[b][e]);
-                        fits = fits && in_range(size);
+                        fits = fits && in_range(size, kTop);
                     }
                     if (__builtin_expect(!__all(fits), 0)) {
                         fits = true;
@@ -926,7 +929,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                                 }
                                 size += fabsf(x8[b][e]);
                             }
-                            fits = fits && in_range(size);
+                            fits = fits && in_range(size, kTop);
                         }
                         finite = finite && __all(all);
                     }

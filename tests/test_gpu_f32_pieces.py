@@ -93,3 +93,13 @@ def test_not_finite(fmt, value, where):
         ok = torch.isfinite(b)
         assert torch.equal(torch.isneginf(a), torch.isneginf(b)) and ok.any()
         torch.testing.assert_close(a[ok], b[ok], rtol=2.0 ** -7 if a.dtype == torch.bfloat16 else 1e-4, atol=1e-2 if a.dtype == torch.bfloat16 else 1e-5)
+
+
+@pytest.mark.parametrize("fmt", [f for f in FORMATS if f[2] == B.KVQ_FP32])
+def test_products_beyond_the_range(fmt):
+    """A key whose score is -infinity in fp32 although query and key are ordinary numbers (1.1e21 .. and -1.7e21 in one channel)."""
+    def poison(q, k, v):
+        q[:, :, 7] = k[:, :, 7] = 0.0
+        q[5:25, :, 7], k[3, :, 7] = 1.1e21 * 1.03 ** torch.arange(20, device=DEV)[:, None], -1.7e21
+
+    _close(*_attend(fmt, 40, 70, 0, poison=poison)[1:])
