@@ -176,7 +176,7 @@ template <int DIM, int G, bool BF16> struct F32Lds {
     // in different banks.  A wave that has cached and current tiles leaves two of them, the first while others still work.
     static constexpr int kQuad = 256 + 16, kSlot = DIM / 8 * kQuad, kOut = kFWaves * kSlot;
     static constexpr int kSlot8 = kWork > kOut ? kWork : kOut;
-    static constexpr int kRed = kSlot8 + kSlot, kWords = kRed + (kFWaves + 1) * 32 * 3;
+    static constexpr int kRed = kSlot8 + kSlot, kWords = kRed + (kFWaves + 1) * 32 * 4;
 };
 
 // GROUP: channels per (scale, zero-point); DIM and fp32 pairs for KVQ_META_FP32, FP8: E4M3 / BF16 encodings.
@@ -410,18 +410,25 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[b][v] = 0.0f;
-    // Scores are taken relative to m_ref, which moves when a row goes beyond it by more than a factor of 2^8 (weights and sums
-    // are fp32: nothing depends on where it lies).
-    float m_ref = -INFINITY, base = 0.0f, limit = -INFINITY, l_s = 0.0f, l_r = 0.0f, tau = 0.0f;
+    // Scores are taken relative to m_ref, which moves when a row goes beyond it by more than a factor of 2^slack (weights and sums
+    // are fp32: where it lies matters only to sums that come near the end of the range).  `above`: the row's largest score less m_ref.
+    float m_ref = -INFINITY, base = 0.0f, limit = -INFINITY, above = -INFINITY, slack = 8.0f, l_s = 0.0f, l_r = 0.0f, tau = 0.0f;
 
-    // s: scores in log2 units less `base` (-inf: key not seen) -> weights
-    auto weigh = [&](f32x16 &s, float &l) {
+    // s: scores in log2 units less `base` (-inf: key not seen) -> weights.  large: the tile's values lie so high that sums with
+    // weights up to 2^slack might leave the range of fp32; from here on weights stay below 1.
+    auto weigh = [&](f32x16 &s, float &l, bool large) {
+        if (__builtin_expect(large, 0)) {
+            slack = 0.0f;
+            limit = fminf(limit, 0.0f);
+        }
         float mx = s[0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
         mx = fmaxf(mx, other_half(mx));
-        if (__any(mx > limit)) {
-            const float by = mx > limit ? mx : 0.0f, alpha = m_ref == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(-by);
+        above = fmaxf(above, mx);
+        if (__any(above > limit)) {
+            const bool moves = above > limit;
+            const float to = moves ? base + above : base, by = to - base, alpha = m_ref == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(-by);
             l_s *= alpha;
             l_r *= alpha;
             tau *= alpha;
@@ -429,9 +436,10 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[b][v] *= alpha;
-            if (mx > limit) {
-                m_ref = base = base + by;
-                limit = 8.0f;
+            if (moves) {
+                m_ref = base = to;
+                limit = slack;
+                above = 0.0f;
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[v] -= by;
@@ -481,8 +489,10 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             }
             // What the 16-bit operands hold exactly: (code - zero) up to 256; times a step of four significant bits, up to 15.
             // (kTau: values are code - 1, the middle of their range, and what is left of the zero-points goes into tau.)
+            // Steps whose products with weights may leave the range at either end are not among them.
             constexpr float kMid = FP8 ? 0.5f * (float)MASK : 0.0f, kFar = FP8 ? 15.0f - 0.5f * (float)MASK : 240.0f;
-            bool fits_k = !unfit, fits_v = FP8 || !(vs[0] < 0x1p-80f && vs[0] > 0.0f);
+            bool fits_k = !unfit, fits_v = FP8 || vs[0] == 0.0f || (vs[0] >= 0x1p-80f && vs[0] <= 0x1p80f);
+            if (kTau) fits_v = fits_v && fabsf(vz[0]) * vs[0] <= kTop;
 #pragma unroll
             for (int j = 0; j < G; ++j) {
                 fits_k = fits_k && fabsf(kz[j] - kMid) <= kFar;
@@ -616,7 +626,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                     s[v] = rel >= 0 && rel < a.cache_len ? s[v] : -INFINITY;
                 }
             }
-            weigh(s, l_s);
+            weigh(s, l_s, !fits_v);
             if (__builtin_expect(fits_v, 1)) {
                 if constexpr (!FP8) {
 #pragma unroll
@@ -716,14 +726,15 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
         }
     }
     // The output of a wave's cached tiles (in the rotated basis) or current tiles, its maximum and sums, to slot `slot`.
-    float *const red = lds + L::kRed;      // [slot][m, l_s, l_r][row]
+    float *const red = lds + L::kRed;      // [slot][m, l_s, l_r, largest score][row]
     auto leave = [&](int slot) {
         l_s += other_half(l_s);
         l_r += other_half(l_r);
         if (hh == 0) {
-            red[(slot * 3) * 32 + n] = m_ref;
-            red[(slot * 3 + 1) * 32 + n] = l_s;
-            red[(slot * 3 + 2) * 32 + n] = l_r;
+            red[(slot * 4) * 32 + n] = m_ref;
+            red[(slot * 4 + 1) * 32 + n] = l_s;
+            red[(slot * 4 + 2) * 32 + n] = l_r;
+            red[(slot * 4 + 3) * 32 + n] = m_ref + above;
         }
         float *const dst = lds + (slot < kFWaves ? slot * L::kSlot : L::kSlot8) + 4 * lane;
 #pragma unroll
@@ -735,9 +746,10 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
 
     // ---- current tiles
     if (x < x_end) {
+        if (!kBf16) slack = 0.0f;     // (fp32 values are asked for behind the weights)
         if (run_start(wave) < tc) {
             leave(kFWaves);
-            m_ref = limit = -INFINITY;
+            m_ref = limit = above = -INFINITY;
             base = l_s = l_r = 0.0f;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -849,28 +861,35 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
 #pragma unroll
                 for (int v = 0; v < 16; ++v) s[v] = key0 + 8 * (v >> 2) + 4 * hh + (v & 3) < visible ? s[v] : -INFINITY;
             }
-            weigh(s, l_r);
             // The rows of a tile share its values, and the weight 0 of a key that a row does not see must not meet an infinity
             // or a NaN: what is not finite goes into the product as 0 and is added below to the rows that see it.
-            bool finite;
+            bool finite = true, large = false;
             if constexpr (kBf16) {
-                typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
-                u16x2 top = {0, 0};
+                auto beyond = [&](int limit) {
+                    typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
+                    u16x2 top = {0, 0};
 #pragma unroll
-                for (int i = 0; i < kVPieces; ++i) {
-                    const uint32_t ws[4] = {v_rows[i].x, v_rows[i].y, v_rows[i].z, v_rows[i].w};
+                    for (int i = 0; i < kVPieces; ++i) {
+                        const uint32_t ws[4] = {v_rows[i].x, v_rows[i].y, v_rows[i].z, v_rows[i].w};
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, ws[j] & 0x7fff7fffu));
-                }
-                finite = !__any(top.x >= 0x7f80 || top.y >= 0x7f80);
-                if (__builtin_expect(!finite, 0)) {
+                        for (int j = 0; j < 4; ++j) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, ws[j] & 0x7fff7fffu));
+                    }
+                    return __any(top.x >= limit || top.y >= limit);
+                };
+                constexpr int kLarge = (127 + 100) << 7;       // 2^100
+                if (__builtin_expect(beyond(kLarge), 0)) {
+                    finite = !beyond(0x7f80);
                     auto only_finite = [](uint32_t w) {
                         return (w & ((w & 0x7f80u) == 0x7f80u ? 0xffff0000u : ~0u)) & ((w & 0x7f800000u) == 0x7f800000u ? 0xffffu : ~0u);
                     };
 #pragma unroll
                     for (int i = 0; i < kVPieces; ++i)
                         v_rows[i] = u32x4{only_finite(v_rows[i].x), only_finite(v_rows[i].y), only_finite(v_rows[i].z), only_finite(v_rows[i].w)};
+                    large = beyond(kLarge);
                 }
+            }
+            weigh(s, l_r, large);
+            if constexpr (kBf16) {
                 // Rows of the tile through LDS: the transposing read hands a lane four tokens of its channel (of 16 lanes, lane
                 // 4 j + c supplies the address of token j, channels 4 c .. 4 c + 3, and lane i receives channel i).
                 uint16_t *const stage = reinterpret_cast<uint16_t *>(lds + L::kStage + wave * L::kStageWave);
@@ -902,7 +921,6 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                 __builtin_amdgcn_wave_barrier();
             } else {
                 if (kAhead) request(1);
-                finite = true;
 #pragma unroll
                 for (int sl = 0; sl < 2; ++sl) {
                     if (!kAhead) request(sl);
@@ -999,15 +1017,15 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
     while (cached < busy && run_start(cached + 1) <= tc) ++cached;
     const bool mixed = cached < busy && run_start(cached) < tc;
     const float *const my_red = red + r8;
-    float top = mixed ? my_red[kFWaves * 96] : -INFINITY;
-    for (int w = 0; w < busy; ++w) top = fmaxf(top, my_red[w * 96]);
+    float top = mixed ? my_red[kFWaves * 128 + 96] : -INFINITY;
+    for (int w = 0; w < busy; ++w) top = fmaxf(top, my_red[w * 128 + 96]);
     l_s = l_r = 0.0f;
     float y[8] = {}, z[8] = {};
     auto add = [&](int slot, float (&sum)[8]) {
         // (a slot without a key that the row sees has m = -inf and l = 0; if all do, or every score is -inf, all weights are 0)
-        const float m = my_red[slot * 96], f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - top);
-        l_s = fmaf(f, my_red[slot * 96 + 32], l_s);
-        l_r = fmaf(f, my_red[slot * 96 + 64], l_r);
+        const float m = my_red[slot * 128], f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - top);
+        l_s = fmaf(f, my_red[slot * 128 + 32], l_s);
+        l_r = fmaf(f, my_red[slot * 128 + 64], l_r);
         const float *const src = lds + (slot < kFWaves ? slot * L::kSlot : L::kSlot8) + g8 * L::kQuad + 4 * r8;
         const float4 c0 = *reinterpret_cast<const float4 *>(src), c1 = *reinterpret_cast<const float4 *>(src + 128);
         if (m == -INFINITY) return;

@@ -103,3 +103,38 @@ def test_products_beyond_the_range(fmt):
         q[5:25, :, 7], k[3, :, 7] = 1.1e21 * 1.03 ** torch.arange(20, device=DEV)[:, None], -1.7e21
 
     _close(*_attend(fmt, 40, 70, 0, poison=poison)[1:])
+
+
+# (E4M3 steps end at 448: no such cached values)
+@pytest.mark.parametrize("large,fmt", [(large, f) for f in FORMATS for large in ("current", "cached", "both")
+                                       if large == "current" or f[3] == B.KVQ_META_FP32])
+def test_large_values_behind_a_late_maximum(fmt, large, monkeypatch):
+    """Values of 2^119 at keys that score 7.5 (log2) above everything before them: what is summed stays within fp32 only where
+    weights are taken relative to the largest score so far, whatever the reference was before."""
+    dim, bits, io, meta, group = fmt
+    monkeypatch.setattr(B, "_workspace", lambda *args: None)       # unsplit: a run of five tiles for each of the eight waves
+    heads, rows, tokens, scale = 2, 33, 1280, 2.0 ** -3
+    dtype = torch.bfloat16 if io == B.KVQ_BF16 else torch.float32
+    # channel 1 rotates into alternating signs, which the codes hold exactly
+    x = torch.zeros((tokens, heads, dim), device=DEV)
+    x[..., 1] = 1e-3
+    x[130::160, :, 1] = 7.5 * math.log(2.0) / scale
+    v = torch.ones((tokens, heads, dim), device=DEV)
+    v[:, :, 1::2] = -1.0
+    v[130::160] *= 2.0 ** 119
+    k, v = x.to(dtype), v.to(dtype)
+    q = torch.zeros((rows, heads, dim), device=DEV)
+    q[..., 1] = 1.0
+    q = q.to(dtype)
+    cache = B.Cache(B.make_desc(heads, dim, bits, tokens, io, group, 1, meta), DEV)
+    cached = 0 if large == "current" else tokens
+    if cached:
+        B.kvq_quantize_append(cache, k, v)
+    cur = (None, None) if large == "cached" else (k, v)
+    got, mass = torch.full_like(q, float("nan")), torch.full((heads, rows), float("nan"), device=DEV)
+    ref, ref_mass = torch.empty_like(got), torch.empty_like(mass)
+    B.kvq_chunk_attention(cache, 0, cached, q, *cur, got, mass, scale, 0)
+    B.kvq_chunk_attention_fp32(cache, 0, cached, q, *cur, ref, ref_mass, scale, 0)
+    torch.cuda.synchronize()
+    assert float(ref.abs().max()) > 2.0 ** 117
+    _close(got.double() * 2.0 ** -119, mass, ref.double() * 2.0 ** -119, ref_mass, 1e-5 if io == B.KVQ_FP32 else 2.0 ** -8)
