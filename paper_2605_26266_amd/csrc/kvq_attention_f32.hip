@@ -168,10 +168,14 @@ __device__ inline void store4(uint16_t *p, float a, float b, float c, float d)
 // waves' maxima and sums.
 template <int DIM, int G, bool BF16> struct F32Lds {
     static constexpr int kPieces = 3 * (DIM / 16) * 256, kQuery = kPieces, kPlain = kQuery + DIM * 32, kCorr = kPlain + (BF16 ? 0 : kPieces), kMeta = kCorr + G * 32, kMetaWave = 3 * G * 32;
-    static constexpr int kFlags = kMeta + kFWaves * kMetaWave, kWeights = kFlags + kFWaves;
+    static constexpr int kFlags = kMeta + kFWaves * kMetaWave, kOwn = kFlags + kFWaves;
     // BF16 value rows of a current tile, 64 bytes longer than the row (four rows and two 16-channel columns fill the banks once)
-    static constexpr int kStageRow = DIM + 32, kStageWave = kTileTokens * kStageRow / 2, kStage = kWeights;
-    static constexpr int kWork = kWeights + kFWaves * (BF16 && kStageWave > 1024 ? kStageWave : 1024);
+    static constexpr int kStageRow = DIM + 32, kStageWave = kTileTokens * kStageRow / 2;
+    // A wave's own area holds its weights or its values: waves need not be at the same kind of tile.
+    static constexpr int kWeightsWave = 16 * 64, kOwnWave = BF16 && kStageWave > kWeightsWave ? kStageWave : kWeightsWave;
+    static constexpr int kWork = kOwn + kFWaves * kOwnWave;
+    static_assert(kOwnWave >= kWeightsWave && (!BF16 || kOwnWave >= kStageWave), "neither reaches into the next wave's area");
+    static_assert(kOwn % 4 == 0 && kOwnWave % 4 == 0, "16-byte accesses");
     // Outputs: [register quad][lane][4], the quads 16 words apart so that the threads that add the waves' up find their channels
     // in different banks.  A wave that has cached and current tiles leaves two of them, the first while others still work.
     static constexpr int kQuad = 256 + 16, kSlot = DIM / 8 * kQuad, kOut = kFWaves * kSlot;
@@ -245,7 +249,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
     const T *const q_all = static_cast<const T *>(a.q);
 
     // weights of a tile in LDS, for loops that cannot index registers
-    float *const weights = lds + L::kWeights + wave * 1024;
+    float *const weights = lds + L::kOwn + wave * L::kOwnWave;
     auto keep_weights = [&](const f32x16 &s) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) weights[64 * v + lane] = s[v];
@@ -892,7 +896,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             if constexpr (kBf16) {
                 // Rows of the tile through LDS: the transposing read hands a lane four tokens of its channel (of 16 lanes, lane
                 // 4 j + c supplies the address of token j, channels 4 c .. 4 c + 3, and lane i receives channel i).
-                uint16_t *const stage = reinterpret_cast<uint16_t *>(lds + L::kStage + wave * L::kStageWave);
+                uint16_t *const stage = reinterpret_cast<uint16_t *>(lds + L::kOwn + wave * L::kOwnWave);
 #pragma unroll
                 for (int i = 0; i < kVPieces; ++i)
                     *reinterpret_cast<u32x4 *>(stage + (lane + 64 * i) / (DIM / 8) * L::kStageRow + 8 * (lane % (DIM / 8))) = v_rows[i];
