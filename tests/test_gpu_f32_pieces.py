@@ -16,7 +16,8 @@ FORMATS = [(64, 2, B.KVQ_FP32, B.KVQ_META_FP32, 64), (64, 4, B.KVQ_FP32, B.KVQ_M
            (128, 4, B.KVQ_FP32, B.KVQ_META_FP32, 128), (128, 2, B.KVQ_FP32, B.KVQ_META_FP8_BF16, 32), (64, 2, B.KVQ_BF16, B.KVQ_META_FP8_BF16, 64)]
 
 
-def _attend(fmt, rows, current, cached, q_scale=1.0, k_scale=1.0, v_scale=1.0, offset=None, poison=None):
+def _attend(fmt, rows, current, cached, q_scale=1.0, k_scale=1.0, v_scale=1.0, offset=None, spike=2.0, keys_and_values=None,
+            poison=None):
     dim, bits, io, meta, group = fmt
     heads = 2
     dtype = torch.bfloat16 if io == B.KVQ_BF16 else torch.float32
@@ -32,7 +33,9 @@ def _attend(fmt, rows, current, cached, q_scale=1.0, k_scale=1.0, v_scale=1.0, o
         if offset:                    # every third token: all rotated channels far from 0, next to a small range
             for x in (k, v):
                 x[::3] *= 1e-2 / offset
-                x[::3, :, 0] += 2.0
+                x[::3, :, 0] += spike
+        if keys_and_values:
+            keys_and_values(k, v)
         B.kvq_quantize_append(cache, k.to(dtype), v.to(dtype))
     q = t(rows, q_scale).to(dtype)
     k, v = (t(current, k_scale).to(dtype), t(current, v_scale).to(dtype)) if current else (None, None)
@@ -138,3 +141,75 @@ def test_large_values_behind_a_late_maximum(fmt, large, monkeypatch):
     torch.cuda.synchronize()
     assert float(ref.abs().max()) > 2.0 ** 117
     _close(got.double() * 2.0 ** -119, mass, ref.double() * 2.0 ** -119, ref_mass, 1e-5 if io == B.KVQ_FP32 else 2.0 ** -8)
+
+
+GROUPED = [(dim, bits, B.KVQ_FP32, B.KVQ_META_FP8_BF16, group) for dim in (64, 128) for bits in (2, 4) for group in (32, 64, 128) if group <= dim] + \
+    [(64, 4, B.KVQ_BF16, B.KVQ_META_FP8_BF16, 32), (64, 4, B.KVQ_BF16, B.KVQ_META_FP8_BF16, 64)]
+
+
+def _one_sided(k, v):
+    """What ordinary data with one large channel and an offset of the values look like behind the rotation: groups of channels
+    whose range does not hold 0, with zero-points of -30 .. 50 beside ordinary ones."""
+    k[..., 32] *= 10.0
+    v[..., 0] += 2.0 * math.sqrt(v.shape[2])
+    v[: v.shape[0] // 2, :, 0] *= -1.0
+
+
+@pytest.mark.parametrize("fmt", GROUPED)
+@pytest.mark.parametrize("large", ["keys", "values", "both"])
+def test_groups_whose_range_does_not_hold_zero(fmt, large):
+    def change(k, v):
+        a, b = k.clone(), v.clone()
+        _one_sided(a, b)
+        if large != "values":
+            k.copy_(a)
+        if large != "keys":
+            v.copy_(b)
+
+    cache, *results = _attend(fmt, 40, 70, 300, q_scale=0.3, keys_and_values=change)
+    low, high = (-12.0, 15.0) if fmt[1] == 2 else (0.0, 15.0)
+    if fmt[1] == 4 and (large == "values" or fmt[4] == 32):      # beyond what one operand holds, next to ordinary ones
+        zero = B.export_all(cache, 0 if large == "keys" else 1)[2]
+        out = (zero < low) | (zero > high)
+        assert 0.005 < float(out.float().mean()) and float(zero.abs().max()) < 128.0
+    # a score or an output is a sum of terms |zero| / 15 < 8 times larger than without the offset
+    _close(*results, score_error=8e-5)
+
+
+@pytest.mark.parametrize("fmt", GROUPED)
+def test_zero_points_beyond_exact_constants(fmt):
+    """Zero-points above 2^20: fp32 products, where the scores are as inexact as fp32 makes them."""
+    cache, *results = _attend(fmt, 40, 70, 200, q_scale=1e-5, offset=4e4, spike=4200.0 * math.sqrt(fmt[0]))
+    assert float(B.export_all(cache, 0)[2].abs().max()) > 2.0 ** 20
+    # |q~| * zero * step * 2^-24 = 1e-5 * 4200 * sqrt(dim) * 2^-24 in a score
+    _close(*results, score_error=1e-5)
+
+
+@pytest.mark.parametrize("fmt", [(64, 4, B.KVQ_BF16, B.KVQ_META_FP8_BF16, 32), (128, 4, B.KVQ_FP32, B.KVQ_META_FP8_BF16, 32)])
+def test_such_groups_take_about_the_usual_time(fmt):
+    dim, bits, io, meta, group = fmt
+    heads, rows, cached = 8, 256, 2000
+    dtype = torch.bfloat16 if io == B.KVQ_BF16 else torch.float32
+    calls = []
+    for one_sided in (False, True):
+        k, v = (torch.randn((cached, heads, dim), device=DEV) for _ in range(2))
+        if one_sided:
+            _one_sided(k, v)
+        cache = B.Cache(B.make_desc(heads, dim, bits, cached, io, group, 1, meta), DEV)
+        B.kvq_quantize_append(cache, k.to(dtype), v.to(dtype))
+        q = torch.randn((rows, heads, dim), device=DEV).to(dtype)
+        out = torch.empty_like(q)
+        calls.append(lambda cache=cache, q=q, out=out: B.kvq_chunk_attention(cache, 0, cached, q, None, None, out))
+    times = [math.inf, math.inf]
+    for _ in range(5):
+        for i, call in enumerate(calls):
+            call()
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(50):
+                call()
+            end.record()
+            end.synchronize()
+            times[i] = min(times[i], begin.elapsed_time(end))
+    # 2.3 to 2.6 times as long while such tiles took the fp32 matrix instructions
+    assert times[1] < 1.6 * times[0], times
