@@ -212,7 +212,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
         //
         // The rotation leaves every lane (row n, half hh) with the 64 channels of its B operands (bit 3 = hh), so nothing goes
         // through LDS: channel bits 0 .. 3 by one MFMA per 16 channels against the signs of a 16 x 16 Hadamard matrix (bf16
-        // products are exact, sums fp32), bits 4 .. 6 by butterflies between registers.  With a lane per row and all seven
+        // products are exact, sums fp32), bits 4 .. 6 by butterflies between registers.  The signs carry 2^-4, so that the sum of
+        // squares below, |q|^2 / 2 then, is finite where |q|^2 is.  With a lane per row and all seven
         // stages in its registers the preparation was 3200 instructions and five barriers instead of 1500 and none (8 heads x
         // 1024 rows x (4096 + 1024) keys, append included: 64.1 -> 61.4 us).
         int ln = lane;
@@ -225,11 +226,11 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
                 const uint32_t even = (uint32_t)(__popc(low & (2 * p)) + both) & 1u, odd = (uint32_t)(__popc(low & (2 * p + 1)) + both) & 1u;
-                w[p] = 0x3f803f80u ^ (even << 15) ^ (odd << 31);
+                w[p] = 0x3d803d80u ^ (even << 15) ^ (odd << 31);      // +-2^-4
             }
             had = u32x4{w[0], w[1], w[2], w[3]};
         }
-        const float cq = c_log * 0.088388347648318f;
+        const float cq = c_log * (16.0f * 0.088388347648318f);
         // The channels in operand order.  Element j of MFMA jm belongs to word 2 jm + (j >> 4), 2-bit field
         // 2 (j & 7) + ((j >> 3) & 1) of the lane's key words (see key_pair); the conversion takes even elements from
         // its first operand and odd ones from its second.  Here: 8 * slab + channel within the half slab.
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
             qp_scale[rb] = (int)scale_word;
             ssum += xhalf(ssum);
             nu += xhalf(nu);
-            rowop[rb] = row_operand(ssum, 0.0f, CORR ? -a.softmax_scale * a.softmax_scale * kLog2e * nu * (1.0f / (24.0f * D)) : 0.0f);
+            rowop[rb] = row_operand(ssum, 0.0f, CORR ? -a.softmax_scale * a.softmax_scale * kLog2e * nu * (256.0f / (24.0f * D)) : 0.0f);
         }
         // The 96 registers of query pieces live in accumulation registers (MFMA reads them from there directly), which leaves
         // the vector registers to the score tile in flight.

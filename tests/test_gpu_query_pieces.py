@@ -6,6 +6,7 @@ import math
 import pytest
 import torch
 
+from launches import SIXTEEN_BIT, attention_threads
 from paper_2605_26266_amd import binding as B
 from test_gpu_attention import P                                                                                  # noqa: F401
 
@@ -45,3 +46,26 @@ def test_query_pieces(P, axis, correction, blocks, rows, signs, outlier):       
     P.assert_attention_close(out.double().cpu().numpy(), mass.double().cpu().numpy(), ref.double().cpu().numpy(),
                              ref_mass.double().cpu().numpy(), P.TOL_OUT_BF16, "query pieces", mass_floor=1e-3)
     assert float((mass.double() / ref_mass.double()).log().abs().max()) <= score_error
+
+
+@pytest.mark.parametrize("axis", [B.KVQ_KEYS_PER_TOKEN, B.KVQ_KEYS_PER_CHANNEL])
+def test_norms_of_large_queries(P, axis):        # noqa: F811
+    """Queries of norm 8e18, whose square is within fp32 and 128 times the square is not; ordinary scores and corrections."""
+    heads, rows, cached, current, scale = 4, 3000, 200, 40, 1.2e-19
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(9)
+
+    def t(n, times=1.0):
+        return (torch.randn((n, heads, 128), generator=gen, device=DEV) * times).to(torch.bfloat16)
+
+    cache = B.Cache(B.make_desc(heads, 128, 2, 224, B.KVQ_BF16, key_axis=axis), DEV)
+    B.kvq_quantize_append(cache, t(cached), t(cached))
+    q, k, v = t(rows, 7e17), t(current), t(current)
+    out, mass = torch.full_like(q, float("nan")), torch.empty((heads, rows), dtype=torch.float32, device=DEV)
+    ref, ref_mass = torch.empty_like(out), torch.empty_like(mass)
+    B.kvq_chunk_attention(cache, 0, cached, q, k, v, out, mass, scale)
+    B.kvq_chunk_attention_fp32(cache, 0, cached, q, k, v, ref, ref_mass, scale)
+    torch.cuda.synchronize()
+    assert attention_threads(cache, 0, cached, q, k, v, out) == SIXTEEN_BIT
+    P.assert_attention_close(out.double().cpu().numpy(), mass.double().cpu().numpy(), ref.double().cpu().numpy(),
+                             ref_mass.double().cpu().numpy(), P.TOL_OUT_BF16, "large queries")
