@@ -4,6 +4,7 @@ import ctypes
 import pytest
 import torch
 
+from launches import SIXTEEN_BIT, attention_threads
 from paper_2605_26266_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -41,10 +42,18 @@ SHAPES = [
     (8, 1, 900, 1000, True, [3000], 5, 2990),        # 32 blocks of 256 rows in the 16-bit kernels
     (44, 1, 1600, 33, False, [2000], 0, 2000),       # 308 blocks: 256 whole, 52 split
 ]
+# Keys per token: the last two above, and what the first ones stand for over rows enough for the 16-bit kernels
+SIXTEEN_BIT_SHAPES = SHAPES[-2:] + [
+    (2, 3, 2600, 2700, True, [500, 269], 45, 700),   # ragged window over two blocks, rows that see part of a piece only
+    (3, 1, 6000, 6000, True, [96], 0, 96),           # pieces that hold current tiles alone, some invisible to early rows
+    (8, 1, 1281, 1, False, [3024], 31, 2993),        # a last row block with one row
+    (5, 1, 2100, 0, False, [4000], 1, 3999),         # no current block
+    (2, 1, 8200, 8200, False, [], 0, 0),             # no cached tokens
+]
 
 
 @pytest.mark.parametrize("fmt", FORMATS)
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SHAPES + SIXTEEN_BIT_SHAPES[2:])
 def test_split_call_agrees_with_the_unsplit_one(fmt, shape):
     bits, meta, group, axis = fmt
     heads, ratio, rows, current, causal, blocks, start, length = shape
@@ -66,6 +75,8 @@ def test_split_call_agrees_with_the_unsplit_one(fmt, shape):
     ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)     # NaN patterns: only what was written may be read
     out, mass = _call(cache, start, length, q, k, v, ratio, causal, ws)
     ref, ref_mass = _call(cache, start, length, q, k, v, ratio, causal, None)
+    if shape in SIXTEEN_BIT_SHAPES and nbytes:
+        assert attention_threads(cache, start, length, q, k, v, out.to(q.dtype), causal, workspace=ws) == SIXTEEN_BIT
     assert torch.isfinite(out).all()
     # Either side rounds its probabilities and its output to 16 bits.  Relative to the result a rounding to 8 bits is 2^-9 /
     # sqrt(3) rms, for the terms of a sum of independent values as for the sum; four of them: 2.3e-3.  (What a 32-key tile
@@ -93,7 +104,7 @@ def test_too_small_a_workspace_means_no_split():
 @pytest.mark.parametrize("bits", [2, 4])
 def test_split_call_on_a_flagged_cache_is_served_by_the_vector_kernel(bits):
     """Zero-points beyond the 16-bit kernels' domain: the merge launch computes the call in place of the pieces."""
-    heads, tokens, rows = 8, 1500, 900
+    heads, tokens, rows = 8, 1500, 1800
     gen = torch.Generator(device=DEV)
     gen.manual_seed(3)
     k = torch.randn((tokens, heads, 128), generator=gen, device=DEV) * 1e-5
@@ -104,7 +115,8 @@ def test_split_call_on_a_flagged_cache_is_served_by_the_vector_kernel(bits):
     B.kvq_quantize_append(cache, k, v)
     assert float(B.export_all(cache, 0)[2].abs().max()) > 70000.0
     q = q * 0.02
-    assert B.lib().kvq_attention_workspace_bytes(cache.handle, 0, tokens, rows, 64, 1) > 0
+    ws = B._workspace(cache, 0, tokens, rows, 64, 1, None)
+    assert ws is not None and attention_threads(cache, 0, tokens, q, cur, cur, torch.empty_like(q), workspace=ws) == SIXTEEN_BIT
     out, mass = torch.empty_like(q), torch.empty((heads, rows), dtype=torch.float32, device=DEV)
     ref, ref_mass = torch.empty_like(out), torch.empty_like(mass)
     B.kvq_chunk_attention(cache, 0, tokens, q, cur, cur, out, mass)
