@@ -101,11 +101,19 @@ def _check(status: int, where: str) -> None:
         raise KvqError(status, where)
 
 
+def _from_torch(private: str, public):
+    """A function of torch's own that answers without the objects that the public one makes on the way; the public one where
+    this torch does not have it."""
+    return getattr(torch._C, private, public)
+
+
+_current_device = _from_torch("_cuda_getDevice", torch.cuda.current_device)
+_raw_stream = _from_torch("_cuda_getCurrentRawStream", lambda device: torch.cuda.current_stream(device).cuda_stream)
+_is_capturing = _from_torch("_cuda_isCurrentStreamCapturing", torch.cuda.is_current_stream_capturing)
+
+
 def _stream(stream: Optional[torch.cuda.Stream]) -> int:
-    if stream is not None:
-        return int(stream.cuda_stream)
-    # (what torch.cuda.current_stream().cuda_stream says, without the two objects that it makes on the way)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream) if stream is not None else _raw_stream(_current_device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -266,14 +274,14 @@ def _workspace(cache: Cache, cache_start: int, cache_len: int, rows: int, n_cur:
             return None
         with torch.cuda.stream(stream):
             return _allocate(nbytes, cache.storage)
-    if torch._C._cuda_getDevice() != cache.storage.get_device():      # the current stream belongs to the current device
+    if _current_device() != cache.storage.get_device():      # the current stream belongs to the current device
         return None
     return _allocate(nbytes, cache.storage)       # (a stream context for the current stream takes 1.5 us of the host's time)
 
 
 def _allocate(nbytes: int, like: torch.Tensor) -> Optional[torch.Tensor]:
     try:
-        if torch._C._cuda_isCurrentStreamCapturing() and not _allocator_takes_part_in_capture(like.device):
+        if _is_capturing() and not _allocator_takes_part_in_capture(like.device):
             return None
         return like.new_empty(nbytes)
     except torch.OutOfMemoryError:

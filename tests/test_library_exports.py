@@ -140,3 +140,20 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_torch_functions_that_are_not_public_have_a_public_one_behind_them(B, monkeypatch):
+    """A torch without the names that the binding asks for the current stream: the module loads and uses the public functions."""
+    import importlib.util
+    import torch
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream", "_cuda_isCurrentStreamCapturing"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    stream = type("Stream", (), {"cuda_stream": 77})
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: stream if device == 3 else None)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    spec = importlib.util.spec_from_file_location("paper_2605_26266_amd.binding_without", B.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module._stream(None) == 77 and module._stream(stream) == 77
+    assert module._current_device() == 3 and module._is_capturing()
