@@ -164,11 +164,11 @@ __device__ inline void store4(uint16_t *p, float a, float b, float c, float d)
 }
 
 // LDS, in words.  While tiles are worked on: query pieces [piece][slab][lane][4], the query in fp32 [slab][quad][lane][4], fp32 tensors: pieces of
-// the query before rotation; correction factors and the query's sums over groups [group][row], metadata
-// of each wave's tile [value scale | value zero | key scale, or what the value zero-points leave][group][token], and for each wave the weights or the values of a tile; later the waves' outputs; behind both the
+// the query before rotation; correction factors and, once asked for, the query's sums over groups [group][row], metadata
+// of each wave's tile [value scale | value zero | key scale, or what the value zero-points leave | what the key ones leave][group][token], and for each wave the weights or the values of a tile; later the waves' outputs; behind both the
 // waves' maxima and sums.
 template <int DIM, int G, bool BF16> struct F32Lds {
-    static constexpr int kPieces = 3 * (DIM / 16) * 256, kQuery = kPieces, kPlain = kQuery + DIM * 32, kCorr = kPlain + (BF16 ? 0 : kPieces), kSum = kCorr + G * 32, kMeta = kSum + G * 32, kMetaWave = 3 * G * 32;
+    static constexpr int kPieces = 3 * (DIM / 16) * 256, kQuery = kPieces, kPlain = kQuery + DIM * 32, kCorr = kPlain + (BF16 ? 0 : kPieces), kSum = kCorr + G * 32, kMeta = kSum + G * 32, kMetaWave = 4 * G * 32;
     static constexpr int kFlags = kMeta + kFWaves * kMetaWave, kOwn = kFlags + kFWaves;
     // BF16 value rows of a current tile, 64 bytes longer than the row (four rows and two 16-channel columns fill the banks once)
     static constexpr int kStageRow = DIM + 32, kStageWave = kTileTokens * kStageRow / 2;
@@ -394,16 +394,6 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             if constexpr (GROUP >= 128) nu += lane_xor<32>(nu);
             if (g8 % (GROUP / 8) == 0)
                 lds[L::kCorr + g8 / (GROUP / 8) * 32 + r8] = a.correction == 1 ? -nu * (a.softmax_scale * c_log * (1.0f / 24.0f)) : 0.0f;
-            if constexpr (FP8) {
-                float s = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) s += y[e];
-                s += lane_xor<1>(s);
-                s += lane_xor<2>(s);
-                if constexpr (GROUP >= 64) s += lane_xor<16>(s);
-                if constexpr (GROUP >= 128) s += lane_xor<32>(s);
-                if (g8 % (GROUP / 8) == 0) lds[L::kSum + g8 / (GROUP / 8) * 32 + r8] = s;
-            }
             leave_pieces(pieces);
 #pragma unroll
             for (int p = 0; p < 2; ++p)
@@ -495,6 +485,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
         float *const meta = lds + L::kMeta + wave * L::kMetaWave;      // this wave's metadata: [value scale | zero | key scale][group][token]
         // Register v of a result tile holds key (token) 8 (v >> 2) + 4 hh + (v & 3).
         auto per_key = [&](int row, int g4) { return *reinterpret_cast<const float4 *>(meta + row * 32 + 8 * g4 + 4 * hh); };
+        bool have_sums = false;
         for (;;) {
             const int tile = x;
             const bool edge = tile == 0 || tile == tc - 1;
@@ -506,7 +497,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             // (kTau: values are code - 1, the middle of their range, and what is left of the zero-points goes into tau.)
             // Steps whose products with weights may leave the range at either end are not among them.
             constexpr float kMid = FP8 ? 0.5f * (float)MASK : 0.0f, kFar = FP8 ? 15.0f - 0.5f * (float)MASK : 240.0f;
-            bool fits_k = FP8 || !unfit, fits_v = FP8 || vs[0] == 0.0f || (vs[0] >= 0x1p-80f && vs[0] <= 0x1p80f);
+            bool fits_k = !unfit, fits_v = FP8 || vs[0] == 0.0f || (vs[0] >= 0x1p-80f && vs[0] <= 0x1p80f);
             if (kTau) fits_v = fits_v && fabsf(vz[0]) * vs[0] <= kTop;
 #pragma unroll
             for (int j = 0; j < G; ++j) {
@@ -519,14 +510,16 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             // the nearest one within, and what that leaves, the same for all channels of the group, is added as a constant of the
             // key (times the query's sum over the group) or of the value (on all channels of the group).  As fp32 MFMAs such tiles
             // took twice the time and more (12 heads x 500 rows x (1500 + 500) keys, head_dim 64, BF16, 4 bits, groups of 32: 26 us on
-            // centred values; with one large key channel and an offset of the values 66 us that way, 29 this way).
+            // centred values; with one large key channel and an offset of the values 66 us that way, 29 this way).  Work that such tiles alone need stands at
+            // branches that were there: sums over the query in its preparation and a branch inside the scores cost every call 0.4 us.
             constexpr float kLow = (float)MASK - 15.0f, kHigh = 15.0f, kExact = 0x1p20f;
             bool far_k = false, far_v = false;
             if constexpr (FP8) {
-                far_k = !fits_k;
+                far_k = !fits_k && !unfit;
                 far_v = !fits_v;
                 if (__builtin_expect(far_k || far_v, 0)) {
-                    fits_k = fits_v = true;
+                    fits_k = !unfit;
+                    fits_v = true;
 #pragma unroll
                     for (int j = 0; j < G; ++j) {
                         fits_k = fits_k && fabsf(kz[j]) <= kExact;
@@ -534,15 +527,17 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                     }
                     fits_k = __all(fits_k);
                     fits_v = __all(fits_v);
-                    if (far_v && fits_v)
+                    far_k = far_k && fits_k;
+                    far_v = far_v && fits_v;
 #pragma unroll
-                        for (int j = 0; j < G; ++j) {
-                            const float z = __builtin_amdgcn_fmed3f(vz[j], kLow, kHigh);
-                            if (hh == 0) meta[(2 * G + j) * 32 + n] = (z - vz[j]) * vs[j];
-                            vz[j] = z;
-                        }
+                    for (int j = 0; j < G; ++j) {
+                        const float k = far_k ? __builtin_amdgcn_fmed3f(kz[j], kLow, kHigh) : kz[j];
+                        const float v = far_v ? __builtin_amdgcn_fmed3f(vz[j], kLow, kHigh) : vz[j];
+                        meta[((2 + hh) * G + j) * 32 + n] = hh ? (k - kz[j]) * ks[j] : (v - vz[j]) * vs[j];
+                        kz[j] = k;
+                        vz[j] = v;
+                    }
                 }
-                fits_k = fits_k && !unfit;
             }
 #pragma unroll
             for (int j = 0; j < G; ++j) {
@@ -561,24 +556,6 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
                     const uint32_t w = pack_bf16(s0 * s0, s1 * s1);
                     const uint32_t w0 = (w & 0xffffu) * 0x10001u, w1 = (w >> 16) * 0x10001u;
                     s = mfma_bf16(u32x4{w0, (w0 & 0xffffu) | (w1 & 0xffff0000u), w1, 0u}, corr_op, s);
-                    if (__builtin_expect(far_k, 0)) {
-                        // both factors in three pieces, the six products above 2^-27 (lane half hh: group g + hh)
-#pragma unroll
-                        for (int g = 0; g < G; g += 2) {
-                            float rest = 0.0f;
-#pragma unroll
-                            for (int j = g; j < g + 2 && j < G; ++j) {
-                                const float z = __builtin_amdgcn_fmed3f(kz[j], kLow, kHigh);
-                                if (hh == j - g) rest = (z - kz[j]) * ks[j];
-                                kz[j] = z;
-                            }
-                            const float sum = lds[L::kSum + (G == 1 ? 0 : g + hh) * 32 + n];
-                            const Pieces e = split3(rest, rest), q = split3(sum, sum);
-                            constexpr uint32_t kLowHalf = 0xffffu, kHighHalf = 0xffff0000u;
-                            s = mfma_bf16(u32x4{(e.hi & kLowHalf) | (e.mid & kHighHalf), (e.lo & kLowHalf) | (e.mid & kHighHalf), e.hi, 0u},
-                                          u32x4{(q.lo & kLowHalf) | (q.mid & kHighHalf), q.hi, (q.mid & kLowHalf) | (q.hi & kHighHalf), 0u}, s);
-                        }
-                    }
                 }
                 auto multiply = [&](const u32x4 &op, int i) {
                     s = mfma_bf16(op, query(2, i), s);
@@ -681,6 +658,34 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             for (int i = 0; i < WPL; ++i) vcur[i] = vw[i];
             const bool more = ++x < c_end;
             if (more) fetch(x);
+            if (FP8 && __builtin_expect(far_k, 0)) {
+                // what is left of the zero-points times the query's sum over the group: both factors in three pieces, the six
+                // products above 2^-27 (lane half hh: group g + hh)
+                if (!have_sums) {       // (waves that come here write the same sums to the same place)
+                    have_sums = true;
+#pragma unroll 1
+                    for (int g = 0; g < G; ++g) {
+                        float sum = 0.0f;
+#pragma unroll 1
+                        for (int i = g * (GROUP / 8); i < (g + 1) * (GROUP / 8); ++i) {      // quads of this lane half's channels
+                            const float4 x = *reinterpret_cast<const float4 *>(lds + L::kQuery + 4 * (i * 64 + lane));
+                            sum += (x.x + x.y) + (x.z + x.w);
+                        }
+                        lds[L::kSum + g * 32 + n] = sum + other_half(sum);
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                }
+#pragma unroll
+                for (int g = 0; g < G; g += 2) {
+                    const float rest = G == 1 && hh ? 0.0f : meta[(3 * G + (G == 1 ? 0 : g + hh)) * 32 + n];
+                    const float q_sum = lds[L::kSum + (G == 1 ? 0 : g + hh) * 32 + n];
+                    const Pieces e = split3(rest, rest), q = split3(q_sum, q_sum);
+                    constexpr uint32_t kLowHalf = 0xffffu, kHighHalf = 0xffff0000u;
+                    s = mfma_bf16(u32x4{(e.hi & kLowHalf) | (e.mid & kHighHalf), (e.lo & kLowHalf) | (e.mid & kHighHalf), e.hi, 0u},
+                                  u32x4{(q.lo & kLowHalf) | (q.mid & kHighHalf), q.hi, (q.mid & kLowHalf) | (q.hi & kHighHalf), 0u}, s);
+                }
+            }
             if (edge) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
