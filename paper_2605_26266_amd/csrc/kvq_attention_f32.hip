@@ -415,25 +415,26 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[b][v] = 0.0f;
-    // Scores are taken relative to m_ref, which moves when a row goes beyond it by more than a factor of 2^slack (weights and sums
-    // are fp32: where it lies matters only to sums that come near the end of the range).  `above`: the row's largest score less m_ref.
-    float m_ref = -INFINITY, base = 0.0f, limit = -INFINITY, above = -INFINITY, slack = 8.0f, l_s = 0.0f, l_r = 0.0f, tau = 0.0f;
+    // Scores are taken relative to `base`, which moves when a row goes beyond it by more than a factor of 2^slack (weights and sums
+    // are fp32: where it lies matters only to sums that come near the end of the range).  `above`: the row's largest score less
+    // `base`, -inf before the first one.
+    float base = 0.0f, above = -INFINITY, slack = 8.0f, l_s = 0.0f, l_r = 0.0f, tau = 0.0f;
 
     // s: scores in log2 units less `base` (-inf: key not seen) -> weights.  large: the tile's values lie so high that sums with
     // weights up to 2^slack might leave the range of fp32; from here on weights stay below 1.
     auto weigh = [&](f32x16 &s, float &l, bool large) {
-        if (__builtin_expect(large, 0)) {
-            slack = 0.0f;
-            limit = fminf(limit, 0.0f);
-        }
+        if (__builtin_expect(large, 0)) slack = 0.0f;
         float mx = s[0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
         mx = fmaxf(mx, other_half(mx));
+        const bool first = above == -INFINITY;
         above = fmaxf(above, mx);
-        if (__any(above > limit)) {
-            const bool moves = above > limit;
-            const float to = moves ? base + above : base, by = to - base, alpha = m_ref == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(-by);
+        const bool moves = above > (first ? -INFINITY : slack);
+        if (__any(moves)) {
+            const float to = moves ? base + above : base, by = to - base, alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-by);
+            base = to;
+            above = moves ? 0.0f : above;
             l_s *= alpha;
             l_r *= alpha;
             tau *= alpha;
@@ -441,11 +442,6 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[b][v] *= alpha;
-            if (moves) {
-                m_ref = base = to;
-                limit = slack;
-                above = 0.0f;
-            }
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[v] -= by;
         }
@@ -814,10 +810,10 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
         l_s += other_half(l_s);
         l_r += other_half(l_r);
         if (hh == 0) {
-            red[(slot * 4) * 32 + n] = m_ref;
+            red[(slot * 4) * 32 + n] = above == -INFINITY ? -INFINITY : base;
             red[(slot * 4 + 1) * 32 + n] = l_s;
             red[(slot * 4 + 2) * 32 + n] = l_r;
-            red[(slot * 4 + 3) * 32 + n] = m_ref + above;
+            red[(slot * 4 + 3) * 32 + n] = base + above;
         }
         float *const dst = lds + (slot < kFWaves ? slot * L::kSlot : L::kSlot8) + 4 * lane;
 #pragma unroll
@@ -832,7 +828,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void attention_f32_kernel(Attentio
         if (!kBf16) slack = 0.0f;     // (fp32 values are asked for behind the weights)
         if (run_start(wave) < tc) {
             leave(kFWaves);
-            m_ref = limit = above = -INFINITY;
+            above = -INFINITY;
             base = l_s = l_r = 0.0f;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
