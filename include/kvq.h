@@ -191,14 +191,15 @@ kvq_status kvq_quantize_append_static(kvq_cache *cache, const void *k, const voi
  * mode that always runs the fp32 vector kernel).
  * cache_len == 0 (first chunk) and n_cur == 0 are allowed, not both; m == 0 is a no-op.
  * `out` must not alias the inputs.
- * Which kernel runs: 16-bit matrix cores for BF16 caches with head_dim 128 (every format), fp32 matrix cores (all
- * arithmetic in fp32) for the other caches with per-token keys and for those calls of the former whose estimated time is
- * clearly shorter there (few query rows, or few keys), the fp32 vector kernel for per-channel keys outside BF16 / head_dim
+ * Which kernel runs: the 16-bit matrix kernels for BF16 caches with head_dim 128 (every format), the fp32 matrix kernel
+ * (fp32 results on the same matrix cores: fp32 operands enter as three BF16 pieces that add up to them, sums are fp32) for the
+ * other caches with per-token keys and for those calls of the former whose estimated time is clearly shorter there (calls
+ * whose blocks of 256 query rows would not fill the GPU, as a rule), the fp32 vector kernel for per-channel keys outside BF16 / head_dim
  * 128, for the exact correction and for calls beyond what the matrix kernels index.  The 16-bit kernels carry a zero-point as
  * two 16-bit pieces, exact below 2^16.  A cache that has stored a larger one since it was created or last reset (vectors
  * whose offset is tens of thousands of times their range) is marked by the append; for such a cache the launch of a 16-bit
  * kernel returns without writing and the launch enqueued behind it computes the call with the vector kernel's arithmetic
- * (the results of kvq_chunk_attention_fp32).  Calls on the fp32 matrix cores take any zero-point: the same expressions,
+ * (the results of kvq_chunk_attention_fp32).  Calls on the fp32 matrix kernel take any zero-point: the same expressions,
  * summed in another order.  The mark is only cleared by kvq_cache_reset followed by an append.
  */
 kvq_status kvq_chunk_attention(const kvq_cache *cache, int64_t cache_start, int64_t cache_len,

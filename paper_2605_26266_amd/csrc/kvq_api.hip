@@ -90,7 +90,9 @@ bool tensor_ok(const void *p, int64_t stride_token, int64_t stride_head, int hea
 // 12 / 32 pieces.  32 query heads x 1 row x (8192 + 64) keys, group-wise kernel: 361 (374) / 114 (121) / 70 (78) / 87 (107) /
 // 122 (165) us with 1 / 4 / 8 / 16 / 32; fp32 kernel, 8 units: 108 (108) / 39 (40) / 26 (29) / 21 (22) / 20 (23) / 21 (24) /
 // 32 (42) us with 1 / 4 / 8 / 17 / 24 / 32 / 64; head_dim 64, 2 heads x 300 rows x (4000 + 300) keys, 20 units: 38 (44) / 26 (30) /
-// 20 (23) / 16 (20) / 17 (18) / 30 (47) us with 1 / 2 / 4 / 8 / 12 / 32 (0.19 us a tile; fp32 tensors and groups take 0.3).  24 heads x 4680 rows x (28080 + 4680) keys, 200 units after a full round: 2043
+// 20 (23) / 16 (20) / 17 (18) / 30 (47) us with 1 / 2 / 4 / 8 / 12 / 32 (0.19 us a tile; fp32 tensors and groups take 0.3).  Over
+// random calls (see choose()) all three estimates are high, by 5 to 20 % on average, and alike: the 16-bit kernels took 0.79 to
+// 0.98 of theirs, the fp32 kernel 0.81 to 0.97.  24 heads x 4680 rows x (28080 + 4680) keys, 200 units after a full round: 2043
 // (2094) / 2133 (2131) / 2044 (1982) / 2089 (2043) / 2110 (2178) us with 1 / 2 / 5 / 6 / 9.
 struct KernelCost {
     int rows;          // query rows of a unit
@@ -164,13 +166,15 @@ const KernelCost &cost_of(Route r, int head_dim)
     return r == Route::group ? kCostGroup : kCostPerToken;
 }
 
-// Kernel and grid of a call.  A call that fills a sliver of the 256-row blocks (the last tokens of a prompt, a decoded token),
-// or that has a few tiles of keys behind the 16-bit kernels' longer preparation, takes the fp32 kernel with its 32-row units
-// over all query heads of a key/value head, where that is estimated to be clearly faster (8 key/value heads with 4 query heads
-// each, 1 row, 8192 + 64 keys, groups of 32: 70 us in the group-wise kernel, 39 us here).  Where the line lies: of 220 random
-// calls of these caches with estimates near each other, timed on both kernels, the fp32 one took 0.85 of the other's time on
-// average where the estimate promised less than 0.8 (none of 37 was slower by more than 1 %), 0.92 between 0.8 and 0.95 (9 of
-// 106 slower), and as long beyond.
+// Kernel and grid of a call.  The fp32 kernel's units are 32 rows over all query heads of a key/value head and its tile costs a
+// third of a 16-bit kernel's, which however works for eight times the rows: it is the faster one wherever the 256-row blocks do
+// not fill the chip about once (a decoded token, the last tokens of a prompt, one to eight heads over some thousand rows).  8
+// key/value heads with 4 query heads each, 1 row, 8192 + 64 keys, groups of 32: 70 us in the group-wise kernel, 21 us here; 8
+// heads x 143 rows x 286 keys: 31 and 13 us; 16 x 8 heads x 19 rows x 13314 keys, 128 blocks of 256 rows: 524 and 174 us.  Where
+// the line lies: 800 random calls of these caches, 1 to 48 heads, 1 to 5000 rows, up to 60000 keys, keys with and without a large
+// channel, a quarter of them without a work space, were timed on both kernels.  Where the estimate promised less than 0.8 the fp32
+// kernel took 0.51 of the other's time on average and none of 665 calls was slower by more than 1 %; between 0.8 and 0.95 0.83 (2
+// of 42 slower, at most 1.10); from there to 1.25 as long (20 of 43 slower, at most 1.35).
 struct Choice {
     Route route;
     kvq::SplitArgs sp;
