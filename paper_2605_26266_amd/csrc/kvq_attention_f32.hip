@@ -25,9 +25,9 @@
 // Bound by instruction issue: about 420 vector instructions per tile and wave at head_dim 64 (unpacking 100, scale and softmax
 // 110, weights in three pieces 104) beside 24 MFMAs.  Why this shape: with fp32 MFMAs (64 clocks for 4096 flop against 32 for
 // 32768) the matrix instructions alone took 4096 (8192) clocks per tile and wave, now 768 (1536), and every wave rotated the
-// query and its output by itself.  12 heads x 500 rows x (1500 + 500) keys, BF16, head_dim 64: 51.4 -> 22.5 us (137 TFLOP/s).
+// query and its output by itself.  12 heads x 500 rows x (1500 + 500) keys, BF16, head_dim 64: 51.2 -> 22.4 us (137 TFLOP/s).
 // 32 query heads on 8 x 1 row x (8192 + 64) keys, groups of 32: 34.4 -> 17 us (kernel alone, in 17 pieces).  4 heads x 300 rows x
-// (1500 + 300) keys in fp32, head_dim 128: 33.7 us with current tiles on fp32 MFMAs, 28.4 us with six products.
+// (1500 + 300) keys in fp32, head_dim 128: 39.8 -> 26.0 us (33.7 with the current tiles still on fp32 MFMAs).
 #include "kvq_internal.h"
 
 namespace kvq {

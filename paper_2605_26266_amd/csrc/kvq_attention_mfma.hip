@@ -169,7 +169,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
     u32x4 qop[kRB][8];  // B operands of the score MFMA: lane (n, hh) holds channels 16*slab + 8*hh .. +7 of rows n + 32 rb
     u32x4 rowop[kRB];   // B operand of the constant-term MFMA, per 32-row block
     int qp_scale[kRB] = {};
-    // (per-channel caches: one slab less, which takes the last reload out of the loop over stages, 10.0 -> 9.6 ms, see loader_tid)
+    // (per-channel caches: one slab less.  With two, a register is reloaded from scratch on every stage: 10.0 ms in place of 9.6 at
+    // 48 heads x 4096 rows x (65536 + 4096) keys, 16 blocks)
     constexpr int kLoRes = kLoF16 ? (PERCH ? 1 : KVQ_Q_LOW_RESIDENT_SLABS) : 0;
     u32x4 lo_res[kRB][kLoRes > 0 ? kLoRes : 1];
     const uint32_t lo_off = (uint32_t)((wave * kRowsPerWave + n) * kQRowWords + 4 * hh);  // words into q_stage
@@ -635,7 +636,8 @@ __global__ __launch_bounds__(kThreads, 1) void attention_mfma_kernel(AttentionAr
         const uint8_t *m_kscale8 = cv.k_scale8 + meta0, *m_vscale8 = cv.v_scale8 + meta0;
         const uint16_t *m_kzero16 = cv.k_zero16 + meta0, *m_vzero16 = cv.v_zero16 + meta0;
         // Per-channel 4-bit caches, whose kernel keeps registers in scratch: the thread's index is made anew at each use.  A reload of
-        // what follows from it would wait behind the prefetch loads on every stage (48 heads x 4096 rows x (65536 + 4096) keys, 16 blocks: 10.9 -> 10.0 ms).
+        // what follows from it would wait behind the prefetch loads on every stage (0.9 of 10 ms at 48 heads x 4096 rows x
+        // (65536 + 4096) keys, 16 blocks).
         const int wave_s = __builtin_amdgcn_readfirstlane(wave);
         auto loader_tid = [&]() {
             if constexpr (!(PERCH && !kFp4)) return tid;

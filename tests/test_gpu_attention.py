@@ -1,4 +1,7 @@
-"""GPU parity of kvq_chunk_attention against the CPU oracle (outputs and attention masses)."""
+"""GPU parity of kvq_chunk_attention against the CPU oracle (outputs and attention masses).
+
+Where a test over a few hundred rows or keys speaks of the matrix-core kernel of a BF16 / head_dim 128 format, it is the fp32 kernel
+that the call runs on; test_gpu_sixteen_bit.py repeats these tests on the 16-bit kernels."""
 import numpy as np
 import pytest
 import torch
@@ -30,7 +33,7 @@ def _fill(P, cache, w):
 @pytest.mark.parametrize("correction", [1, 0])
 @pytest.mark.parametrize("bits", [2, 4])
 def test_tiny_fp32(P, bits, correction):
-    """Tiny config, fp32 I/O: the fp32 vector kernel against the double oracle, all rows."""
+    """Tiny config, fp32 I/O: the fp32 matrix kernel against the double oracle, all rows."""
     import oracle
     from paper_2605_26266_amd import workloads as wl
     w = wl.WORKLOADS["tiny"].with_bits(bits)
@@ -575,7 +578,7 @@ def test_seeded_sweep_of_rings_and_windows(P):
 @pytest.mark.parametrize("causal", [False, True])
 def test_grouped_query_heads_and_causal_block(P, io, group, fp8, causal):
     """Partial-prefill shape: 6 query heads over 2 key/value heads, the current block causal.  Runs the
-    per-token and the group-wise matrix-core kernels (bf16) and the vector kernel (fp32 I/O)."""
+    fp32 matrix kernel on both I/O types (longer causal calls: test_gpu_sixteen_bit.py)."""
     import oracle
     from dataclasses import replace
     from paper_2605_26266_amd import binding as B, workloads as wl
